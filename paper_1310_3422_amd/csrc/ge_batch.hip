@@ -461,6 +461,11 @@ __device__ __forceinline__ void run_task_halo(const BatchArgs &a, const BatchTas
 #pragma unroll
         for (int j = 0; j < K; ++j) e[j] = T(0);
     }
+    // Neighbouring windows overlap and the rod is advanced in place: every
+    // wave's loads have to be in before any wave stores (calls of fewer than
+    // K levels pass no other barrier).
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
     switch (__builtin_amdgcn_readfirstlane(mode)) {
     case 1: halo_blocks<T, K, COMP, 1>(a, rd, w, wr, ws, aL, aR, hasL, hasR, s, e, hx, he); break;
     case 3: halo_blocks<T, K, COMP, 3>(a, rd, w, wr, ws, aL, aR, hasL, hasR, s, e, hx, he); break;
