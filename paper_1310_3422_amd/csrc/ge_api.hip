@@ -82,6 +82,8 @@ bool status_take(StatusWords &w, int word)
 SchemeCoef scheme_coef(double r)
 {
     SchemeCoef c;
+    c.r = r;
+    c.k = r / (1.0 + 2.0 * r);
     c.c1 = (r + r * r) / (1.0 + 2.0 * r);
     c.c2 = (r * r) / (1.0 + 2.0 * r);
     c.cs = r / (1.0 + r);
@@ -179,7 +181,8 @@ struct ge_plan_s {
     int sdc;       // sub-domain width k >= 2 (the sub-domain scheme), or 0
     double g_left, g_right;
     const void *src_b;
-    double c1, c2, cs, e1, e2, es, tau, h;
+    ge::SchemeCoef sc;
+    double e1, e2, es, tau, h;
     ge::StatusWords status;   // word 0: a launch stored a NaN or infinite value
     bool launched;            // a kernel may hold the status pointer
     ge::SideStream side;      // wall kernel of split launches (side_state 1)
@@ -189,7 +192,7 @@ struct ge_plan_s {
 namespace {
 
 
-// Fewest tiles at which a plan keeps a second stream for split launches
+// Fewest tiles at which a plan of the pair keeps a second stream for split launches
 // (the split itself starts at 128 interior tiles per compute unit).
 constexpr int64_t kSideStreamTiles = 128 * 64;
 
@@ -322,10 +325,7 @@ ge_status plan_sdc(ge_plan_t *out, const ge_desc *d)
     const double r = d->r;
     p->h = 1.0 / (double)(p->n + 1);
     p->tau = r * p->h * p->h;
-    const ge::SchemeCoef sc = ge::scheme_coef(r);
-    p->c1 = sc.c1;
-    p->c2 = sc.c2;
-    p->cs = sc.cs;
+    p->sc = ge::scheme_coef(r);
     p->e1 = (1.0 - r) / (1.0 + r);       // the sweep's own-value weight
     p->e2 = p->es = 0.0;
     (void)ge::status_alloc(p->status);
@@ -456,20 +456,17 @@ ge_status ge_plan(ge_plan_t *out, const ge_desc *d)
     const double r = p->r;
     p->h = 1.0 / (double)(p->n + 1);
     p->tau = r * p->h * p->h;
-    const ge::SchemeCoef sc = ge::scheme_coef(r);
-    p->c1 = sc.c1;
-    p->c2 = sc.c2;
-    p->cs = sc.cs;
+    p->sc = ge::scheme_coef(r);
     p->e1 = p->tau * (1.0 + r) / (1.0 + 2.0 * r);
     p->e2 = p->tau * r / (1.0 + 2.0 * r);
     p->es = p->tau / (1.0 + r);
     (void)ge::status_alloc(p->status);
-    // Per-tile launches over many tiles may split off their wall tiles: a
+    // The pair's per-tile launches over many tiles may split off their wall tiles: a
     // second stream (default priority) lets the wall kernel run beside the
     // interior one; without it (not created) they run one after the other.
     // Made here, not at the first step, so that a step can be captured into
     // a graph.
-    if (!p->persistent && !p->single && p->ntiles >= kSideStreamTiles)
+    if (prec == ge::kFP32C && !p->persistent && !p->single && p->ntiles >= kSideStreamTiles)
         p->side_state = side_create(p->side) ? 1 : -1;
     *out = p;
     return GE_OK;
@@ -564,7 +561,8 @@ ge_status ge_step_n(ge_plan_t plan, void *u, void *workspace, int64_t step0, int
     a.halo = plan->halo;
     a.estride = plan->prec == ge::kFP32C ? ge::comp_offset(plan->n) : 0;
     a.estride_out = a.estride;
-    a.c1 = plan->c1; a.c2 = plan->c2; a.cs = plan->cs;
+    a.r = plan->sc.r; a.k = plan->sc.k; a.cs = plan->sc.cs;
+    a.c1 = plan->sc.c1; a.c2 = plan->sc.c2;
     a.e1 = plan->e1; a.e2 = plan->e2; a.es = plan->es;
     a.gl0 = plan->g_left; a.gr0 = plan->g_right;
     a.tau = plan->tau; a.h = plan->h;

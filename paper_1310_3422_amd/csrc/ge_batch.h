@@ -12,7 +12,8 @@ constexpr int kBatchWaves = 16;   // waves per workgroup of the batch kernel
 struct BatchRod {
     int64_t off;              // element offset of the rod's first point in u
     int64_t n;                // interior points
-    double c1, c2, cs;        // (r+r^2)/(1+2r), r^2/(1+2r), r/(1+r)
+    double r, k, cs;          // r, r/(1+2r), r/(1+r)
+    double c1, c2;            // (r+r^2)/(1+2r), r^2/(1+2r)
     double gl, gr;            // constant wall values
     int64_t woff;             // rod above the on-chip limit: element offset of
                               // its second level buffer in u2; else -1
@@ -66,10 +67,11 @@ __host__ __device__ inline int halo_waves(int64_t n, int k)
 }
 
 // Where the waves of a halo task's rod start: wave j at 62 k j, except the
-// last, which ends at the right wall node rounded up to a 16-byte boundary
-// (so its start stays even and aligned).  `fits`: the rod has two or more
-// waves and the last window does not reach into its neighbour's duplicated
-// lane; only such rods go to halo tasks.
+// last, which ends at the right wall (its start may be any element: it reads
+// and writes its points one by one, and pairs them the other way round when
+// it starts at an odd one).  `fits`: the rod has two or more waves and the
+// last window does not reach into its neighbour's duplicated lane; only such
+// rods go to halo tasks.
 struct HaloLayout {
     int64_t n;
     int k, m;
@@ -80,7 +82,7 @@ struct HaloLayout {
         last = (int64_t)(m - 1) * 62 * k;
         fits = false;
         if (m >= 2) {
-            const int64_t r = (n - 64 * (int64_t)k + 3) / 4 * 4;
+            const int64_t r = n - 64 * (int64_t)k;
             const int64_t need = m == 2 ? 0 : (int64_t)(m - 2) * 62 * k + k;
             if (r >= need) {
                 last = r;

@@ -7,7 +7,7 @@
 // held entirely in registers for all levels, so a rod is read and written
 // once per launch.  Per level the waves of a rod exchange their edge values
 // through LDS (one workgroup barrier per level) and the per-point update is
-// the shared ge_level (ge_level.h), so every rod evolves bit for bit as it
+// the shared one (ge_level.h), so every rod evolves bit for bit as it
 // does through ge_step_n.  The queue counter is reset by a kernel node, and
 // the reset and the sweep are captured in a hipGraph that later calls
 // replay.
@@ -82,29 +82,11 @@ __device__ __forceinline__ void rod_levels(const BatchArgs &a, const BatchRod &r
     const bool has_S = (qS >= 0) && (qS < (int64_t)kWave * K);
     const int kS = has_S ? (int)(qS % K) : 0;
     const int lS = has_S ? (int)(qS / K) : -1;
-    T gl_hi, gl_lo, gr_hi, gr_lo;
-    split_wall<T, COMP>(rd.gl, gl_hi, gl_lo);
-    split_wall<T, COMP>(rd.gr, gr_hi, gr_lo);
-    const Coef<T> cf = lane_coef(Coef<T>{(T)rd.c1, (T)rd.c2, (T)rd.cs, T(0), T(0), T(0)});
-    const T b0[K] = {};
-    FluxTap ft{false, 0.0, 0.0, 1.0, 0.0};
-
-    for_levels(a.step0, a.nsteps, [&](auto par, int lev) {
-        constexpr int p = decltype(par)::value;
-        if (WALL && ghost_in) {
-            put_at<T, K>(s, kR, lane == lR, gr_hi);
-            if constexpr (COMP) put_at<T, K>(e, kR, lane == lR, gr_lo);
-        }
-        const int pb = lev & 1;
-        if (lane == 0) { xs[pb][w][0] = s[0]; xs[pb][w][1] = s[1]; }
-        if (lane == kWave - 1) { xs[pb][w][2] = s[K - 2]; xs[pb][w][3] = s[K - 1]; }
-        if constexpr (COMP) {
-            if (lane == 0) { xe[pb][w][0] = e[0]; xe[pb][w][1] = e[1]; }
-            if (lane == kWave - 1) { xe[pb][w][2] = e[K - 2]; xe[pb][w][3] = e[K - 1]; }
-        }
+    // meet: publish the wave's edges of this level (the caller has written
+    // them to LDS), then wait for the neighbours' edges
+    auto meet = [&](int lev) {
         if constexpr (NBR) {
-            // publish this level's edges (the release orders the writes
-            // above before the flag), then wait for the neighbours' edges
+            // the release orders the edge writes before the flag
             const int tag = lev + 1;   // lev counts this call's levels from 0
             if (lane == 0)
                 __hip_atomic_store(&lvl[w], tag, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
@@ -113,31 +95,101 @@ __device__ __forceinline__ void rod_levels(const BatchArgs &a, const BatchRod &r
         } else {
             __syncthreads();
         }
-        const int wl = w > 0 ? w - 1 : 0, wrr = w < kWaves - 1 ? w + 1 : kWaves - 1;
-        T xl = xs[pb][wl][3], xr = xs[pb][wrr][0], xl2 = xs[pb][wl][2], xr2 = xs[pb][wrr][1];
-        T yl = T(0), yr = T(0), yl2 = T(0), yr2 = T(0);
-        if constexpr (COMP) {
-            yl = xe[pb][wl][3]; yr = xe[pb][wrr][0]; yl2 = xe[pb][wl][2]; yr2 = xe[pb][wrr][1];
+    };
+    const int wl = w > 0 ? w - 1 : 0, wrr = w < kWaves - 1 ? w + 1 : kWaves - 1;
+    T gl_hi, gl_lo, gr_hi, gr_lo;
+    split_wall<T, COMP>(rd.gl, gl_hi, gl_lo);
+    split_wall<T, COMP>(rd.gr, gr_hi, gr_lo);
+
+    if constexpr (!COMP) {
+        // FP64 meets its neighbours with one value a side, FP32 with two
+        constexpr bool TWO_STAGE = sizeof(T) == 8;
+        constexpr int E = TWO_STAGE ? 1 : 2;
+        const Coef<T> cf = lane_coef(Coef<T>{(T)rd.r, (T)rd.k, (T)rd.c1, (T)rd.cs});
+        const bool lane_l = WALL && left_wall && lane == 0;
+        const bool lane_r = WALL && ghost_edge && lane == kWave - 1;
+        const T kl = lane_l ? cf.cs : cf.k, kr = lane_r ? cf.cs : cf.k;
+        const T cl = lane_l ? cf.cs : cf.c1, cr = lane_r ? cf.cs : cf.c1;
+        const T pl = lane_l ? T(0) : cf.cs, pr = lane_r ? T(0) : cf.cs;
+        auto exchange = [&](int lev, T (&xl)[E], T (&xr)[E]) {
+            const int pb = lev & 1;
+#pragma unroll
+            for (int i = 0; i < E; ++i) {
+                if (lane == 0) xs[pb][w][i] = s[i];
+                if (lane == kWave - 1) xs[pb][w][2 + i] = s[K - 1 - i];
+            }
+            meet(lev);
+#pragma unroll
+            for (int i = 0; i < E; ++i) {
+                xl[i] = xs[pb][wl][2 + i];
+                xr[i] = xs[pb][wrr][i];
+                if constexpr (WALL) {
+                    if (left_wall) xl[i] = gl_hi;
+                    if (ghost_edge) xr[i] = gr_hi;
+                }
+            }
+        };
+        for_levels(a.step0, a.nsteps, [&](auto par, int lev) {
+            constexpr int P = decltype(par)::value;
+            T xl[E] = {}, xr[E] = {};
+            if (WALL && ghost_in) put_at<T, K>(s, kR, lane == lR, gr_hi);
+            // the point beside a wall node inside the wave, when it is alone
+            const bool single = WALL && has_S && !ghost_edge && (((n - 1 + P) & 1) == 0);
+            T lone = T(0);
+            if constexpr (TWO_STAGE) {
+                if constexpr (P == 0) exchange(lev, xl, xr);
+                explicit_stage<T, K, P, false>(s, xl[0], xr[0], cf);
+                if constexpr (P == 1) exchange(lev, xl, xr);
+                if (WALL && single) lone = lone_point(get_at<T, K>(s, kS, T(0)), gr_hi, cf.cs);
+                solve_stage<T, K, P, false>(s, xl[0], xr[0], cf, kl, kr);
+            } else {
+                exchange(lev, xl, xr);
+                if (WALL && single)
+                    lone = lone_increment<T, K, false>(s, s, T(0), kS, xl[0], gr_hi, cf.cs);
+                increment_level<T, K, false, P, false>(s, s, T(0), xl[0], xl[E - 1], xr[0],
+                                                       xr[E - 1], cf, cl, pl, cr, pr);
+            }
+            if (WALL && single) put_at<T, K>(s, kS, lane == lS, lone);
+        });
+        return;
+    } else {
+    const PairCoef<T> cf = lane_coef(PairCoef<T>{(T)rd.c1, (T)rd.c2, (T)rd.cs, T(0), T(0), T(0)});
+    const T b0[K] = {};
+    FluxTap ft{false, 0.0, 0.0, 1.0, 0.0};
+
+    for_levels(a.step0, a.nsteps, [&](auto par, int lev) {
+        constexpr int p = decltype(par)::value;
+        if (WALL && ghost_in) {
+            put_at<T, K>(s, kR, lane == lR, gr_hi);
+            put_at<T, K>(e, kR, lane == lR, gr_lo);
         }
+        const int pb = lev & 1;
+        if (lane == 0) { xs[pb][w][0] = s[0]; xs[pb][w][1] = s[1]; }
+        if (lane == kWave - 1) { xs[pb][w][2] = s[K - 2]; xs[pb][w][3] = s[K - 1]; }
+        if (lane == 0) { xe[pb][w][0] = e[0]; xe[pb][w][1] = e[1]; }
+        if (lane == kWave - 1) { xe[pb][w][2] = e[K - 2]; xe[pb][w][3] = e[K - 1]; }
+        meet(lev);
+        T xl = xs[pb][wl][3], xr = xs[pb][wrr][0], xl2 = xs[pb][wl][2], xr2 = xs[pb][wrr][1];
+        T yl = xe[pb][wl][3], yr = xe[pb][wrr][0], yl2 = xe[pb][wl][2], yr2 = xe[pb][wrr][1];
         WallLevel<T> wlv{false, T(0)};
         bool singR = false;
         if constexpr (WALL) {
-            if (left_wall) { xl = gl_hi; if constexpr (COMP) yl = gl_lo; }
-            if (ghost_edge) { xr = gr_hi; if constexpr (COMP) yr = gr_lo; }
+            if (left_wall) { xl = gl_hi; yl = gl_lo; }
+            if (ghost_edge) { xr = gr_hi; yr = gr_lo; }
             wlv.isL = left_wall && (p == 1) && (lane == 0);
             singR = has_S && (((n - 1 + p) & 1) == 0);
         }
         Lone<T> lone{T(0), T(0)};
         if (WALL && singR)
-            lone = right_lone<T, K, COMP, false>(s, e, b0, kS, xl, yl, gr_hi, gr_lo, T(0), cf,
-                                                 T(0));
-        ge_level<T, K, COMP, false, WALL, p>(s, e, b0, T(0), T(0), xl, xl2, xr, xr2, yl, yl2,
-                                             yr, yr2, cf, T(0), wlv, ft);
+            lone = right_lone<T, K, false>(s, e, b0, kS, xl, yl, gr_hi, gr_lo, T(0), cf, T(0));
+        pair_level<T, K, 0, WALL, p>(s, e, b0, T(0), T(0), xl, xl2, xr, xr2, yl, yl2, yr, yr2, cf,
+                                     T(0), wlv, ft);
         if (WALL && singR) {
             put_at<T, K>(s, kS, lane == lS, lone.s);
-            if constexpr (COMP) put_at<T, K>(e, kS, lane == lS, lone.e);
+            put_at<T, K>(e, kS, lane == lS, lone.e);
         }
     });
+    }
 }
 
 // Barrier mode: every wave of the workgroup executes the same number of
@@ -173,7 +225,7 @@ __device__ __forceinline__ void run_task(const BatchArgs &a, const BatchTask &tk
         if constexpr (COMP) load_lane_guarded<T, K>(ue + g0, g0, rd.n, e);
     } else {
         rd.n = (int64_t)kWave * K;
-        rd.c1 = rd.c2 = rd.cs = 0.0;
+        rd.r = rd.k = rd.c1 = rd.c2 = rd.cs = 0.0;
 #pragma unroll
         for (int j = 0; j < K; ++j) s[j] = T(0);
     }
@@ -210,132 +262,67 @@ __device__ __forceinline__ void run_task(const BatchArgs &a, const BatchTask &tk
 // every level.
 //
 // Walls stay exact at the rod's ends.  The first wave starts at the left
-// wall, which enters as the fill of its lane 0.  The last wave is placed so
-// that the right wall node falls at (or within three points of) the end of
-// its window, at a fixed element of lane 63: that costs a select or two per
-// level, where a wall node at a data-dependent element costs a branch tree
-// per access.  It then overlaps its neighbour by more than one lane, and the
-// refresh copies values by position: the writer's lanes covering the
+// wall, which enters as the fill of its lane 0, and the last wave ends at the
+// right wall, the fill of its lane 63, so neither costs anything inside the
+// levels (a wall node at a data-dependent element costs a branch tree per
+// access).  The last wave then overlaps its neighbour by more than one lane,
+// and the refresh copies values by position: the writer's lanes covering the
 // positions store them to LDS, the reader takes k values at the offset.
 // When the last window would reach into its neighbour's duplicated lane (a
-// 1-in-62 case), or the rod has one wave, the wall node stays where the
-// regular placement puts it.
+// 1-in-62 case), or the rod has one wave, the rod goes to another task.
 constexpr int kMaxBatchK = 64;
 constexpr int kSlot = 2 * kMaxBatchK;    // values per exchange slot (two lanes)
 
-template <typename T, int K, bool COMP, bool WALL>
-__device__ __forceinline__ void rod_block(const BatchRod &rd, int wr, int64_t ws, T (&s)[K],
-                                          T (&e)[K], int64_t level0, int nlev)
+// One wave of a rod of several: END 0 = both window edges open, 1 = the
+// window starts at the left wall (it enters as the fill of lane 0, whose
+// first point stands alone at odd levels), 2 = it ends at the right wall
+// (the fill of lane 63).  level0's parity is the window's: a window that
+// starts at an odd point pairs its points the other way round.
+template <typename T, int K, bool COMP, int END>
+__device__ __forceinline__ void rod_block(const BatchRod &rd, T (&s)[K], T (&e)[K],
+                                          int64_t level0, int nlev)
 {
     const int lane = threadIdx.x & (kWave - 1);
-    const int64_t n = rd.n;
-    const int64_t q = n - ws;                         // window position of the right wall node
-    const bool left_wall = (wr == 0);
-    const bool ghost_in = (q >= 0) && (q < (int64_t)kWave * K);
-    const bool ghost_edge = (q == (int64_t)kWave * K);
-    const int kR = ghost_in ? (int)(q % K) : 0;
-    const int lR = ghost_in ? (int)(q / K) : -1;
-    const int64_t qS = q - 1;
-    const bool has_S = (qS >= 0) && (qS < (int64_t)kWave * K);
-    const int kS = has_S ? (int)(qS % K) : 0;
-    const int lS = has_S ? (int)(qS / K) : -1;
-    T gl_hi, gl_lo, gr_hi, gr_lo;
-    split_wall<T, COMP>(rd.gl, gl_hi, gl_lo);
-    split_wall<T, COMP>(rd.gr, gr_hi, gr_lo);
-    const Coef<T> cf = lane_coef(Coef<T>{(T)rd.c1, (T)rd.c2, (T)rd.cs, T(0), T(0), T(0)});
-    const T b0[K] = {};
-    FluxTap ft{false, 0.0, 0.0, 1.0, 0.0};
-
-    for_levels(level0, nlev, [&](auto par, int) {
-        constexpr int p = decltype(par)::value;
-        if (WALL && ghost_in) {
-            put_at<T, K>(s, kR, lane == lR, gr_hi);
-            if constexpr (COMP) put_at<T, K>(e, kR, lane == lR, gr_lo);
+    T g, gx;   // the wall's value, and its compensation
+    split_wall<T, COMP>(END == 1 ? rd.gl : rd.gr, g, gx);
+    if constexpr (!COMP) {
+        const Coef<T> cf = lane_coef(Coef<T>{(T)rd.r, (T)rd.k, (T)rd.c1, (T)rd.cs});
+        const bool lane_l = END == 1 && lane == 0, lane_r = END == 2 && lane == kWave - 1;
+        if constexpr (sizeof(T) == 8) {
+            const T kl = lane_l ? cf.cs : cf.k, kr = lane_r ? cf.cs : cf.k;
+            for_levels(level0, nlev, [&](auto par, int) {
+                constexpr int P = decltype(par)::value;
+                explicit_stage<T, K, P, END == 0>(s, g, g, cf);
+                solve_stage<T, K, P, END == 0>(s, g, g, cf, kl, kr);
+            });
+        } else {
+            const T cl = lane_l ? cf.cs : cf.c1, cr = lane_r ? cf.cs : cf.c1;
+            const T pl = lane_l ? T(0) : cf.cs, pr = lane_r ? T(0) : cf.cs;
+            for_levels(level0, nlev, [&](auto par, int) {
+                increment_level<T, K, false, decltype(par)::value, END == 0>(s, s, T(0), g, g, g, g,
+                                                                             cf, cl, pl, cr, pr);
+            });
         }
-        // fills at a wall edge are the wall value; at an open edge they
-        // only reach the duplicated lane
-        T xl = T(0), xr = T(0), yl = T(0), yr = T(0);
-        WallLevel<T> wlv{false, T(0)};
-        bool singR = false;
-        if constexpr (WALL) {
-            if (left_wall) { xl = gl_hi; if constexpr (COMP) yl = gl_lo; }
-            if (ghost_edge) { xr = gr_hi; if constexpr (COMP) yr = gr_lo; }
-            wlv.isL = left_wall && (p == 1) && (lane == 0);
-            singR = has_S && (((n - 1 + p) & 1) == 0);
-        }
-        Lone<T> lone{T(0), T(0)};
-        if (WALL && singR)
-            lone = right_lone<T, K, COMP, false>(s, e, b0, kS, xl, yl, gr_hi, gr_lo, T(0), cf,
-                                                 T(0));
-        ge_level<T, K, COMP, false, WALL, p, !WALL>(s, e, b0, T(0), T(0), xl, T(0), xr, T(0), yl,
-                                                    T(0), yr, T(0), cf, T(0), wlv, ft);
-        if (WALL && singR) {
-            put_at<T, K>(s, kS, lane == lS, lone.s);
-            if constexpr (COMP) put_at<T, K>(e, kS, lane == lS, lone.e);
-        }
-    });
-}
-
-// The last wave of a rod with its window ending RQ points (0..3) past the
-// right wall node: the node is element K - RQ of lane 63 (RQ = 0: just
-// beyond the window, the fill of lane 63), the lone point beside it element
-// K - 1 - RQ.  Both indices are compile-time constants.  The window start
-// is even, so the local pairing is the global one.
-template <typename T, int K, bool COMP, int RQ>
-__device__ __forceinline__ void rod_block_right(const BatchRod &rd, T (&s)[K], T (&e)[K],
-                                                int64_t level0, int nlev)
-{
-    const int lane = threadIdx.x & (kWave - 1);
-    const int64_t n = rd.n;
-    T gr_hi, gr_lo;
-    split_wall<T, COMP>(rd.gr, gr_hi, gr_lo);
-    const Coef<T> cf = lane_coef(Coef<T>{(T)rd.c1, (T)rd.c2, (T)rd.cs, T(0), T(0), T(0)});
-    const T b0[K] = {};
-    FluxTap ft{false, 0.0, 0.0, 1.0, 0.0};
-    const WallLevel<T> wlv{false, T(0)};
-    constexpr int kS = K - 1 - RQ;
-    const bool lone_odd = ((n - 1) & 1) == 0;   // the lone point exists at even global parity
-    for_levels(level0, nlev, [&](auto par, int) {
-        constexpr int p = decltype(par)::value;
-        if constexpr (RQ > 0) {
-            put_at<T, K>(s, K - RQ, lane == kWave - 1, gr_hi);
-            if constexpr (COMP) put_at<T, K>(e, K - RQ, lane == kWave - 1, gr_lo);
-        }
-        const T xr = RQ == 0 ? gr_hi : T(0), yr = (RQ == 0 && COMP) ? gr_lo : T(0);
-        const bool singR = lone_odd == (p == 0);
-        Lone<T> lone{T(0), T(0)};
-        if (singR)
-            lone = right_lone<T, K, COMP, false>(s, e, b0, kS, T(0), T(0), gr_hi, gr_lo, T(0), cf,
-                                                 T(0));
-        ge_level<T, K, COMP, false, false, p, false>(s, e, b0, T(0), T(0), T(0), T(0), xr, T(0),
-                                                     T(0), T(0), yr, T(0), cf, T(0), wlv, ft);
-        if (singR) {
-            put_at<T, K>(s, kS, lane == kWave - 1, lone.s);
-            if constexpr (COMP) put_at<T, K>(e, kS, lane == kWave - 1, lone.e);
-        }
-    });
-}
-
-// The first wave of a rod that spans several: the left wall enters as the
-// fill of lane 0 and the lone point beside it is element 0 of lane 0; the
-// right edge is open.
-template <typename T, int K, bool COMP>
-__device__ __forceinline__ void rod_block_left(const BatchRod &rd, T (&s)[K], T (&e)[K],
-                                               int64_t level0, int nlev)
-{
-    const int lane = threadIdx.x & (kWave - 1);
-    T gl_hi, gl_lo;
-    split_wall<T, COMP>(rd.gl, gl_hi, gl_lo);
-    const Coef<T> cf = lane_coef(Coef<T>{(T)rd.c1, (T)rd.c2, (T)rd.cs, T(0), T(0), T(0)});
-    const T b0[K] = {};
-    FluxTap ft{false, 0.0, 0.0, 1.0, 0.0};
-    for_levels(level0, nlev, [&](auto par, int) {
-        constexpr int p = decltype(par)::value;
-        const WallLevel<T> wlv{p == 1 && lane == 0, T(0)};
-        ge_level<T, K, COMP, false, true, p, false>(s, e, b0, T(0), T(0), gl_hi, T(0), T(0), T(0),
-                                                    COMP ? gl_lo : T(0), T(0), T(0), T(0), cf,
-                                                    T(0), wlv, ft);
-    });
+    } else {
+        const PairCoef<T> cf =
+            lane_coef(PairCoef<T>{(T)rd.c1, (T)rd.c2, (T)rd.cs, T(0), T(0), T(0)});
+        const T b0[K] = {};
+        FluxTap ft{false, 0.0, 0.0, 1.0, 0.0};
+        for_levels(level0, nlev, [&](auto par, int) {
+            constexpr int p = decltype(par)::value;
+            const WallLevel<T> wlv{END == 1 && p == 1 && lane == 0, T(0)};
+            Lone<T> lone{T(0), T(0)};
+            // the window's last point has an odd place in it
+            if constexpr (END == 2 && p == 1)
+                lone = right_lone<T, K, false>(s, e, b0, K - 1, T(0), T(0), g, gx, T(0), cf, T(0));
+            pair_level<T, K, 0, END == 1, p, END == 0>(s, e, b0, T(0), T(0), g, T(0), g, T(0), gx,
+                                                       T(0), gx, T(0), cf, T(0), wlv, ft);
+            if constexpr (END == 2 && p == 1) {
+                s[K - 1] = lane == kWave - 1 ? lone.s : s[K - 1];
+                e[K - 1] = lane == kWave - 1 ? lone.e : e[K - 1];
+            }
+        });
+    }
 }
 
 // The levels of a halo-lane task for one wave, in blocks of K-1 levels with
@@ -346,14 +333,12 @@ __device__ __forceinline__ void rod_block_left(const BatchRod &rd, T (&s)[K], T 
 // that cover them, and the reader starts at the positions' offset within
 // the first.  aL / aR: window start of this wave minus the left neighbour's,
 // and of the right neighbour minus this wave's.  MODE: 0 = a wave without a
-// rod (it only passes the barriers), 1 = both window edges open, 2 = a wave
-// holding a wall at its regular place, 3 + RQ = the last wave ending RQ
-// points past the right wall node, 7 = the first wave of several.  Every wave of the workgroup passes the
-// same barriers (all rods of a task share K and the level count); the mode
+// rod (it only passes the barriers), 1 + END = a wave of rod_block's kinds.
+// Every wave of the workgroup passes the same barriers (all rods of a task share K and the level count); the mode
 // is chosen once per wave, outside the block loop, so each wave runs one
 // instantiation of the level code.
 template <typename T, int K, bool COMP, int MODE>
-__device__ __forceinline__ void halo_blocks(const BatchArgs &a, const BatchRod &rd, int w, int wr,
+__device__ __forceinline__ void halo_blocks(const BatchArgs &a, const BatchRod &rd, int w,
                                             int64_t ws, int aL, int aR, bool hasL, bool hasR,
                                             T (&s)[K], T (&e)[K], T *hx, T *he)
 {
@@ -368,12 +353,8 @@ __device__ __forceinline__ void halo_blocks(const BatchArgs &a, const BatchRod &
     int64_t done = 0;
     for (int blk = 0;; ++blk) {
         const int nb = (int)((a.nsteps - done) < (K - 1) ? (a.nsteps - done) : (K - 1));
-        if constexpr (MODE == 1)
-            rod_block<T, K, COMP, false>(rd, wr, ws, s, e, a.step0 + done, nb);
-        else if constexpr (MODE >= 3 && MODE <= 6)
-            rod_block_right<T, K, COMP, MODE - 3>(rd, s, e, a.step0 + done, nb);
-        else if constexpr (MODE == 7)
-            rod_block_left<T, K, COMP>(rd, s, e, a.step0 + done, nb);
+        if constexpr (MODE != 0)
+            rod_block<T, K, COMP, MODE - 1>(rd, s, e, a.step0 + (ws & 1) + done, nb);
         done += nb;
         if (done >= a.nsteps)
             break;
@@ -442,17 +423,25 @@ __device__ __forceinline__ void run_task_halo(const BatchArgs &a, const BatchTas
         lo = (wr == L.m - 1 && wr > 0) ? L.start(wr - 1) + 63 * K : 0;
         // the planner gives halo tasks only rods of two or more waves whose
         // last window ends at the wall
-        if (!hasR)
-            mode = 3 + (int)(ws + 64 * K - rd.n);   // RQ in 0..3
-        else
-            mode = wr == 0 ? 7 : 1;
+        mode = !hasR ? 3 : (wr == 0 ? 2 : 1);
         us = static_cast<T *>(a.u) + rd.off;
         ue = static_cast<T *>(a.u) + a.estride + rd.off;
     }
     const int64_t g0 = ws + (int64_t)lane * K;
     if (rod >= 0) {
-        load_lane_guarded<T, K>(us + g0, g0, rd.n, s);
-        if constexpr (COMP) load_lane_guarded<T, K>(ue + g0, g0, rd.n, e);
+        // every window of the rod lies inside it; the last one's start need
+        // not be aligned
+        if (hasR) {
+            load_lane<T, K>(us + g0, s);
+            if constexpr (COMP) load_lane<T, K>(ue + g0, e);
+        } else {
+#pragma unroll
+            for (int j = 0; j < K; ++j) s[j] = us[g0 + j];
+            if constexpr (COMP) {
+#pragma unroll
+                for (int j = 0; j < K; ++j) e[j] = ue[g0 + j];
+            }
+        }
     } else {
 #pragma unroll
         for (int j = 0; j < K; ++j) s[j] = T(0);
@@ -467,20 +456,20 @@ __device__ __forceinline__ void run_task_halo(const BatchArgs &a, const BatchTas
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
     switch (__builtin_amdgcn_readfirstlane(mode)) {
-    case 1: halo_blocks<T, K, COMP, 1>(a, rd, w, wr, ws, aL, aR, hasL, hasR, s, e, hx, he); break;
-    case 3: halo_blocks<T, K, COMP, 3>(a, rd, w, wr, ws, aL, aR, hasL, hasR, s, e, hx, he); break;
-    case 4: halo_blocks<T, K, COMP, 4>(a, rd, w, wr, ws, aL, aR, hasL, hasR, s, e, hx, he); break;
-    case 5: halo_blocks<T, K, COMP, 5>(a, rd, w, wr, ws, aL, aR, hasL, hasR, s, e, hx, he); break;
-    case 6: halo_blocks<T, K, COMP, 6>(a, rd, w, wr, ws, aL, aR, hasL, hasR, s, e, hx, he); break;
-    case 7: halo_blocks<T, K, COMP, 7>(a, rd, w, wr, ws, aL, aR, hasL, hasR, s, e, hx, he); break;
-    default: halo_blocks<T, K, COMP, 0>(a, rd, w, wr, ws, aL, aR, hasL, hasR, s, e, hx, he); break;
+    case 1: halo_blocks<T, K, COMP, 1>(a, rd, w, ws, aL, aR, hasL, hasR, s, e, hx, he); break;
+    case 2: halo_blocks<T, K, COMP, 2>(a, rd, w, ws, aL, aR, hasL, hasR, s, e, hx, he); break;
+    case 3: halo_blocks<T, K, COMP, 3>(a, rd, w, ws, aL, aR, hasL, hasR, s, e, hx, he); break;
+    default: halo_blocks<T, K, COMP, 0>(a, rd, w, ws, aL, aR, hasL, hasR, s, e, hx, he); break;
     }
     // lanes 1..62, lane 0 of the first wave and lane 63 of the last (the last
     // wave from its neighbour's core end on)
     T fin = T(0);
-    if (rod >= 0 && (lane > 0 || wr == 0) && (lane < kWave - 1 || !hasR)) {
-        store_lane_range<T, K>(us + g0, g0, lo, rd.n, s, fin);
-        if constexpr (COMP) store_lane_range<T, K>(ue + g0, g0, lo, rd.n, e, fin);
+    if (rod >= 0 && hasR && (lane > 0 || wr == 0) && lane < kWave - 1) {
+        store_lane_chunks<T, K>(us + g0, g0, 0, rd.n, s, fin);
+        if constexpr (COMP) store_lane_chunks<T, K>(ue + g0, g0, 0, rd.n, e, fin);
+    } else if (rod >= 0 && !hasR) {
+        store_lane_guarded<T, K>(us + g0, g0, lo, rd.n, s, fin);
+        if constexpr (COMP) store_lane_guarded<T, K>(ue + g0, g0, lo, rd.n, e, fin);
     }
     if (rod >= 0) raise_if_nonfinite(a.status, fin);
     __syncthreads();   // LDS slots are reused by the next task
@@ -509,6 +498,8 @@ __device__ __forceinline__ void run_task_long(const BatchArgs &a, const BatchTas
     ta.halo = a.long_halo;
     ta.core = W - 2 * (int64_t)a.long_halo;
     ta.ntiles = (rd.n + ta.core - 1) / ta.core;
+    ta.r = rd.r;
+    ta.k = rd.k;
     ta.c1 = rd.c1;
     ta.c2 = rd.c2;
     ta.cs = rd.cs;
@@ -530,13 +521,7 @@ __device__ __forceinline__ void run_task_long(const BatchArgs &a, const BatchTas
         ta.estride_out = (ps & 1) ? a.estride : a.estride2;
         ta.level0 = a.step0 + done;
         ta.nlev = lev;
-        for (int64_t t = w; t < ta.ntiles; t += kWaves) {
-            const int64_t ws = t == 0 ? 0 : t * ta.core - ta.halo;
-            if (ws == 0 || ws + W >= rd.n)
-                run_tile<T, K, 1, COMP, false, true>(ta, lane, t, ws);
-            else
-                run_tile<T, K, 1, COMP, false, false>(ta, lane, t, ws);
-        }
+        for (int64_t t = w; t < ta.ntiles; t += kWaves) run_tile<T, K, 1, COMP, false>(ta, lane, t);
         // the next pass reads what every wave stored (same workgroup: the
         // barrier orders the global stores before the loads)
         __syncthreads();

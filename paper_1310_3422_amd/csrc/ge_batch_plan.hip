@@ -381,6 +381,12 @@ void free_batch(ge_batch_s *b)
     delete b;
 }
 
+BatchRod batch_rod(int64_t off, int64_t n, const ge::SchemeCoef &sc, double gl, double gr,
+                   int64_t woff)
+{
+    return BatchRod{off, n, sc.r, sc.k, sc.cs, sc.c1, sc.c2, gl, gr, woff};
+}
+
 // Time one run of the batch kernel (synchronisation mode `sync`) on a
 // synthetic batch whose tasks are all K-point-per-lane tasks; returns
 // microseconds per level per task.
@@ -401,7 +407,7 @@ double time_tasks(int prec, int sync, int k, bool walls, int grid, void *u, size
     if ((size_t)(stride * rods.size() * esz * (prec == ge::kFP32C ? 2 : 1)) > ubytes) return -1;
     const ge::SchemeCoef sc = ge::scheme_coef(2.0);
     for (size_t i = 0; i < rods.size(); ++i)
-        rods[i] = BatchRod{(int64_t)i * stride, rod_n, sc.c1, sc.c2, sc.cs, 0.25, -0.5, -1};
+        rods[i] = batch_rod((int64_t)i * stride, rod_n, sc, 0.25, -0.5, -1);
     for (int t = 0; t < ntasks; ++t) {
         memset(&tasks[t], 0, sizeof(BatchTask));
         tasks[t].k = k;
@@ -581,8 +587,8 @@ ge_status ge_batch_plan(ge_batch_t *out, const ge_batch_desc *d)
     for (int64_t i = 0; i < d->nrods; ++i) {
         const ge::SchemeCoef sc = ge::scheme_coef(d->r[i]);
         const bool lng = d->n[i] > on_chip_cap(prec);
-        rods[i] = BatchRod{d->offsets[i], d->n[i], sc.c1, sc.c2, sc.cs, d->g_left[i],
-                           d->g_right[i], lng ? woff : -1};
+        rods[i] = batch_rod(d->offsets[i], d->n[i], sc, d->g_left[i], d->g_right[i],
+                            lng ? woff : -1);
         if (lng) woff += (d->n[i] + 63) / 64 * 64;
     }
     b->long_elems = woff;

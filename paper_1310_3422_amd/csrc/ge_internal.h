@@ -17,7 +17,8 @@ ge_status vset_error(ge_status st, const char *fmt, va_list ap);
 // by the same expressions for every entry point (single rod and batch), so
 // both paths feed the kernels identical values.
 struct SchemeCoef {
-    double c1, c2, cs;   // (r+r^2)/(1+2r), r^2/(1+2r), r/(1+r)
+    double r, k, cs;     // r, r/(1+2r), r/(1+r)
+    double c1, c2;       // (r+r^2)/(1+2r), r^2/(1+2r)
 };
 SchemeCoef scheme_coef(double r);
 

@@ -32,8 +32,9 @@ struct TileArgs {
     int64_t estride_out;     // FP32C: element offset of the e block of `out`
     int32_t halo;            // window points each side of the core
     int32_t nlev;            // levels advanced by this launch
-    double c1, c2, cs;       // (r+r^2)/(1+2r), r^2/(1+2r), r/(1+r)
-    double e1, e2, es;       // tau(1+r)/(1+2r), tau r/(1+2r), tau/(1+r)
+    double r, k, cs;         // r, r/(1+2r), r/(1+r)
+    double c1, c2;           // (r+r^2)/(1+2r), r^2/(1+2r)
+    double e1, e2, es;       // pair: tau(1+r)/(1+2r), tau r/(1+2r), tau/(1+r)
     double gl0, gr0;         // constant walls (used when gl_t / gr_t are null)
     double tau, h;           // for the wall-flux diagnostic
     // sub-domain scheme (launch_sdc): core and halo count sub-domain
@@ -48,9 +49,10 @@ struct TileArgs {
 // Supported (precision, points per lane, waves per workgroup) choices.
 bool tile_config_supported(int prec, int k, int nw);
 
-// A second stream and two events on which a launch that splits its wall
-// tiles from its interior tiles runs the wall kernel beside the interior
-// one (forked from and joined back into the launch stream).
+// A second stream and two events on which a launch of the compensated pair
+// that splits its wall tiles from its interior tiles runs the wall kernel
+// beside the interior one (forked from and joined back into the launch
+// stream).
 struct SideStream {
     hipStream_t stream;
     hipEvent_t fork, join;

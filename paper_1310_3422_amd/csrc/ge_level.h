@@ -3,24 +3,44 @@
 //
 // Scheme (Section 2, two-point groups): at level m with p = m mod 2 the
 // points are coupled as (0,1),(2,3),... (0-based) when p = 0 and
-// (1,2),(3,4),... when p = 1.  A coupled pair solved by the confluence
-// formulas Eq. (3)/(4) is written here in the equivalent second-difference
-// form: with D_i = u_{i-1} - 2u_i + u_{i+1},
-//     u_i' = u_i + c1 D_i + c2 D_q,   c1 = (r+r^2)/(1+2r), c2 = r^2/(1+2r),
-// where q is i's partner.  A point alone beside a wall (point 0 when p = 1,
-// point n-1 when n-1+p is even) takes scheme A, Eq. (1), or scheme B,
-// Eq. (2), in the same form: u_i' = u_i + cs (D_i + g(t_{m+1}) - g(t_m)),
-// cs = r/(1+r), where D_i used the wall value at t_m.  A source f = a(t) b(x)
-// adds a(t_m + tau/2) (e1 b_i + e2 b_q) to a pair member and
-// a(t_m + tau/2) es b_i to a lone point.
+// (1,2),(3,4),... when p = 1.
 //
-// D_i is formed from first differences d_i = u_{i+1} - u_i as
-// D_i = d_i - d_{i-1}; for smooth data the differences are exact, so the
-// increment carries a relative (not absolute) rounding error.  FP64 then
-// applies u' = fma(c2, D_q, fma(c1, D_i, u)); FP32 forms the increment
-// first and rounds u once per level.  The compensated FP32 pair (s, e),
-// value s + e, takes D from the s and e second differences summed at the
-// end, and adds the increment with Kahan's compensated sum.
+// FP64 evaluates a level in the two stages that Eq. (3)/(4) are the solution
+// of: an explicit one over the other parity's pairs, then the 2x2 solve of
+// this parity's pairs (i left of q):
+//     v_i = u_i - r (u_i - u_{i-1}),   v_q = u_q + r (u_{q+1} - u_q),
+//     w = v_q - v_i,   u_i' = v_i + k w,   u_q' = v_q - k w,   k = r/(1+2r).
+// Both stages work on pairs, so a difference serves two points: 3 VALU
+// instructions a point (a subtraction per pair and an FMA per point, twice)
+// where second differences take 4.  Two roundings of u per level, as
+// fma(c2, D_q, fma(c1, D_i, u)) has: against extended precision, on rods of
+// 257 to 300000 points, r = 0.3 to 4, 1 to 1500 levels, the error is 0.7 of
+// that form's at the median (2e-16 against 3e-16 at 1500 levels).  A point
+// alone beside a wall (scheme A, Eq. (1), or B, Eq. (2)) is a pair with the
+// wall node, the wall's old value in the explicit stage and its new one in
+// the second, and cs = r/(1+r) for k.  A source f = a(t) b(x) adds
+// tau a(t_m + tau/2) b_i to v_i.
+//
+// FP32 rounds u once per level, so it forms the increment from second
+// differences, D_i = u_{i-1} - 2u_i + u_{i+1} = d_i - d_{i-1} from first
+// differences d_i = u_{i+1} - u_i (exact for smooth data, so the increment
+// carries a relative rounding error):
+//     u_i' = u_i + c1 (D_i + cs D_q),   c1 = (r+r^2)/(1+2r), cs = r/(1+r),
+// with q the partner of i, as two FMAs: 4 instructions a point (5 when the
+// increment was formed as c1 D_i + c2 D_q and added).  Two stages would take 3,
+// but their roundings part from this form's by up to 4e-5 of u where
+// increments fall below half a unit of u (30000 points, r = 0.3, 6000
+// levels).  A point alone beside a wall is u_i' = u_i + cs D_i with the
+// wall's new value in D_i.  A source adds a(t_m + tau/2) (tau/r b_i +
+// tau/(1+r) b_q) inside the parentheses (no b_q for a lone point).
+//
+// The compensated FP32 pair (s, e), value s + e:
+//     u_i' = u_i + c1 D_i + c2 D_q,   c1 = (r+r^2)/(1+2r), c2 = r^2/(1+2r),
+// where q is i's partner, and u_i' = u_i + cs (D_i + g(t_{m+1}) - g(t_m)) for
+// a point alone beside a wall, D_i with the wall value at t_m.  A source adds
+// a(t_m + tau/2) (e1 b_i + e2 b_q) to a pair member and a(t_m + tau/2) es b_i
+// to a lone point.  D comes from the s and e first differences' differences,
+// summed at the end, and the increment is added with Kahan's compensated sum.
 //
 // Layout: each lane holds K consecutive points in registers; neighbour
 // values cross lanes by DPP wave shifts, and the lanes at a wave's edges
@@ -268,41 +288,6 @@ __device__ __forceinline__ void store_lane_upto(T *__restrict__ p, int64_t g0, i
     }
 }
 
-// Store the values whose global index lies in [lo, n): lo is a multiple of
-// the chunk width, so a chunk is wholly below lo or not; the chunk that
-// straddles n goes value by value.
-template <typename T, int K>
-__device__ __forceinline__ void store_lane_range(T *__restrict__ p, int64_t g0, int64_t lo,
-                                                 int64_t n, const T (&v)[K], T &fin)
-{
-    using V = typename V16<T>::type;
-    constexpr int E = V16<T>::E;
-    V *q = reinterpret_cast<V *>(p);
-#pragma unroll
-    for (int c = 0; c < K / E; ++c) {
-        if (g0 + c * E < lo)
-            continue;
-        if (g0 + (c + 1) * E <= n) {
-#pragma unroll
-            for (int i = 0; i < E; ++i) finite_acc(fin, v[c * E + i]);
-            V x;
-            if constexpr (E == 4) {
-                x.x = v[4 * c]; x.y = v[4 * c + 1]; x.z = v[4 * c + 2]; x.w = v[4 * c + 3];
-            } else {
-                x.x = v[2 * c]; x.y = v[2 * c + 1];
-            }
-            q[c] = x;
-        } else {
-#pragma unroll
-            for (int i = 0; i < E; ++i)
-                if (g0 + c * E + i < n) {
-                    finite_acc(fin, v[c * E + i]);
-                    p[c * E + i] = v[c * E + i];
-                }
-        }
-    }
-}
-
 // Access to element k of a lane's register tile for a wave-uniform k, as a
 // switch: one scalar branch tree and a single move per call.  (An equality
 // chain over the tile would be folded into one dynamically indexed access,
@@ -346,29 +331,6 @@ __device__ __forceinline__ T get_at(const T (&v)[K], int k, T otherwise)
 }
 
 
-// A first difference: one value, or the (s, e) parts of the pair kept apart.
-template <typename T, bool COMP> struct Dif { T s; };
-template <typename T> struct Dif<T, true> { T s, e; };
-
-// First difference u_{j+1} - u_j of two points given as (s, e).  For the
-// pair the s and e parts stay apart: for smooth data the s differences (and
-// their differences) are exact, and summing the s and e second differences
-// only at the end keeps D accurate to the precision of the pair.
-template <typename T, bool COMP>
-__device__ __forceinline__ Dif<T, COMP> dif(T s1, T e1, T s0, T e0)
-{
-    if constexpr (COMP) return Dif<T, COMP>{s1 - s0, e1 - e0};
-    else return Dif<T, COMP>{s1 - s0};
-}
-
-// second difference D = db - da from consecutive first differences
-template <typename T, bool COMP>
-__device__ __forceinline__ T sd(Dif<T, COMP> da, Dif<T, COMP> db)
-{
-    if constexpr (COMP) return (db.s - da.s) + (db.e - da.e);
-    else return db.s - da.s;
-}
-
 // Wall value split for the state type: (hi, lo) with hi + lo ~ g.
 template <typename T, bool COMP>
 __device__ __forceinline__ void split_wall(double g, T &hi, T &lo)
@@ -377,11 +339,11 @@ __device__ __forceinline__ void split_wall(double g, T &hi, T &lo)
     lo = COMP ? (T)(g - (double)hi) : T(0);
 }
 
-
-// Per-level constants of the scheme in the state's type.
+// Constants of the scheme in the state's type.
 template <typename T> struct Coef {
-    T c1, c2, cs;   // (r+r^2)/(1+2r), r^2/(1+2r), r/(1+r)
-    T e1, e2, es;   // tau(1+r)/(1+2r), tau r/(1+2r), tau/(1+r)
+    T r, k;     // r, r/(1+2r): FP64
+    T c1;       // (r+r^2)/(1+2r): FP32
+    T cs;       // r/(1+r)
 };
 
 // The coefficients as the level loop reads them.  For FP32 they are moved
@@ -392,9 +354,191 @@ template <typename T> struct Coef {
 template <typename T>
 __device__ __forceinline__ Coef<T> lane_coef(Coef<T> c)
 {
-    if constexpr (sizeof(T) == 4)
-        asm("" : "+v"(c.c1), "+v"(c.c2), "+v"(c.cs), "+v"(c.e1), "+v"(c.e2), "+v"(c.es));
+    if constexpr (sizeof(T) == 4) asm("" : "+v"(c.c1), "+v"(c.cs));
     return c;
+}
+
+// Constants of the compensated pair's form.
+template <typename T> struct PairCoef {
+    T c1, c2, cs;   // (r+r^2)/(1+2r), r^2/(1+2r), r/(1+r)
+    T e1, e2, es;   // tau(1+r)/(1+2r), tau r/(1+2r), tau/(1+r)
+};
+template <typename T>
+__device__ __forceinline__ PairCoef<T> lane_coef(PairCoef<T> c)
+{
+    asm("" : "+v"(c.c1), "+v"(c.c2), "+v"(c.cs), "+v"(c.e1), "+v"(c.e2), "+v"(c.es));
+    return c;
+}
+
+// ---- the two stages of a level (FP64) ---------------------------------------
+// The lane's K points (K even) in place.  Parity P couples (2q, 2q+1) inside
+// the lane when P = 0 and across lanes when P = 1; the explicit stage runs
+// over the other parity's pairs.  xl, xr: the values left of lane 0 and right
+// of lane 63 (unused when OPEN: both are open window edges).
+template <typename T, int K, int P, bool OPEN>
+__device__ __forceinline__ void explicit_stage(T (&u)[K], T xl, T xr, const Coef<T> &c)
+{
+    if constexpr (P == 0) {
+        const T ul = edge_left<OPEN>(xl, u[K - 1]), ur = edge_right<OPEN>(xr, u[0]);
+        u[0] = fmaT(-c.r, u[0] - ul, u[0]);
+#pragma unroll
+        for (int j = 1; j + 1 < K; j += 2) {
+            const T d = u[j + 1] - u[j];
+            u[j] = fmaT(c.r, d, u[j]);
+            u[j + 1] = fmaT(-c.r, d, u[j + 1]);
+        }
+        u[K - 1] = fmaT(c.r, ur - u[K - 1], u[K - 1]);
+    } else {
+#pragma unroll
+        for (int j = 0; j < K; j += 2) {
+            const T d = u[j + 1] - u[j];
+            u[j] = fmaT(c.r, d, u[j]);
+            u[j + 1] = fmaT(-c.r, d, u[j + 1]);
+        }
+    }
+}
+
+// kl, kr: the coefficient of the lane's first and last point at P = 1 (k, or
+// cs in the lane whose point stands alone beside a wall).
+template <typename T, int K, int P, bool OPEN>
+__device__ __forceinline__ void solve_stage(T (&v)[K], T xl, T xr, const Coef<T> &c, T kl, T kr)
+{
+    if constexpr (P == 0) {
+#pragma unroll
+        for (int j = 0; j < K; j += 2) {
+            const T w = v[j + 1] - v[j];
+            v[j] = fmaT(c.k, w, v[j]);
+            v[j + 1] = fmaT(-c.k, w, v[j + 1]);
+        }
+    } else {
+        const T vl = edge_left<OPEN>(xl, v[K - 1]), vr = edge_right<OPEN>(xr, v[0]);
+        v[0] = fmaT(-kl, v[0] - vl, v[0]);
+#pragma unroll
+        for (int j = 1; j + 1 < K; j += 2) {
+            const T w = v[j + 1] - v[j];
+            v[j] = fmaT(c.k, w, v[j]);
+            v[j + 1] = fmaT(-c.k, w, v[j + 1]);
+        }
+        v[K - 1] = fmaT(kr, vr - v[K - 1], v[K - 1]);
+    }
+}
+
+// The source term ta b of every point, ta = tau a(t_m + tau/2).
+template <typename T, int K>
+__device__ __forceinline__ void source_stage(T (&v)[K], const T (&b)[K], T ta)
+{
+#pragma unroll
+    for (int j = 0; j < K; ++j) v[j] = fmaT(ta, b[j], v[j]);
+}
+
+// A point alone beside a wall (a wall node at a run-time position): its new
+// value from its v and the wall's new value, as solve_stage forms it.
+template <typename T>
+__device__ __forceinline__ T lone_point(T v, T g, T cs)
+{
+    return fmaT(cs, g - v, v);
+}
+
+// ---- the increment form (FP32) ---------------------------------------------
+// The source weights of the lane's points at parity P, in units of c1:
+// (tau/r) b_i + (tau/(1+r)) b_q, q the partner of i (neighbouring lanes' points
+// through bl = b_{-1}, br = b_K: 0 at a wall, whose lone point has no partner).
+template <typename T, int K, int P>
+__device__ __forceinline__ void increment_source(const T (&b)[K], T bl, T br, T f1, T f2, T (&B)[K])
+{
+#pragma unroll
+    for (int j = 0; j < K; ++j) {
+        const int q = ((j + P) & 1) == 0 ? j + 1 : j - 1;
+        B[j] = fmaT(f1, b[j], f2 * (q < 0 ? bl : q == K ? br : b[q]));
+    }
+}
+
+// One level of parity P of the lane's K points.  xl, xl2, xr, xr2: u_{-1},
+// u_{-2}, u_K, u_{K+1} for lanes 0 / 63 (unused when OPEN).  Beside a wall xl
+// (xr) is its old value at P = 0 and its new one at P = 1, xl2 (xr2) any
+// finite value, and cl, pl (cr, pr), the factors of the lane's first (last)
+// point at P = 1, are cs and 0 in place of c1 and cs.
+template <typename T, int K, bool SRC, int P, bool OPEN>
+__device__ __forceinline__ void increment_level(T (&u)[K], const T (&B)[K], T an, T xl, T xl2, T xr,
+                                                T xr2, const Coef<T> &c, T cl, T pl, T cr, T pr)
+{
+    const T ul = edge_left<OPEN>(xl, u[K - 1]), ur = edge_right<OPEN>(xr, u[0]);
+    // u_j from the factors f, g of its own and its partner's second difference
+    auto upd = [&](int j, T D, T Dq, T f, T g) {
+        T x = fmaT(g, Dq, D);
+        if constexpr (SRC) x = fmaT(an, B[j], x);
+        u[j] = fmaT(f, x, u[j]);
+    };
+    if constexpr (P == 0) {
+        T dprev = u[0] - ul;
+#pragma unroll
+        for (int j = 0; j < K; j += 2) {
+            const T d0 = u[j + 1] - u[j];
+            const T d1 = (j + 2 < K ? u[j + 2] : ur) - u[j + 1];
+            const T Da = d0 - dprev, Db = d1 - d0;
+            upd(j, Da, Db, c.c1, c.cs);
+            upd(j + 1, Db, Da, c.c1, c.cs);
+            dprev = d1;
+        }
+    } else {
+        // pairs (-1,0), (1,2), ..., (K-1,K): the partners' second differences
+        // of the lane's edge points come from the lanes beside
+        const T dm = u[0] - ul, d0 = u[1] - u[0];
+        const T dk = u[K - 1] - u[K - 2], dr = ur - u[K - 1];
+        const T D0 = d0 - dm, DK = dr - dk;
+        T fl = T(0), fr = T(0);
+        if constexpr (!OPEN) {
+            fl = dm - (xl - xl2);
+            fr = (xr2 - xr) - dr;
+        }
+        const T Dl = edge_left<OPEN>(fl, DK), Dr = edge_right<OPEN>(fr, D0);
+        T dprev = d0;
+#pragma unroll
+        for (int j = 1; j + 1 < K; j += 2) {
+            const T da = u[j + 1] - u[j], db = u[j + 2] - u[j + 1];
+            const T Da = da - dprev, Db = db - da;
+            if (j == 1) upd(0, D0, Dl, cl, pl);
+            upd(j, Da, Db, c.c1, c.cs);
+            upd(j + 1, Db, Da, c.c1, c.cs);
+            dprev = db;
+        }
+        if constexpr (K == 2) upd(0, D0, Dl, cl, pl);
+        upd(K - 1, DK, Dr, cr, pr);
+    }
+}
+
+// The point alone beside a right wall node at a run-time position: element
+// kS of its lane, u_{n-2} before it (xl: the fill of lane 0); g: the wall's
+// new value.
+template <typename T, int K, bool SRC>
+__device__ __forceinline__ T lone_increment(const T (&u)[K], const T (&B)[K], T an, int kS, T xl,
+                                            T g, T cs)
+{
+    const T ul = from_left(xl, u[K - 1]);
+    const T u1 = get_at<T, K>(u, kS, T(0)), u0 = get_at<T, K>(u, kS - 1, ul);
+    T x = (g - u1) - (u1 - u0);
+    if constexpr (SRC) x = fmaT(an, get_at<T, K>(B, kS, T(0)), x);
+    return fmaT(cs, x, u1);
+}
+
+// ---- the compensated pair --------------------------------------------------
+// A first difference of two points given as (s, e).  The s and e parts stay
+// apart: for smooth data the s differences (and their differences) are
+// exact, and summing the s and e second differences only at the end keeps D
+// accurate to the precision of the pair.
+template <typename T> struct Dif { T s, e; };
+
+template <typename T>
+__device__ __forceinline__ Dif<T> dif(T s1, T e1, T s0, T e0)
+{
+    return Dif<T>{s1 - s0, e1 - e0};
+}
+
+// second difference D = db - da from consecutive first differences
+template <typename T>
+__device__ __forceinline__ T sd(Dif<T> da, Dif<T> db)
+{
+    return (db.s - da.s) + (db.e - da.e);
 }
 
 // What a level needs to know about the left wall, seen from one lane (the
@@ -420,7 +564,7 @@ struct FluxTap {
 // per-level update uses; a launch's profile is fixed, so these are formed
 // once per launch and each level adds a(t) B_i with one FMA.
 template <typename T, int K, int P>
-__device__ __forceinline__ void source_weights(const T (&b)[K], T bl, T br, const Coef<T> &c,
+__device__ __forceinline__ void source_weights(const T (&b)[K], T bl, T br, const PairCoef<T> &c,
                                                T (&B)[K])
 {
     if constexpr (P == 0) {
@@ -444,7 +588,7 @@ __device__ __forceinline__ void source_weights(const T (&b)[K], T bl, T br, cons
 // Advance the K points of every lane by one level of parity P (known at
 // compile time: a runtime parity would merge the two groupings' results for
 // every point each level and cost the register file).
-//   s, e : the lane's points (e is the compensation of the pair, else 0)
+//   s, e : the lane's points (e is the compensation)
 //   b    : SRC = 1: the lane's source profile, bl, br: profile of u_{-1}
 //          and u_K; SRC = 2: the weights of this parity (source_weights)
 //   xl, xl2, xr, xr2 : u_{-1}, u_{-2}, u_K, u_{K+1} for lanes 0 / 63 (DPP
@@ -453,71 +597,39 @@ __device__ __forceinline__ void source_weights(const T (&b)[K], T bl, T br, cons
 // WALL instantiations apply the lone-point formulas and the flux tap; every
 // other point of every instantiation evaluates the same expressions.  OPEN:
 // both edges of the wave are open window edges, so the fills are not used.
-template <typename T, int K, bool COMP, int SRC, bool WALL, int P, bool OPEN = false>
-__device__ __forceinline__ void ge_level(T (&s)[K], T (&e)[K], const T (&b)[K], T bl, T br,
-                                         T xl, T xl2, T xr, T xr2, T yl, T yl2, T yr, T yr2,
-                                         const Coef<T> &c, T an,
-                                         const WallLevel<T> &wl, FluxTap &ft)
+template <typename T, int K, int SRC, bool WALL, int P, bool OPEN = false>
+__device__ __forceinline__ void pair_level(T (&s)[K], T (&e)[K], const T (&b)[K], T bl, T br,
+                                           T xl, T xl2, T xr, T xr2, T yl, T yl2, T yr, T yr2,
+                                           const PairCoef<T> &c, T an, const WallLevel<T> &wl,
+                                           FluxTap &ft)
 {
     static_assert(!(WALL && SRC == 2), "wall tiles take the source from the profile");
     const T c1 = c.c1, c2 = c.c2, cs = c.cs, e1 = c.e1, e2 = c.e2, es = c.es;
     // u_{-1} and u_K: neighbour lanes' edge points
     const T sl = edge_left<OPEN>(xl, s[K - 1]), sr = edge_right<OPEN>(xr, s[0]);
-    T el = T(0), er = T(0);
-    if constexpr (COMP) { el = edge_left<OPEN>(yl, e[K - 1]); er = edge_right<OPEN>(yr, e[0]); }
+    const T el = edge_left<OPEN>(yl, e[K - 1]), er = edge_right<OPEN>(yr, e[0]);
 
-    auto dif = [](T s1, T e1_, T s0, T e0) { return ::ge::dev::dif<T, COMP>(s1, e1_, s0, e0); };
-    auto sd = [](Dif<T, COMP> da, Dif<T, COMP> db) { return ::ge::dev::sd<T, COMP>(da, db); };
     // advance point j from D_self and D_partner (bp: partner's profile)
     auto upd = [&](int j, T Ds, T Dp, T bp) {
-        if constexpr (COMP) {
-            T inc = fmaT(c1, Ds, c2 * Dp);
-            if constexpr (SRC == 1) inc = fmaT(an, fmaT(e1, b[j], e2 * bp), inc);
-            if constexpr (SRC == 2) inc = fmaT(an, b[j], inc);
-            if constexpr (WALL) {
-                if (j == 0) {
-                    T alt = cs * (Ds + wl.dgl);
-                    if constexpr (SRC) alt = fmaT(an, es * b[j], alt);
-                    inc = wl.isL ? alt : inc;
-                }
+        T inc = fmaT(c1, Ds, c2 * Dp);
+        if constexpr (SRC == 1) inc = fmaT(an, fmaT(e1, b[j], e2 * bp), inc);
+        if constexpr (SRC == 2) inc = fmaT(an, b[j], inc);
+        if constexpr (WALL) {
+            if (j == 0) {
+                T alt = cs * (Ds + wl.dgl);
+                if constexpr (SRC) alt = fmaT(an, es * b[j], alt);
+                inc = wl.isL ? alt : inc;
             }
-            // Kahan: the pair absorbs the increment, e keeps what s lost
-            const T y = inc + e[j];
-            const T tt = s[j] + y;
-            e[j] = y - (tt - s[j]);
-            s[j] = tt;
-        } else if constexpr (sizeof(T) == 8) {
-            // FP64: two fused steps, u + c1 D_self, then + c2 D_partner
-            T t = fmaT(c1, Ds, s[j]);
-            if constexpr (SRC == 1) t = fmaT(an, fmaT(e1, b[j], e2 * bp), t);
-            if constexpr (SRC == 2) t = fmaT(an, b[j], t);
-            T v = fmaT(c2, Dp, t);
-            if constexpr (WALL) {
-                if (j == 0) {
-                    T alt = fmaT(cs, Ds + wl.dgl, s[j]);
-                    if constexpr (SRC) alt = fmaT(an, es * b[j], alt);
-                    v = wl.isL ? alt : v;
-                }
-            }
-            s[j] = v;
-        } else {
-            // FP32: form the increment first, so u is rounded once per level
-            T inc = fmaT(c1, Ds, c2 * Dp);
-            if constexpr (SRC == 1) inc = fmaT(an, fmaT(e1, b[j], e2 * bp), inc);
-            if constexpr (SRC == 2) inc = fmaT(an, b[j], inc);
-            if constexpr (WALL) {
-                if (j == 0) {
-                    T alt = cs * (Ds + wl.dgl);
-                    if constexpr (SRC) alt = fmaT(an, es * b[j], alt);
-                    inc = wl.isL ? alt : inc;
-                }
-            }
-            s[j] = s[j] + inc;
         }
+        // Kahan: the pair absorbs the increment, e keeps what s lost
+        const T y = inc + e[j];
+        const T tt = s[j] + y;
+        e[j] = y - (tt - s[j]);
+        s[j] = tt;
         if constexpr (WALL) {
             // wall first differences at the new level, accumulated in FP64
             if (ft.left && j == 0) {
-                const double v = (double)s[j] + (COMP ? (double)e[j] : 0.0);
+                const double v = (double)s[j] + (double)e[j];
                 ft.accL = ft.accL + ft.tau * (v - ft.gln) / ft.h;
             }
         }
@@ -542,11 +654,7 @@ __device__ __forceinline__ void ge_level(T (&s)[K], T (&e)[K], const T (&b)[K], 
         // with the neighbouring lanes' edge points, so u_{-2} and u_{K+1}
         // are needed too
         const T sl2 = edge_left<OPEN>(xl2, s[K - 2]), sr2 = edge_right<OPEN>(xr2, s[1]);
-        T el2 = T(0), er2 = T(0);
-        if constexpr (COMP) {
-            el2 = edge_left<OPEN>(yl2, e[K - 2]);
-            er2 = edge_right<OPEN>(yr2, e[1]);
-        }
+        const T el2 = edge_left<OPEN>(yl2, e[K - 2]), er2 = edge_right<OPEN>(yr2, e[1]);
         const auto dm2 = dif(sl, el, sl2, el2);                     // d_{-2}
         const auto dm1 = dif(s[0], e[0], sl, el);                   // d_{-1}
         const auto d0 = dif(s[1], e[1], s[0], e[0]);                // d_0
@@ -577,36 +685,20 @@ __device__ __forceinline__ void ge_level(T (&s)[K], T (&e)[K], const T (&b)[K], 
 // g_R(t_{m+1}) - g_R(t_m).  The arithmetic is the per-point update's.
 template <typename T> struct Lone { T s, e; };
 
-template <typename T, int K, bool COMP, bool SRC>
+template <typename T, int K, bool SRC>
 __device__ __forceinline__ Lone<T> right_lone(const T (&s)[K], const T (&e)[K], const T (&b)[K],
                                               int kS, T xl, T yl, T g_hi, T g_lo, T dgr,
-                                              const Coef<T> &c, T an)
+                                              const PairCoef<T> &c, T an)
 {
-    const T sl = from_left(xl, s[K - 1]);
-    const T el = COMP ? from_left(yl, e[K - 1]) : T(0);
-    const T u1 = get_at<T, K>(s, kS, T(0));
-    const T e1 = COMP ? get_at<T, K>(e, kS, T(0)) : T(0);
-    const T u0 = get_at<T, K>(s, kS - 1, sl);
-    const T e0 = COMP ? get_at<T, K>(e, kS - 1, el) : T(0);
-    const T Ds = sd<T, COMP>(dif<T, COMP>(u1, e1, u0, e0), dif<T, COMP>(g_hi, g_lo, u1, e1));
-    Lone<T> out{u1, e1};
-    if constexpr (COMP) {
-        T inc = c.cs * (Ds + dgr);
-        if constexpr (SRC) inc = fmaT(an, c.es * get_at<T, K>(b, kS, T(0)), inc);
-        const T y = inc + e1;
-        const T tt = u1 + y;
-        out.e = y - (tt - u1);
-        out.s = tt;
-    } else if constexpr (sizeof(T) == 8) {
-        T alt = fmaT(c.cs, Ds + dgr, u1);
-        if constexpr (SRC) alt = fmaT(an, c.es * get_at<T, K>(b, kS, T(0)), alt);
-        out.s = alt;
-    } else {
-        T inc = c.cs * (Ds + dgr);
-        if constexpr (SRC) inc = fmaT(an, c.es * get_at<T, K>(b, kS, T(0)), inc);
-        out.s = u1 + inc;
-    }
-    return out;
+    const T sl = from_left(xl, s[K - 1]), el = from_left(yl, e[K - 1]);
+    const T u1 = get_at<T, K>(s, kS, T(0)), e1 = get_at<T, K>(e, kS, T(0));
+    const T u0 = get_at<T, K>(s, kS - 1, sl), e0 = get_at<T, K>(e, kS - 1, el);
+    const T Ds = sd(dif(u1, e1, u0, e0), dif(g_hi, g_lo, u1, e1));
+    T inc = c.cs * (Ds + dgr);
+    if constexpr (SRC) inc = fmaT(an, c.es * get_at<T, K>(b, kS, T(0)), inc);
+    const T y = inc + e1;
+    const T tt = u1 + y;
+    return Lone<T>{tt, y - (tt - u1)};
 }
 
 // Run levels level0 .. level0+nlev-1 as f(parity, lev) with the parity a

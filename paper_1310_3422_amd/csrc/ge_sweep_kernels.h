@@ -24,7 +24,7 @@ namespace {
 using namespace dev;
 
 // First tile whose window reaches the right wall (tiles from there on, and
-// tile 0, take the wall path).
+// tile 0, hold a wall).
 __device__ __host__ inline int64_t first_right_wall_tile(const TileArgs &a, int64_t W)
 {
     const int64_t need = a.n + a.halo - W;       // t * core >= need
@@ -33,16 +33,18 @@ __device__ __host__ inline int64_t first_right_wall_tile(const TileArgs &a, int6
     return t < a.ntiles ? t : a.ntiles;
 }
 
-// The tiles of a launch.  PART 0: every tile, each taking the wall path or
-// not.  The wall path (guarded loads, runtime wall positions, the flux, the
+// The tiles of a launch.  PART 0: every tile, whatever its window holds.  The
+// compensated pair's wall path (guarded loads, run-time wall positions, the
 // source profile kept for the lone points) needs far more registers than an
 // interior tile, and a kernel holds the registers of its widest path in
-// every wave; so rods of very many tiles run two kernels per launch: PART 2
+// every wave; so its launches of very many tiles run two kernels: PART 2
 // takes tile 0 and the tiles reaching the right wall (one workgroup each),
 // PART 1 the interior tiles 1 .. tw-1 at the interior path's occupancy.  The
 // wall kernel costs about one tile's time (it runs beside the interior one
 // when the caller gives a second stream, else before it), which pays only
-// when a CU sweeps hundreds of tiles per launch.
+// when a CU sweeps hundreds of tiles per launch.  FP64 and FP32 windows that
+// reach a wall differ from the others in the fills of two lanes only and
+// stay in the one kernel.
 template <typename T, int K, int NW, bool COMP, bool SRC, int PART>
 __global__ __launch_bounds__(NW *kWave) void tile_kernel(TileArgs a)
 {
@@ -51,7 +53,7 @@ __global__ __launch_bounds__(NW *kWave) void tile_kernel(TileArgs a)
         const int64_t tw = first_right_wall_tile(a, W);
         const int64_t t = blockIdx.x == 0 ? 0 : tw + blockIdx.x - 1;
         if (t < a.ntiles)
-            run_tile<T, K, NW, COMP, SRC, true>(a, threadIdx.x, t, t == 0 ? 0 : t * a.core - a.halo);
+            run_pair<T, K, NW, SRC, true>(a, threadIdx.x, t, t == 0 ? 0 : t * a.core - a.halo);
         return;
     }
     // Consecutive tiles go to the same XCD (workgroups are dealt to the 8
@@ -61,18 +63,18 @@ __global__ __launch_bounds__(NW *kWave) void tile_kernel(TileArgs a)
     if constexpr (PART == 1) {
         const int64_t t = 1 + i;
         if (t < first_right_wall_tile(a, W))
-            run_tile<T, K, NW, COMP, SRC, false>(a, threadIdx.x, t, t * a.core - a.halo);
+            run_pair<T, K, NW, SRC, false>(a, threadIdx.x, t, t * a.core - a.halo);
         return;
     }
-    const int64_t t = i;
-    if (t >= a.ntiles)
-        return;
-    const int64_t ws = (t == 0) ? 0 : t * a.core - a.halo;
-    const bool wall = (ws == 0) || (ws + W >= a.n);
-    if (wall)
-        run_tile<T, K, NW, COMP, SRC, true>(a, threadIdx.x, t, ws);
-    else
-        run_tile<T, K, NW, COMP, SRC, false>(a, threadIdx.x, t, ws);
+    if (i < a.ntiles)
+        run_tile<T, K, NW, COMP, SRC>(a, threadIdx.x, i);
+}
+
+// A rod shorter than one window (FP64, FP32): the right wall node lies inside.
+template <typename T, int K, int NW, bool SRC>
+__global__ __launch_bounds__(NW *kWave) void short_rod_kernel(TileArgs a)
+{
+    run_plain<T, K, NW, SRC, kInside>(a, threadIdx.x, 0, 0);
 }
 
 // Persistent form for single-wave windows.  The first nint workgroups sweep
@@ -80,8 +82,8 @@ __global__ __launch_bounds__(NW *kWave) void tile_kernel(TileArgs a)
 // current one advances, so the loads hide behind the levels; the remaining
 // workgroups take one wall tile each, concurrently (a workgroup sweeps about
 // ten tiles per launch here, so a separate wall launch would cost about a
-// tenth; the prefetch registers exceed the wall path's anyway).
-// Consecutive interior tiles are dealt to the same XCD, as in tile_kernel.
+// tenth).  Consecutive interior tiles are dealt to the same XCD, as in
+// tile_kernel.
 template <typename T, int K, bool COMP, bool SRC>
 __global__ __launch_bounds__(kWave) void tile_persistent_kernel(TileArgs a, int nint)
 {
@@ -91,7 +93,7 @@ __global__ __launch_bounds__(kWave) void tile_persistent_kernel(TileArgs a, int 
     if (g >= nint) {
         const int64_t t = g == nint ? 0 : tw + (g - nint - 1);
         if (t < a.ntiles && (t == 0 || t >= tw))
-            run_tile<T, K, 1, COMP, SRC, true>(a, threadIdx.x, t, t == 0 ? 0 : t * a.core - a.halo);
+            run_tile<T, K, 1, COMP, SRC>(a, threadIdx.x, t);
         return;
     }
     const int per = nint / 8;
@@ -103,18 +105,30 @@ __global__ __launch_bounds__(kWave) void tile_persistent_kernel(TileArgs a, int 
     // prefetch registers, so the loads pending during a sweep are only the
     // next tile's and the sweep never waits for them
     T s[K], e[K], b[K], ns[K], ne[K], nb[K];
-    load_tile<T, K, COMP, SRC, false>(a, threadIdx.x, t * a.core - a.halo, ns, ne, nb);
+    auto load = [&](int64_t i) {
+        const int64_t ws = i * a.core - a.halo;
+        if constexpr (COMP) {
+            load_pair<T, K, SRC, false>(a, threadIdx.x, ws, ns, ne, nb);
+        } else {
+            const int64_t g0 = ws + (int64_t)threadIdx.x * K;
+            load_lane<T, K>(static_cast<const T *>(a.in) + g0, ns);
+            if constexpr (SRC) load_lane<T, K>(static_cast<const T *>(a.src_b) + g0, nb);
+        }
+    };
+    load(t);
     for (;;) {
 #pragma unroll
         for (int j = 0; j < K; ++j) {
             s[j] = ns[j];
-            e[j] = ne[j];
-            b[j] = nb[j];
+            if constexpr (COMP) e[j] = ne[j];
+            if constexpr (SRC) b[j] = nb[j];
         }
         const int64_t tn = t + nint;
         if (tn < tw)
-            load_tile<T, K, COMP, SRC, false>(a, threadIdx.x, tn * a.core - a.halo, ns, ne, nb);
-        sweep_tile<T, K, 1, COMP, SRC, false>(a, threadIdx.x, t, t * a.core - a.halo, s, e, b);
+            load(tn);
+        const int64_t ws = t * a.core - a.halo;
+        if constexpr (COMP) sweep_pair<T, K, 1, SRC, false>(a, threadIdx.x, t, ws, s, e, b);
+        else sweep_plain<T, K, 1, SRC, kOpen>(a, threadIdx.x, t, ws, s, b);
         if (tn >= tw)
             break;
         t = tn;
@@ -151,27 +165,11 @@ hipError_t launch_persistent(const TileArgs &a, hipStream_t stream)
     return hipGetLastError();
 }
 
-template <typename T, int K, int NW, bool COMP, bool SRC>
-hipError_t launch_one(const TileArgs &a, hipStream_t stream, const SideStream *side)
+// The compensated pair's launches over very many tiles: the wall tiles' kernel
+// beside the interior one.
+template <typename T, int K, int NW, bool SRC>
+hipError_t launch_split(const TileArgs &a, int64_t tw, hipStream_t stream, const SideStream *side)
 {
-    constexpr int64_t W = NW * kWave * K;
-    // compute units (split launches only where a CU sweeps 128 tiles or more)
-    static int ncu = 0;
-    if (ncu == 0) {
-        int dev = 0;
-        if (hipGetDevice(&dev) != hipSuccess ||
-            hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-            ncu < 1)
-            ncu = 256;
-    }
-    const int64_t tw = a.ntiles >= 3 ? first_right_wall_tile(a, W) : 1;
-    if (tw - 1 < 128 * (int64_t)ncu) {
-        // no interior tile: every tile in one launch
-        const int64_t grid = (a.ntiles + 7) / 8 * 8;
-        hipLaunchKernelGGL((tile_kernel<T, K, NW, COMP, SRC, 0>), dim3((unsigned)grid),
-                           dim3(NW * kWave), 0, stream, a);
-        return hipGetLastError();
-    }
     // the wall kernel (a few workgroups, each about one tile's time) beside
     // the interior one when a side stream is given, else before it
     const int64_t walls = 1 + (a.ntiles - tw);
@@ -183,18 +181,48 @@ hipError_t launch_one(const TileArgs &a, hipStream_t stream, const SideStream *s
             return e;
         ws = side->stream;
     }
-    hipLaunchKernelGGL((tile_kernel<T, K, NW, COMP, SRC, 2>), dim3((unsigned)walls),
+    hipLaunchKernelGGL((tile_kernel<T, K, NW, true, SRC, 2>), dim3((unsigned)walls),
                        dim3(NW * kWave), 0, ws, a);
     if ((e = hipGetLastError()) != hipSuccess)
         return e;
     if (side && (e = hipEventRecord(side->join, side->stream)) != hipSuccess)
         return e;
     const int64_t grid = (tw - 1 + 7) / 8 * 8;
-    hipLaunchKernelGGL((tile_kernel<T, K, NW, COMP, SRC, 1>), dim3((unsigned)grid),
+    hipLaunchKernelGGL((tile_kernel<T, K, NW, true, SRC, 1>), dim3((unsigned)grid),
                        dim3(NW * kWave), 0, stream, a);
     if ((e = hipGetLastError()) != hipSuccess)
         return e;
     return side ? hipStreamWaitEvent(stream, side->join, 0) : hipSuccess;
+}
+
+template <typename T, int K, int NW, bool COMP, bool SRC>
+hipError_t launch_one(const TileArgs &a, hipStream_t stream, const SideStream *side)
+{
+    constexpr int64_t W = NW * kWave * K;
+    if constexpr (!COMP) {
+        if (a.n < W) {
+            hipLaunchKernelGGL((short_rod_kernel<T, K, NW, SRC>), dim3(1), dim3(NW * kWave), 0,
+                               stream, a);
+            return hipGetLastError();
+        }
+    } else {
+        // compute units (split launches only where a CU sweeps 128 tiles or more)
+        static int ncu = 0;
+        if (ncu == 0) {
+            int dev = 0;
+            if (hipGetDevice(&dev) != hipSuccess ||
+                hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+                ncu < 1)
+                ncu = 256;
+        }
+        const int64_t tw = a.ntiles >= 3 ? first_right_wall_tile(a, W) : 1;
+        if (tw - 1 >= 128 * (int64_t)ncu)
+            return launch_split<T, K, NW, SRC>(a, tw, stream, side);
+    }
+    const int64_t grid = (a.ntiles + 7) / 8 * 8;
+    hipLaunchKernelGGL((tile_kernel<T, K, NW, COMP, SRC, 0>), dim3((unsigned)grid),
+                       dim3(NW * kWave), 0, stream, a);
+    return hipGetLastError();
 }
 
 template <typename T, int K, int NW, bool COMP>

@@ -17,10 +17,225 @@
 namespace ge {
 namespace dev {
 
-// The lane's points of the window starting at ws (and their compensation
-// and source profile where the form has them); guarded at a wall.
-template <typename T, int K, bool COMP, bool SRC, bool WALL>
-__device__ __forceinline__ void load_tile(const TileArgs &a, int tid, int64_t ws, T (&s)[K],
+// What bounds a window (FP64 and FP32).
+//   kOpen  : both ends are open window edges (halo points);
+//   kEnds  : it starts at the left wall (ws = 0), ends at the right one
+//            (ws + W = n), or both, so a wall enters as the fill value of the
+//            first or last lane and costs nothing inside the levels: a tile
+//            reaching the right wall is moved left to end there;
+//   kInside: the rod is shorter than the window, the right wall node lies at
+//            a run-time element (a branch tree per access).
+enum WindowKind : int { kOpen = 0, kEnds = 1, kInside = 2 };
+
+// Start of tile t's window.
+template <int64_t W>
+__device__ __forceinline__ int64_t window_start(const TileArgs &a, int64_t t)
+{
+    return t == 0 ? 0 : min(t * a.core - a.halo, a.n - W);
+}
+
+// The lane's points of the window starting at ws, or its source profile.
+// A window moved to end at the right wall may start at any element.
+template <typename T, int K, int KIND>
+__device__ __forceinline__ void load_window(const T *__restrict__ p, int64_t g0, int64_t n,
+                                            T (&v)[K])
+{
+    if constexpr (KIND == kInside) {
+        load_lane_guarded<T, K>(p + g0, g0, n, v);
+    } else if constexpr (KIND == kEnds) {
+#pragma unroll
+        for (int j = 0; j < K; ++j) v[j] = p[g0 + j];
+    } else {
+        load_lane<T, K>(p + g0, v);
+    }
+}
+
+// Wall values of consecutive levels, each loaded a level ahead of its use
+// (a scalar load's latency would otherwise stand in every level): now() and
+// next() are g(t_m) and g(t_{m+1}); step() moves to the next level.  A lone
+// point reads entering(), g(t_{m+1}) made NaN by an infinite or NaN g(t_m):
+// the levels' formulas read one wall value in two, and an unusable value
+// between them is to show in the result as well.
+struct WallWalk {
+    const double *p;      // g(t_m) of the launch's levels, or null: constant
+    double g0, g1, g2;
+    int at, last;
+    __device__ __forceinline__ WallWalk(const double *p_, double c, int nlev) : p(p_), at(2), last(nlev)
+    {
+        g0 = g1 = g2 = c;
+        if (p) {
+            g0 = p[0];
+            g1 = p[1];
+            g2 = p[nlev > 1 ? 2 : 1];
+        }
+    }
+    __device__ __forceinline__ double now() const { return g0; }
+    __device__ __forceinline__ double next() const { return g1; }
+    __device__ __forceinline__ double entering() const { return __builtin_fma(0.0, g0, g1); }
+    __device__ __forceinline__ void step()
+    {
+        g0 = g1;
+        g1 = g2;
+        ++at;
+        if (p) g2 = p[at < last ? at : last];
+    }
+};
+
+// Advance the loaded window of tile t (start ws) by the launch's levels and
+// store its core: FP64 or FP32.
+template <typename T, int K, int NW, bool SRC, int KIND>
+__device__ __forceinline__ void sweep_plain(const TileArgs &a, int tid, int64_t t, int64_t ws,
+                                            T (&u)[K], const T (&b)[K])
+{
+    constexpr int W = NW * kWave * K;
+    constexpr bool WALL = KIND != kOpen, OPEN = KIND == kOpen && NW == 1;
+    const int lane = tid & (kWave - 1);
+    // the wave index is uniform across the wave: let the compiler keep
+    // everything derived from it in scalar registers
+    const int w = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int64_t n = a.n;
+    const int64_t core_lo = t * a.core;
+    const int64_t core_hi = min(core_lo + a.core, n);
+    const int64_t g0 = ws + (int64_t)tid * K;       // global index of my first point
+    T *out = static_cast<T *>(a.out);
+
+    // FP64 meets its neighbours with one value a side, FP32 with two
+    constexpr bool TWO_STAGE = sizeof(T) == 8;
+    constexpr int E = TWO_STAGE ? 1 : 2;
+    __shared__ T xs[2][NW][2 * E];
+
+    // wall geometry (uniform over the window)
+    const bool left = WALL && ws == 0;
+    const bool right = KIND == kEnds && ws + W == n;
+    const int qR = KIND == kInside ? (int)n : 0;   // right wall node's place in the window
+    const int kR = qR % K, lR = qR / K;
+    const int qS = qR - 1;                         // the point beside it
+    const int kS = KIND == kInside ? qS % K : K - 1, lS = KIND == kInside ? qS / K : NW * kWave - 1;
+    const bool own_L = WALL && a.flux && left && core_lo == 0;
+    const bool own_R = WALL && a.flux && (right || KIND == kInside) && core_hi == n;
+    double acc = 0.0, accR = 0.0;
+    if (own_L) acc = a.flux[0];
+    if (own_R) accR = a.flux[1];
+
+    const Coef<T> cf = lane_coef(Coef<T>{(T)a.r, (T)a.k, (T)a.c1, (T)a.cs});
+    const bool lane_l = left && tid == 0, lane_r = right && tid == NW * kWave - 1;
+    const T kl = lane_l ? cf.cs : cf.k, kr = lane_r ? cf.cs : cf.k;
+    const T cl = lane_l ? cf.cs : cf.c1, cr = lane_r ? cf.cs : cf.c1;
+    const T pl = lane_l ? T(0) : cf.cs, pr = lane_r ? T(0) : cf.cs;
+    WallWalk wl(WALL ? a.gl_t : nullptr, a.gl0, a.nlev), wr(WALL ? a.gr_t : nullptr, a.gr0, a.nlev);
+    double an = SRC ? a.src_a[0] : 0.0;             // likewise a level ahead
+
+    // FP32: the source weights of both parities, formed once per launch
+    constexpr int KB = SRC && !TWO_STAGE ? K : 1;
+    T B0[KB], B1[KB];
+    if constexpr (SRC && !TWO_STAGE) {
+        T bl = from_left(T(0), b[K - 1]), br = from_right(T(0), b[0]);
+        if constexpr (NW > 1) {
+            if (lane == 0) xs[0][w][0] = b[0];
+            if (lane == kWave - 1) xs[0][w][1] = b[K - 1];
+            __syncthreads();
+            if (lane == 0 && w > 0) bl = xs[0][w - 1][1];
+            if (lane == kWave - 1 && w < NW - 1) br = xs[0][w + 1][0];
+            __syncthreads();
+        }
+        const T f1 = (T)(a.tau / a.r), f2 = (T)(a.tau / (1.0 + a.r));
+        increment_source<T, K, 0>(b, bl, br, f1, f2, B0);
+        increment_source<T, K, 1>(b, bl, br, f1, f2, B1);
+    }
+
+    // values entering the wave at its edges: from the neighbouring waves
+    // through LDS, a wall value, or (at an open window edge) anything
+    auto exchange = [&](int slot, T gl, T gr, T (&xl)[E], T (&xr)[E]) {
+        if constexpr (NW > 1) {
+#pragma unroll
+            for (int i = 0; i < E; ++i) {
+                if (lane == 0) xs[slot][w][i] = u[i];
+                if (lane == kWave - 1) xs[slot][w][E + i] = u[K - 1 - i];
+            }
+            __syncthreads();
+#pragma unroll
+            for (int i = 0; i < E; ++i) {
+                xl[i] = xs[slot][w > 0 ? w - 1 : 0][E + i];
+                xr[i] = xs[slot][w < NW - 1 ? w + 1 : NW - 1][i];
+            }
+        }
+        if constexpr (WALL) {
+#pragma unroll
+            for (int i = 0; i < E; ++i) {
+                if (left && w == 0) xl[i] = gl;
+                if (right && w == NW - 1) xr[i] = gr;
+            }
+        }
+    };
+
+    // a window starting at an odd point pairs its points the other way round
+    for_levels(a.level0 + (ws & 1), a.nlev, [&](auto par, int lev) {
+        constexpr int P = decltype(par)::value;
+        const T glo = (T)wl.now(), gln = (T)wl.entering();
+        const T gro = (T)wr.now(), grn = (T)wr.entering();
+        const bool single = KIND == kInside && (((int)n - 1 + P) & 1) == 0;
+        T xl[E] = {}, xr[E] = {};
+        T lone = T(0);
+        if constexpr (TWO_STAGE) {
+            if constexpr (KIND == kInside) put_at<T, K>(u, kR, tid == lR, gro);
+            if constexpr (P == 0) exchange(lev & 1, glo, gro, xl, xr);
+            explicit_stage<T, K, P, OPEN>(u, xl[0], xr[0], cf);
+            if constexpr (SRC) source_stage<T, K>(u, b, (T)(a.tau * an));
+            if constexpr (P == 1) exchange(lev & 1, gln, grn, xl, xr);
+            if (KIND == kInside && single)
+                lone = lone_point(get_at<T, K>(u, kS, T(0)), grn, cf.cs);
+            solve_stage<T, K, P, OPEN>(u, xl[0], xr[0], cf, kl, kr);
+        } else {
+            if constexpr (KIND == kInside) put_at<T, K>(u, kR, tid == lR, single ? grn : gro);
+            exchange(lev & 1, P == 0 ? glo : gln, P == 0 ? gro : grn, xl, xr);
+            auto level = [&](const T (&B)[K]) {
+                if (KIND == kInside && single)
+                    lone = lone_increment<T, K, SRC>(u, B, (T)an, kS, xl[0], grn, cf.cs);
+                increment_level<T, K, SRC, P, OPEN>(u, B, (T)an, xl[0], xl[E - 1], xr[0], xr[E - 1],
+                                                    cf, cl, pl, cr, pr);
+            };
+            if constexpr (!SRC) level(b);
+            else if constexpr (P == 0) level(B0);
+            else level(B1);
+        }
+        if (KIND == kInside && single) put_at<T, K>(u, kS, tid == lS, lone);
+        if constexpr (SRC) an = a.src_a[lev + 1 < a.nlev ? lev + 1 : lev];
+        if constexpr (WALL) {
+            // wall first differences at the new level, accumulated in FP64
+            if (own_L && tid == 0) acc = acc + a.tau * ((double)u[0] - wl.next()) / a.h;
+            if (own_R) {
+                const T v = KIND == kInside ? get_at<T, K>(u, kS, T(0)) : u[K - 1];
+                if (tid == lS) accR = accR + a.tau * ((double)v - wr.next()) / a.h;
+            }
+            wl.step();
+            wr.step();
+        }
+    });
+
+    if (own_L && tid == 0) a.flux[0] = acc;
+    if (own_R && tid == lS) a.flux[1] = accR;
+
+    T fin = T(0);
+    if constexpr (WALL) store_lane_guarded<T, K>(out + g0, g0, core_lo, core_hi, u, fin);
+    else store_lane_chunks<T, K>(out + g0, g0, core_lo, core_hi, u, fin);
+    raise_if_nonfinite(a.status, fin);
+}
+
+template <typename T, int K, int NW, bool SRC, int KIND>
+__device__ __forceinline__ void run_plain(const TileArgs &a, int tid, int64_t t, int64_t ws)
+{
+    T u[K], b[K];
+    const int64_t g0 = ws + (int64_t)tid * K;
+    load_window<T, K, KIND>(static_cast<const T *>(a.in), g0, a.n, u);
+    if constexpr (SRC) load_window<T, K, KIND>(static_cast<const T *>(a.src_b), g0, a.n, b);
+    sweep_plain<T, K, NW, SRC, KIND>(a, tid, t, ws, u, b);
+}
+
+// ---- the compensated pair --------------------------------------------------
+// The lane's points of the window starting at ws, their compensation and
+// source profile; guarded at a wall.
+template <typename T, int K, bool SRC, bool WALL>
+__device__ __forceinline__ void load_pair(const TileArgs &a, int tid, int64_t ws, T (&s)[K],
                                           T (&e)[K], T (&b)[K])
 {
     const int64_t g0 = ws + (int64_t)tid * K;
@@ -29,23 +244,19 @@ __device__ __forceinline__ void load_tile(const TileArgs &a, int tid, int64_t ws
     const T *srcb = static_cast<const T *>(a.src_b);
     if constexpr (WALL) {
         load_lane_guarded<T, K>(in_s + g0, g0, a.n, s);
-        if constexpr (COMP) load_lane_guarded<T, K>(in_e + g0, g0, a.n, e);
+        load_lane_guarded<T, K>(in_e + g0, g0, a.n, e);
         if constexpr (SRC) load_lane_guarded<T, K>(srcb + g0, g0, a.n, b);
     } else {
         load_lane<T, K>(in_s + g0, s);
-        if constexpr (COMP) load_lane<T, K>(in_e + g0, e);
+        load_lane<T, K>(in_e + g0, e);
         if constexpr (SRC) load_lane<T, K>(srcb + g0, b);
-    }
-    if constexpr (!COMP) {
-#pragma unroll
-        for (int j = 0; j < K; ++j) e[j] = T(0);
     }
 }
 
 // Advance the loaded window of tile t (start ws) by the launch's levels and
 // store its core.
-template <typename T, int K, int NW, bool COMP, bool SRC, bool WALL>
-__device__ __forceinline__ void sweep_tile(const TileArgs &a, int tid, int64_t t, int64_t ws,
+template <typename T, int K, int NW, bool SRC, bool WALL>
+__device__ __forceinline__ void sweep_pair(const TileArgs &a, int tid, int64_t t, int64_t ws,
                                            T (&s)[K], T (&e)[K], const T (&b)[K])
 {
     constexpr int W = NW * kWave * K;
@@ -97,7 +308,7 @@ __device__ __forceinline__ void sweep_tile(const TileArgs &a, int tid, int64_t t
     if (own_L) accL = a.flux[0];
     if (own_R) accR = a.flux[1];
 
-    const Coef<T> cf = lane_coef(Coef<T>{(T)a.c1, (T)a.c2, (T)a.cs, (T)a.e1, (T)a.e2, (T)a.es});
+    const PairCoef<T> cf = lane_coef(PairCoef<T>{(T)a.c1, (T)a.c2, (T)a.cs, (T)a.e1, (T)a.e2, (T)a.es});
     FluxTap ft{own_L && tid == 0, accL, a.tau, a.h, 0.0};
 
     // Interior tiles with a source form each point's source weight for both
@@ -118,9 +329,9 @@ __device__ __forceinline__ void sweep_tile(const TileArgs &a, int tid, int64_t t
             if (a.gr_t) { gro = a.gr_t[lev]; grn = a.gr_t[lev + 1]; }
             if (ghost_in) {
                 T gh, gl_;
-                split_wall<T, COMP>(gro, gh, gl_);
+                split_wall<T, true>(gro, gh, gl_);
                 put_at<T, K>(s, kR, tid == lR, gh);
-                if constexpr (COMP) put_at<T, K>(e, kR, tid == lR, gl_);
+                put_at<T, K>(e, kR, tid == lR, gl_);
             }
         }
 
@@ -133,7 +344,7 @@ __device__ __forceinline__ void sweep_tile(const TileArgs &a, int tid, int64_t t
             const int pb = lev & 1;
             if (lane == 0) { xs[pb][w][0] = s[0]; xs[pb][w][1] = s[1]; }
             if (lane == kWave - 1) { xs[pb][w][2] = s[K - 2]; xs[pb][w][3] = s[K - 1]; }
-            if constexpr (COMP) {
+            {
                 if (lane == 0) { xe[pb][w][0] = e[0]; xe[pb][w][1] = e[1]; }
                 if (lane == kWave - 1) { xe[pb][w][2] = e[K - 2]; xe[pb][w][3] = e[K - 1]; }
             }
@@ -141,7 +352,7 @@ __device__ __forceinline__ void sweep_tile(const TileArgs &a, int tid, int64_t t
             const int wl = w > 0 ? w - 1 : 0, wr = w < NW - 1 ? w + 1 : NW - 1;
             xl = xs[pb][wl][3]; xr = xs[pb][wr][0];
             xl2 = xs[pb][wl][2]; xr2 = xs[pb][wr][1];
-            if constexpr (COMP) {
+            {
                 yl = xe[pb][wl][3]; yr = xe[pb][wr][0];
                 yl2 = xe[pb][wl][2]; yr2 = xe[pb][wr][1];
             }
@@ -152,48 +363,48 @@ __device__ __forceinline__ void sweep_tile(const TileArgs &a, int tid, int64_t t
         if constexpr (WALL) {
             if (left_wall && w == 0) {
                 T gh, glw;
-                split_wall<T, COMP>(glo, gh, glw);
+                split_wall<T, true>(glo, gh, glw);
                 xl = gh;
-                if constexpr (COMP) yl = glw;
+                yl = glw;
             }
             if (ghost_edge && w == NW - 1) {
                 T gh, glw;
-                split_wall<T, COMP>(gro, gh, glw);
+                split_wall<T, true>(gro, gh, glw);
                 xr = gh;
-                if constexpr (COMP) yr = glw;
+                yr = glw;
             }
             wlv.dgl = (T)(gln - glo);
             wlv.isL = left_wall && (p == 1) && (tid == 0);
             ft.gln = gln;
-            split_wall<T, COMP>(gro, gr_hi, gr_lo);
+            split_wall<T, true>(gro, gr_hi, gr_lo);
             dgr = (T)(grn - gro);
             singR = has_S && (((n - 1 + p) & 1) == 0);
         }
         const T an = SRC ? (T)a.src_a[lev] : T(0);
         Lone<T> lone{T(0), T(0)};
         if (WALL && singR)
-            lone = right_lone<T, K, COMP, SRC>(s, e, b, kS, xl, yl, gr_hi, gr_lo, dgr, cf, an);
+            lone = right_lone<T, K, SRC>(s, e, b, kS, xl, yl, gr_hi, gr_lo, dgr, cf, an);
         if constexpr (COMB) {
             if constexpr (p == 0)
-                ge_level<T, K, COMP, 2, WALL, p, NW == 1 && !WALL>(s, e, B0, bl, br, xl, xl2, xr,
+                pair_level<T, K, 2, WALL, p, NW == 1 && !WALL>(s, e, B0, bl, br, xl, xl2, xr,
                                                                    xr2, yl, yl2, yr, yr2, cf, an,
                                                                    wlv, ft);
             else
-                ge_level<T, K, COMP, 2, WALL, p, NW == 1 && !WALL>(s, e, B1, bl, br, xl, xl2, xr,
+                pair_level<T, K, 2, WALL, p, NW == 1 && !WALL>(s, e, B1, bl, br, xl, xl2, xr,
                                                                    xr2, yl, yl2, yr, yr2, cf, an,
                                                                    wlv, ft);
         } else {
-            ge_level<T, K, COMP, SRC ? 1 : 0, WALL, p, NW == 1 && !WALL>(
+            pair_level<T, K, SRC ? 1 : 0, WALL, p, NW == 1 && !WALL>(
                 s, e, b, bl, br, xl, xl2, xr, xr2, yl, yl2, yr, yr2, cf, an, wlv, ft);
         }
         if (WALL && singR) {
             put_at<T, K>(s, kS, tid == lS, lone.s);
-            if constexpr (COMP) put_at<T, K>(e, kS, tid == lS, lone.e);
+            put_at<T, K>(e, kS, tid == lS, lone.e);
         }
         if (WALL && own_R) {
             // wall first difference at the new level, accumulated in FP64
             const double v = (double)get_at<T, K>(s, kS, T(0)) +
-                             (COMP ? (double)get_at<T, K>(e, kS, T(0)) : 0.0);
+                             (double)get_at<T, K>(e, kS, T(0));
             if (tid == lS) accR = accR + a.tau * (v - grn) / a.h;
         }
     });
@@ -205,20 +416,36 @@ __device__ __forceinline__ void sweep_tile(const TileArgs &a, int tid, int64_t t
     T fin = T(0);
     if constexpr (WALL) {
         store_lane_guarded<T, K>(out_s + g0, g0, core_lo, core_hi, s, fin);
-        if constexpr (COMP) store_lane_guarded<T, K>(out_e + g0, g0, core_lo, core_hi, e, fin);
+        store_lane_guarded<T, K>(out_e + g0, g0, core_lo, core_hi, e, fin);
     } else {
         store_lane_chunks<T, K>(out_s + g0, g0, core_lo, core_hi, s, fin);
-        if constexpr (COMP) store_lane_chunks<T, K>(out_e + g0, g0, core_lo, core_hi, e, fin);
+        store_lane_chunks<T, K>(out_e + g0, g0, core_lo, core_hi, e, fin);
     }
     raise_if_nonfinite(a.status, fin);
 }
 
-template <typename T, int K, int NW, bool COMP, bool SRC, bool WALL>
-__device__ __forceinline__ void run_tile(const TileArgs &a, int tid, int64_t t, int64_t ws)
+template <typename T, int K, int NW, bool SRC, bool WALL>
+__device__ __forceinline__ void run_pair(const TileArgs &a, int tid, int64_t t, int64_t ws)
 {
     T s[K], e[K], b[K];
-    load_tile<T, K, COMP, SRC, WALL>(a, tid, ws, s, e, b);
-    sweep_tile<T, K, NW, COMP, SRC, WALL>(a, tid, t, ws, s, e, b);
+    load_pair<T, K, SRC, WALL>(a, tid, ws, s, e, b);
+    sweep_pair<T, K, NW, SRC, WALL>(a, tid, t, ws, s, e, b);
+}
+
+// Tile t's window, whichever kind it is (n >= W for FP64 and FP32).
+template <typename T, int K, int NW, bool COMP, bool SRC>
+__device__ __forceinline__ void run_tile(const TileArgs &a, int tid, int64_t t)
+{
+    constexpr int64_t W = NW * kWave * K;
+    if constexpr (COMP) {
+        const int64_t ws = t == 0 ? 0 : t * a.core - a.halo;
+        if (ws == 0 || ws + W >= a.n) run_pair<T, K, NW, SRC, true>(a, tid, t, ws);
+        else run_pair<T, K, NW, SRC, false>(a, tid, t, ws);
+    } else {
+        const int64_t ws = window_start<W>(a, t);
+        if (t == 0 || ws + W == a.n) run_plain<T, K, NW, SRC, kEnds>(a, tid, t, ws);
+        else run_plain<T, K, NW, SRC, kOpen>(a, tid, t, ws);
+    }
 }
 
 }  // namespace dev
