@@ -25,21 +25,44 @@ struct ConvArgs {
 };
 
 struct WgradArgs {
-    const void *x;        // bf16 [batch][width][cin]
-    const void *g;        // bf16 [batch][width][cout]
-    float *part;          // per-workgroup partials
+    const void *x;        // bf16 [batch][width][padded input channels]
+    const void *g;        // bf16 [batch][width][padded output channels]
+    float *part;          // per-workgroup sums, wgrad_part_floats each
     int width;
     int batch;
     int dil;              // tap spacing of the layer
 };
 
+// One layer of a reduction: its workgroups' sums into its flat gradient.
+struct WgradReduce {
+    const float *part;
+    float *grad;
+    int ci, co;           // real channels
+};
+struct WgradReduceLayer {
+    const float *part;
+    float *grad;
+    int ci, co, ni, mo;   // real and computed channels
+    int block0;           // first block of the launch that works on it
+};
+struct WgradReduceArgs {
+    WgradReduceLayer l[6];
+    int layers, nblocks;
+};
+
 constexpr int kMaxWgradBlocks = 256;
 constexpr int kMaxDil = 16;         // largest tap spacing of a layer
+constexpr int kWgradSegment = 128;  // positions a half workgroup reduces at a time
 
 hipError_t launch_conv(int cin, int cout, int epi, const ConvArgs &a, int batch, hipStream_t s);
-hipError_t launch_wgrad(int cin, int cout, const WgradArgs &a, int blocks, hipStream_t s);
-hipError_t launch_wgrad_reduce(const float *part, int nblocks, int cinp, int coutp, int ci,
-                               int co, float *grad, hipStream_t s);
+// Weight gradients (ge_nn_wgrad.hip): the workgroups of a launch, the floats
+// one of them writes for a layer of ci and co real channels, the products, and
+// the sums of up to six layers in one launch.
+int wgrad_blocks(int width, int batch);
+int64_t wgrad_part_floats(int ci, int co);
+hipError_t launch_wgrad(int ci, int co, const WgradArgs &a, int blocks, hipStream_t s);
+hipError_t launch_wgrad_reduce(const WgradReduce *r, int layers, int nblocks, hipStream_t s);
+hipError_t launch_rod_scale(const float *u, int W, int batch, float *scale, hipStream_t s);
 hipError_t launch_features(const float *u, const float *r, int W, int batch, void *x,
                            float *scale, hipStream_t s);
 hipError_t launch_loss(const float *out, const float *u, const float *u64, const float *r,

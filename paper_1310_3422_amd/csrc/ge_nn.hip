@@ -13,8 +13,7 @@
 // transposed) -- runs in conv_kernel as an implicit GEMM on
 // v_mfma_f32_16x16x32_bf16: A = activations (positions x input channels),
 // B = weights (input x output channels), K = 5 taps x input channels.  The
-// weight gradient runs in wgrad_kernel (K = positions) with a fixed-order
-// reduction over workgroups, so training is deterministic.
+// weight gradients are in ge_nn_wgrad.hip.
 #include <hip/hip_bf16.h>
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -167,152 +166,25 @@ __global__ __launch_bounds__(kThreads) void conv_kernel(ConvArgs a)
 }
 
 // ---------------------------------------------------------------------------
-// Weight gradient dW[k][o][i] = sum_{b,w} g[b][w][o] x[b][w + (k - 2) d][i] and
-// bias gradient db[o] = sum g[b][w][o].  One wave per tap (5 waves); each
-// workgroup reduces a fixed range of 128-position segments into registers
-// and writes its partial sums; wgrad_reduce adds the partials in order.
-// The GEMM runs with M = output channels, N = input channels, K = positions,
-// from LDS tiles stored transposed (positions contiguous): gT[o][p] and, per
-// tap, xT[i][p] = x[p + (k - 2) d][i].
-constexpr int kWP = 128;               // positions per segment
-constexpr int kWS = kWP + 8;           // padded LDS row (bf16)
-
-template <int CIN, int COUT>
-__global__ __launch_bounds__(64 * kTaps) void wgrad_kernel(WgradArgs a)
-{
-    constexpr int MT = COUT / 16, NT = CIN / 16;
-    __shared__ __attribute__((aligned(16))) bf16 gT[COUT * kWS];
-    __shared__ __attribute__((aligned(16))) bf16 xT[kTaps * CIN * kWS];
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int tap = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int r16 = lane & 15, g4 = lane >> 4;
-    const int W = a.width;
-    const int segs_per_rod = W / kWP;
-    const int64_t nseg = (int64_t)a.batch * segs_per_rod;
-    const int64_t s_lo = nseg * blockIdx.x / gridDim.x;
-    const int64_t s_hi = nseg * (blockIdx.x + 1) / gridDim.x;
-
-    f32x4 acc[MT][NT];
-#pragma unroll
-    for (int m = 0; m < MT; ++m)
-#pragma unroll
-        for (int n = 0; n < NT; ++n) acc[m][n] = f32x4{0.f, 0.f, 0.f, 0.f};
-    float dbias = 0.f;   // thread tid < COUT accumulates db[tid]
-
-    const bf16 *gsrc = static_cast<const bf16 *>(a.g);
-    const bf16 *xsrc = static_cast<const bf16 *>(a.x);
-    for (int64_t sg = s_lo; sg < s_hi; ++sg) {
-        const int64_t b = sg / segs_per_rod;
-        const int p0 = (int)(sg % segs_per_rod) * kWP;
-        __syncthreads();   // previous segment's tiles are no longer read
-        // g tile, transposed: gT[o][p] = g[b][p0 + p][o]
-        for (int i = tid; i < kWP * COUT; i += 64 * kTaps) {
-            const int p = i / COUT, o = i % COUT;
-            gT[o * kWS + p] = gsrc[((int64_t)b * W + p0 + p) * COUT + o];
-        }
-        // x tiles per tap, transposed and shifted: xT[k][i][p] = x[b][p0 + p + (k - 2) d][i]
-        for (int i = tid; i < kTaps * kWP * CIN; i += 64 * kTaps) {
-            const int k = i / (kWP * CIN), rem = i % (kWP * CIN);
-            const int p = rem / CIN, ci = rem % CIN;
-            const int w = p0 + p + (k - 2) * a.dil;
-            xT[(k * CIN + ci) * kWS + p] =
-                (w >= 0 && w < W) ? xsrc[((int64_t)b * W + w) * CIN + ci] : (bf16)0.0f;
-        }
-        __syncthreads();
-        if (tid < COUT) {
-            float sacc = 0.f;
-            for (int p = 0; p < kWP; ++p) sacc += bf2f(gT[tid * kWS + p]);
-            dbias += sacc;
-        }
-#pragma unroll
-        for (int ks = 0; ks < kWP / 32; ++ks) {
-            bf16x8 af[MT], bfr[NT];
-#pragma unroll
-            for (int m = 0; m < MT; ++m)
-                af[m] = *reinterpret_cast<const bf16x8 *>(
-                    &gT[(16 * m + r16) * kWS + 32 * ks + 8 * g4]);
-#pragma unroll
-            for (int n = 0; n < NT; ++n)
-                bfr[n] = *reinterpret_cast<const bf16x8 *>(
-                    &xT[(tap * CIN + 16 * n + r16) * kWS + 32 * ks + 8 * g4]);
-#pragma unroll
-            for (int m = 0; m < MT; ++m)
-#pragma unroll
-                for (int n = 0; n < NT; ++n)
-                    acc[m][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[m], bfr[n], acc[m][n],
-                                                                       0, 0, 0);
-        }
-    }
-    // partial sums: part[block][k][o][i] and part_db[block][o]
-    float *part = a.part + (int64_t)blockIdx.x * (kTaps * COUT * CIN + COUT);
-#pragma unroll
-    for (int m = 0; m < MT; ++m)
-#pragma unroll
-        for (int n = 0; n < NT; ++n)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int o = 16 * m + 4 * g4 + j, ci = 16 * n + r16;
-                part[(tap * COUT + o) * CIN + ci] = acc[m][n][j];
-            }
-    if (tid < COUT) part[kTaps * COUT * CIN + tid] = dbias;
-}
-
-// Sum the workgroups' partials in workgroup order into the flat, unpadded
-// gradient of one layer: dw[(k*co + o)*ci + i] then db[o].
-__global__ void wgrad_reduce_kernel(const float *part, int nblocks, int cinp, int coutp, int ci,
-                                    int co, float *grad)
-{
-    const int64_t nw = (int64_t)kTaps * co * ci;
-    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= nw + co) return;
-    int64_t src;
-    if (e < nw) {
-        const int k = (int)(e / ((int64_t)co * ci));
-        const int o = (int)((e / ci) % co), i = (int)(e % ci);
-        src = ((int64_t)k * coutp + o) * cinp + i;
-    } else {
-        src = (int64_t)kTaps * coutp * cinp + (e - nw);
-    }
-    const int64_t stride = (int64_t)kTaps * coutp * cinp + coutp;
-    float s = 0.f;
-    for (int bk = 0; bk < nblocks; ++bk) s += part[(int64_t)bk * stride + src];
-    grad[e] = s;
-}
-
-// ---------------------------------------------------------------------------
-// Features of one rod (one workgroup per rod): the second difference
-// D_i = u_{i-1} - 2u_i + u_{i+1} (zero walls) scaled by its RMS s, and the
-// mesh ratio mapped to [-1, 1] over [0.5, 2]; other channels zero.
+// Features of one rod: the second difference D_i = u_{i-1} - 2u_i + u_{i+1}
+// (zero walls) scaled by its RMS s (rod_scale_kernel), and the mesh ratio
+// mapped to [-1, 1] over [0.5, 2]; other channels zero.  One thread a point,
+// its 64-byte row in four stores.
 __global__ __launch_bounds__(256) void features_kernel(const float *u, const float *r, int W,
-                                                       bf16 *x, float *scale)
+                                                       int64_t M, bf16 *x, const float *scale)
 {
-    const int b = blockIdx.x, tid = threadIdx.x;
+    const int64_t p = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (p >= M) return;
+    const int b = (int)(p / W), i = (int)(p - (int64_t)b * W);
     const float *ub = u + (int64_t)b * W;
-    __shared__ float red[256];
-    float ss = 0.f;
-    for (int i = tid; i < W; i += 256) {
-        const float um = i > 0 ? ub[i - 1] : 0.f, up = i < W - 1 ? ub[i + 1] : 0.f;
-        const float d = (um - ub[i]) + (up - ub[i]);
-        ss += d * d;
-    }
-    red[tid] = ss;
-    __syncthreads();
-    for (int s = 128; s > 0; s >>= 1) {
-        if (tid < s) red[tid] += red[tid + s];
-        __syncthreads();
-    }
-    const float sc = sqrtf(red[0] / W) + 1e-30f;
-    if (tid == 0) scale[b] = sc;
+    const float um = i > 0 ? ub[i - 1] : 0.f, up = i < W - 1 ? ub[i + 1] : 0.f;
+    const float d = (um - ub[i]) + (up - ub[i]);
     const float rn = (r[b] - 1.25f) / 0.75f;
-    bf16 *xb = x + (int64_t)b * W * 32;
-    for (int i = tid; i < W; i += 256) {
-        const float um = i > 0 ? ub[i - 1] : 0.f, up = i < W - 1 ? ub[i + 1] : 0.f;
-        const float d = (um - ub[i]) + (up - ub[i]);
-        bf16 *row = xb + (int64_t)i * 32;
-        row[0] = f2bf(d / sc);
-        row[1] = f2bf(rn);
-        for (int c = 2; c < 32; ++c) row[c] = f2bf(0.f);
-    }
+    const uint32_t lo = (uint32_t)__builtin_bit_cast(uint16_t, f2bf(d / scale[b])) |
+                        ((uint32_t)__builtin_bit_cast(uint16_t, f2bf(rn)) << 16);
+    uint4 *row = reinterpret_cast<uint4 *>(x + p * 32);
+    row[0] = make_uint4(lo, 0, 0, 0);
+    row[1] = row[2] = row[3] = make_uint4(0, 0, 0, 0);
 }
 
 // Loss on the normalised increment t = (u64 - u) / (64 r s), and its
@@ -331,9 +203,9 @@ __global__ __launch_bounds__(256) void loss_kernel(const float *out, const float
         const float t = (u64[i] - u[i]) / (64.0f * r[b] * scale[b]);
         const float d = out[i] - t;
         e2 = d * d;
-        bf16 *gr = g + i * 32;
-        gr[0] = f2bf(2.0f * d / (float)M);
-        for (int c = 1; c < 32; ++c) gr[c] = f2bf(0.f);
+        uint4 *gr = reinterpret_cast<uint4 *>(g + i * 32);
+        gr[0] = make_uint4(__builtin_bit_cast(uint16_t, f2bf(2.0f * d / (float)M)), 0, 0, 0);
+        gr[1] = gr[2] = gr[3] = make_uint4(0, 0, 0, 0);
     }
     red[threadIdx.x] = e2;
     __syncthreads();
@@ -344,13 +216,22 @@ __global__ __launch_bounds__(256) void loss_kernel(const float *out, const float
     if (threadIdx.x == 0) part[blockIdx.x] = red[0];
 }
 
-__global__ void sum_in_order_kernel(const float *part, int n, float scale, float *out)
+// The partial sums added in a fixed order: each of 256 threads adds every
+// 256th, then a tree over the threads.
+__global__ __launch_bounds__(256) void sum_parts_kernel(const float *part, int n, float scale,
+                                                        float *out)
 {
-    if (threadIdx.x == 0 && blockIdx.x == 0) {
-        float s = 0.f;
-        for (int i = 0; i < n; ++i) s += part[i];
-        out[0] = s * scale;
+    __shared__ float red[256];
+    const int tid = threadIdx.x;
+    float s = 0.f;
+    for (int i = tid; i < n; i += 256) s += part[i];
+    red[tid] = s;
+    __syncthreads();
+    for (int k = 128; k > 0; k >>= 1) {
+        if (tid < k) red[tid] += red[tid + k];
+        __syncthreads();
     }
+    if (tid == 0) out[0] = red[0] * scale;
 }
 
 // u_next = u + 64 r s out (the jump), optionally to a separate buffer
@@ -502,35 +383,14 @@ hipError_t launch_conv(int cin, int cout, int epi, const ConvArgs &a, int batch,
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_wgrad(int cin, int cout, const WgradArgs &a, int blocks, hipStream_t s)
-{
-    if (a.dil < 1 || a.dil > kMaxDil) return hipErrorInvalidValue;
-#define GE_WG(CI, CO) \
-    if (cin == CI && cout == CO) { \
-        hipLaunchKernelGGL((wgrad_kernel<CI, CO>), dim3(blocks), dim3(64 * kTaps), 0, s, a); \
-        return hipGetLastError(); \
-    }
-    GE_WG(32, 64)
-    GE_WG(64, 64)
-    GE_WG(64, 32)
-#undef GE_WG
-    return hipErrorInvalidValue;
-}
-
-hipError_t launch_wgrad_reduce(const float *part, int nblocks, int cinp, int coutp, int ci,
-                               int co, float *grad, hipStream_t s)
-{
-    const int64_t n = (int64_t)kTaps * co * ci + co;
-    hipLaunchKernelGGL(wgrad_reduce_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s,
-                       part, nblocks, cinp, coutp, ci, co, grad);
-    return hipGetLastError();
-}
-
 hipError_t launch_features(const float *u, const float *r, int W, int batch, void *x,
                            float *scale, hipStream_t s)
 {
-    hipLaunchKernelGGL(features_kernel, dim3(batch), dim3(256), 0, s, u, r, W,
-                       static_cast<bf16 *>(x), scale);
+    hipError_t e = launch_rod_scale(u, W, batch, scale, s);
+    if (e != hipSuccess) return e;
+    const int64_t M = (int64_t)W * batch;
+    hipLaunchKernelGGL(features_kernel, dim3((unsigned)((M + 255) / 256)), dim3(256), 0, s, u, r, W,
+                       M, static_cast<bf16 *>(x), scale);
     return hipGetLastError();
 }
 
@@ -544,8 +404,7 @@ hipError_t launch_loss(const float *out, const float *u, const float *u64, const
                        static_cast<bf16 *>(g), part);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || !loss) return e;
-    hipLaunchKernelGGL(sum_in_order_kernel, dim3(1), dim3(64), 0, s, part, nb, 1.0f / (float)M,
-                       loss);
+    hipLaunchKernelGGL(sum_parts_kernel, dim3(1), dim3(256), 0, s, part, nb, 1.0f / (float)M, loss);
     return hipGetLastError();
 }
 

@@ -87,7 +87,8 @@ struct ge_nn_s {
     float *bf[6];                   // padded biases
     void *x;                        // bf16 [B][W][32] features
     void *pre[5], *h[5];            // bf16 [B][W][64]
-    float *out, *scale, *loss_part, *wpart;
+    float *out, *scale, *loss_part;
+    float *wpart[6];                // weight-gradient sums of the workgroups, per layer
     void *gl;                       // bf16 [B][W][32] loss gradient
     void *gh, *gp[2];               // bf16 [B][W][64]
     float *save, *unn;              // re-checked stepping: window start, network result
@@ -186,23 +187,16 @@ hipError_t fused_jump(ge_nn_s *n, const float *u, const float *r, int batch, flo
     return launch_jump_fused(a, batch, s);
 }
 
-int wgrad_blocks(ge_nn_s *n, int batch)
-{
-    const int64_t nseg = (int64_t)batch * (n->width / 128);
-    return (int)std::min<int64_t>(kMaxWgradBlocks, nseg);
-}
-
 // loss gradient already in n->gl; fills n->g (flat parameter gradient)
 hipError_t backward(ge_nn_s *n, int batch, hipStream_t s)
 {
     const int W = n->width;
-    const int nb = wgrad_blocks(n, batch);
+    const int nb = wgrad_blocks(W, batch);
     // layer 6: weight gradient from h5 and the loss gradient; input gradient
     {
         const Layer &L = kLayers[5];
-        WgradArgs wa{n->h[4], n->gl, n->wpart, W, batch, L.dil};
-        hipError_t e = launch_wgrad(64, 32, wa, nb, s);
-        if (e == hipSuccess) e = launch_wgrad_reduce(n->wpart, nb, 64, 32, L.ci, L.co, n->g + L.off, s);
+        WgradArgs wa{n->h[4], n->gl, n->wpart[5], W, batch, L.dil};
+        hipError_t e = launch_wgrad(L.ci, L.co, wa, nb, s);
         if (e != hipSuccess) return e;
         ConvArgs a{};
         a.x = n->gl;
@@ -219,9 +213,8 @@ hipError_t backward(ge_nn_s *n, int batch, hipStream_t s)
     int cur = 0;
     for (int l = 4; l >= 1; --l) {
         const Layer &L = kLayers[l];
-        WgradArgs wa{n->h[l - 1], n->gp[cur], n->wpart, W, batch, L.dil};
-        hipError_t e = launch_wgrad(64, 64, wa, nb, s);
-        if (e == hipSuccess) e = launch_wgrad_reduce(n->wpart, nb, 64, 64, L.ci, L.co, n->g + L.off, s);
+        WgradArgs wa{n->h[l - 1], n->gp[cur], n->wpart[l], W, batch, L.dil};
+        hipError_t e = launch_wgrad(L.ci, L.co, wa, nb, s);
         if (e != hipSuccess) return e;
         ConvArgs a{};
         a.x = n->gp[cur];
@@ -237,10 +230,13 @@ hipError_t backward(ge_nn_s *n, int batch, hipStream_t s)
         cur = 1 - cur;
     }
     const Layer &L = kLayers[0];
-    WgradArgs wa{n->x, n->gp[cur], n->wpart, W, batch, L.dil};
-    hipError_t e = launch_wgrad(32, 64, wa, nb, s);
-    if (e == hipSuccess) e = launch_wgrad_reduce(n->wpart, nb, 32, 64, L.ci, L.co, n->g + L.off, s);
-    return e;
+    WgradArgs wa{n->x, n->gp[cur], n->wpart[0], W, batch, L.dil};
+    hipError_t e = launch_wgrad(L.ci, L.co, wa, nb, s);
+    if (e != hipSuccess) return e;
+    WgradReduce red[6];
+    for (int l = 0; l < 6; ++l)
+        red[l] = WgradReduce{n->wpart[l], n->g + kLayers[l].off, kLayers[l].ci, kLayers[l].co};
+    return launch_wgrad_reduce(red, 6, nb, s);
 }
 
 }  // namespace
@@ -269,7 +265,6 @@ ge_status ge_nn_create(ge_nn_t *out, int32_t width, int32_t max_batch, uint64_t 
               dalloc(n, &n->x, M * 32 * 2) && dalloc(n, &n->out, M * 4) &&
               dalloc(n, &n->scale, (size_t)max_batch * 4) &&
               dalloc(n, &n->loss_part, ((M + 255) / 256 + 1) * 4) &&
-              dalloc(n, &n->wpart, (size_t)kMaxWgradBlocks * (5 * 64 * 64 + 64) * 4) &&
               dalloc(n, &n->gl, M * 32 * 2) && dalloc(n, &n->gh, M * 64 * 2) &&
               dalloc(n, &n->gp[0], M * 64 * 2) && dalloc(n, &n->gp[1], M * 64 * 2);
     for (int l = 0; ok && l < 5; ++l)
@@ -280,7 +275,9 @@ ge_status ge_nn_create(ge_nn_t *out, int32_t width, int32_t max_batch, uint64_t 
     ok = ok && hipHostMalloc((void **)&n->h_count, sizeof(int), hipHostMallocDefault) == hipSuccess;
     for (int l = 0; ok && l < 6; ++l) {
         const Layer &L = kLayers[l];
-        ok = dalloc(n, &n->wf[l], 5LL * L.cop * L.cip * 2) && dalloc(n, &n->bf[l], L.cop * 4);
+        ok = dalloc(n, &n->wpart[l],
+                    wgrad_blocks(width, max_batch) * (size_t)wgrad_part_floats(L.ci, L.co) * 4);
+        ok = ok && dalloc(n, &n->wf[l], 5LL * L.cop * L.cip * 2) && dalloc(n, &n->bf[l], L.cop * 4);
         if (ok && l > 0) ok = dalloc(n, &n->wd[l], 5LL * L.cip * L.cod * 2);
     }
     if (!ok) {
@@ -448,10 +445,11 @@ ge_status ge_nn_layer_probe(ge_nn_t n, int32_t layer, int32_t op, const void *x,
                     : launch_conv(L.cod, L.cip, kEpiF32, a, batch, s);
     } else if (op == 2) {
         if (!x || !g) return fail(GE_ERR_INVALID, "ge_nn_layer_probe: x and g must be given");
-        const int nb = wgrad_blocks(n, batch);
-        WgradArgs wa{x, g, n->wpart, n->width, batch, L.dil};
-        e = launch_wgrad(L.cip, L.cod, wa, nb, s);
-        if (e == hipSuccess) e = launch_wgrad_reduce(n->wpart, nb, L.cip, L.cod, L.ci, L.co, out, s);
+        const int nb = wgrad_blocks(n->width, batch);
+        WgradArgs wa{x, g, n->wpart[l], n->width, batch, L.dil};
+        e = launch_wgrad(L.ci, L.co, wa, nb, s);
+        const WgradReduce red{n->wpart[l], out, L.ci, L.co};
+        if (e == hipSuccess) e = launch_wgrad_reduce(&red, 1, nb, s);
     } else {
         return fail(GE_ERR_INVALID, "ge_nn_layer_probe: op %d is not 0, 1 or 2", op);
     }

@@ -299,8 +299,7 @@ __global__ __launch_bounds__(kFThreads) void jump_fused_kernel(FusedArgs a)
     }
 }
 
-// Per-rod scale: RMS of the rod's second differences (zero walls), in the
-// same summation order as features_kernel.
+// Per-rod scale: RMS of the rod's second differences (zero walls).
 __global__ __launch_bounds__(256) void rod_scale_kernel(const float *u, int W, float *scale)
 {
     const int b = blockIdx.x, tid = threadIdx.x;
@@ -323,6 +322,12 @@ __global__ __launch_bounds__(256) void rod_scale_kernel(const float *u, int W, f
 
 }  // namespace
 
+hipError_t launch_rod_scale(const float *u, int W, int batch, float *scale, hipStream_t s)
+{
+    hipLaunchKernelGGL(rod_scale_kernel, dim3(batch), dim3(256), 0, s, u, W, scale);
+    return hipGetLastError();
+}
+
 hipError_t launch_jump_fused(const FusedArgs &a, int batch, hipStream_t s)
 {
     int reach = 0;
@@ -331,8 +336,7 @@ hipError_t launch_jump_fused(const FusedArgs &a, int batch, hipStream_t s)
         reach += 2 * a.dil[l];
     }
     if (reach > kFHalo) return hipErrorInvalidValue;   // the tile would not stay valid
-    hipLaunchKernelGGL(rod_scale_kernel, dim3(batch), dim3(256), 0, s, a.u, a.width, a.scale);
-    hipError_t e = hipGetLastError();
+    hipError_t e = launch_rod_scale(a.u, a.width, batch, a.scale, s);
     if (e != hipSuccess) return e;
     const dim3 grid((a.width + kFP - 1) / kFP, batch);
     hipLaunchKernelGGL(jump_fused_kernel, grid, dim3(kFThreads), 0, s, a);
