@@ -98,7 +98,10 @@ typedef struct {
     int32_t tile;       /* points per lane (even; 0 = the library's choice)   */
     int32_t depth;      /* levels fused per launch (>= 1; 0 = library choice) */
     int32_t waves;      /* waves per workgroup (1 or 4, with k >= 2 also 2    */
-                        /* and 8; 0 = library choice)                         */
+                        /* and 8; 0 = library choice).  With tile, depth,     */
+                        /* waves and schedule all 0, FP64 and FP32 rods of    */
+                        /* 256 to 768000 points run in windows of 4 or 8      */
+                        /* overlapping waves at a depth of their own.         */
     double g_left;      /* wall value g_L, used when a call gives no array    */
     double g_right;     /* wall value g_R, likewise                           */
     const void *src_b;  /* device, n values of the state's element type       */

@@ -163,6 +163,83 @@ bool persistent_pays(int prec, int tile, int waves, int depth, bool src)
            ge::persistent_supported(prec, tile) && (tile >= 32 || prec == ge::kFP64);
 }
 
+// A rod that leaves compute units idle under tiles runs in windows of
+// overlapping waves (launch_block).  The time of a call is then its levels
+// times one level's latency plus its launches' fixed cost, about 6 us:
+// measured (960 levels, FP64; FP32 within 5%) at 0.087, 0.101, 0.115, 0.13 and
+// 0.155 us a level for the shapes below, growing with the points a wave
+// steps.  One window per unit, so a shape's core is n / 256 and its halo, hence
+// the levels per launch, what its capacity leaves.  At 262655 points 8 points
+// a lane, 438 levels per launch: 121 us for 960 levels (tiles at best 179, at
+// 32 points a lane 289); at 700000 8 x 8 waves, 160 us (220); from 768000 on
+// the tiles' many small windows fill the chip and win.  Rods of up to 2048
+// points take one window and no workspace whatever the cost.
+struct BlockShape {
+    int k, waves;
+    double level_us;
+};
+constexpr BlockShape kBlockShapes[] = {{4, 4, 0.087}, {6, 4, 0.101}, {8, 4, 0.115}, {10, 4, 0.13},
+                                       {8, 8, 0.155}};
+constexpr double kBlockLaunchUs = 6.0;
+constexpr int64_t kBlockMin = 256, kBlockOneWindow = 2048, kBlockMax = 768000;
+constexpr int64_t kComputeUnits = 256;
+
+struct BlockChoice {
+    int k, waves, depth, halo;
+    int64_t core;
+};
+
+bool block_choice(int prec, int64_t n, BlockChoice *out)
+{
+    if (prec == ge::kFP32C || n < kBlockMin || n > kBlockMax)
+        return false;
+    double best = 1e300;
+    for (const BlockShape &s : kBlockShapes) {
+        const int64_t cap = ge::block_capacity(s.k, s.waves);
+        if (n < 64 * s.k)
+            continue;
+        if (n <= kBlockOneWindow) {
+            if (n > cap)
+                continue;
+            *out = BlockChoice{s.k, s.waves, 1 << 16, 0, n};
+            return true;
+        }
+        const int64_t core = round_up((n + kComputeUnits - 1) / kComputeUnits, 2);
+        const int halo = (int)((cap - core) / 4 * 2);
+        if (halo < 65)
+            continue;
+        const double us = s.level_us + kBlockLaunchUs / (halo - 1);
+        if (us < best) {
+            best = us;
+            *out = BlockChoice{s.k, s.waves, halo - 1, halo, core};
+        }
+    }
+    return best < 1e300;
+}
+
+// The tile of a plan that leaves everything to the library, for rods of fewer
+// than 2^23.5 points: narrower rows than a rod that fills the chip several
+// times over, so that it has enough waves (960 levels: 2e6 points FP64 20
+// points a lane 341 us, 32 points 480; FP32 16 points 374, 32 points 513; 6e6
+// points FP64 28 points 736 against 779, FP32 16 points at 64 levels 747
+// against 830; the pair at 262655 points 4 points a lane, one wave, 556
+// against 1212 with 16 points and four waves, at 6e6 8 points 2093 against
+// 2339).  A pair of up to 4096 points stays in one window.
+Choice default_for_length(int prec, int64_t n, bool src)
+{
+    if (prec == ge::kFP32C) {
+        if (n <= 4096) return {n <= 1024 ? 4 : n <= 2048 ? 8 : 16, 4, 128};
+        if (n < 600000) return {4, 1, 48};
+        if (n < 12000000) return {8, 4, 96};
+    } else if (n < kBlockMin) {
+        return {4, 1, 48};
+    } else if (n < 12000000) {
+        if (prec == ge::kFP64) return {n < 4000000 ? 20 : 28, 1, 128};
+        return {16, 1, n < 4000000 ? 128 : 64};
+    }
+    return default_choice(prec, 0, src);
+}
+
 }  // namespace
 
 struct ge_plan_s {
@@ -178,6 +255,7 @@ struct ge_plan_s {
     int64_t ntiles;
     bool single;   // the whole rod fits one window: no halo, all levels per launch
     bool persistent;  // multi-tile launches by the persistent single-wave kernel
+    bool block;    // windows of overlapping waves (launch_block)
     int sdc;       // sub-domain width k >= 2 (the sub-domain scheme), or 0
     double g_left, g_right;
     const void *src_b;
@@ -391,13 +469,20 @@ ge_status ge_plan(ge_plan_t *out, const ge_desc *d)
     const bool src = d->src_b != nullptr;
     if (depth < 0)
         return fail(GE_ERR_INVALID, "ge_plan: depth = %d, need depth >= 1", depth);
-    const Choice ch = default_choice(prec, depth, src);
+    BlockChoice bc;
+    const bool free_choice = tile == 0 && waves == 0 && depth == 0 && d->schedule == 0;
+    const bool block = free_choice && block_choice(prec, d->n, &bc);
+    const Choice ch = block ? Choice{bc.k, bc.waves, bc.depth}
+                            : free_choice ? default_for_length(prec, d->n, src)
+                                          : default_choice(prec, depth, src);
     if (tile == 0) {
         tile = ch.tile;
         if (waves == 0) waves = ch.waves;
     }
     if (waves == 0) waves = prec == ge::kFP32C ? 4 : 1;
-    if (depth == 0) {
+    if (block) {
+        depth = ch.depth;
+    } else if (depth == 0) {
         // clipped so that the halo stays within a quarter of the window
         depth = ch.depth;
         const int al = (prec == ge::kFP64) ? 2 : 4;
@@ -405,7 +490,7 @@ ge_status ge_plan(ge_plan_t *out, const ge_desc *d)
     }
     if (depth < 1)
         return fail(GE_ERR_INVALID, "ge_plan: depth = %d, need depth >= 1", depth);
-    if (!ge::tile_config_supported(prec, tile, waves))
+    if (!block && !ge::tile_config_supported(prec, tile, waves))
         return fail(GE_ERR_INVALID, "ge_plan: tile %d with %d waves is not built for precision %d",
                     tile, waves, prec);
     if (d->schedule < 0 || d->schedule > 2)
@@ -427,7 +512,15 @@ ge_status ge_plan(ge_plan_t *out, const ge_desc *d)
     p->g_right = d->g_right;
     p->src_b = d->src_b;
     const int align = (prec == ge::kFP64) ? 2 : 4;   // values per 16-byte chunk
-    if (p->n <= p->window) {
+    if (block) {
+        p->block = true;
+        p->depth = depth;
+        p->window = ge::block_capacity(tile, waves);
+        p->single = p->n <= p->window;
+        p->halo = p->single ? 0 : bc.halo;
+        p->core = p->single ? p->n : bc.core;
+        p->ntiles = (p->n + p->core - 1) / p->core;
+    } else if (p->n <= p->window) {
         // One window holds the rod and both walls: nothing enters from an
         // open edge, so every level of a call runs in one in-place launch.
         p->single = true;
@@ -452,7 +545,7 @@ ge_status ge_plan(ge_plan_t *out, const ge_desc *d)
     // enough tiles for the prefetch to matter
     const bool auto_persistent = d->schedule == 0 && persistent_pays(prec, tile, waves, p->depth, src) &&
                                  p->ntiles >= 64;
-    p->persistent = !p->single && p->ntiles >= 3 && (d->schedule == 2 || auto_persistent);
+    p->persistent = !block && !p->single && p->ntiles >= 3 && (d->schedule == 2 || auto_persistent);
     const double r = p->r;
     p->h = 1.0 / (double)(p->n + 1);
     p->tau = r * p->h * p->h;
@@ -580,6 +673,8 @@ ge_status ge_step_n(ge_plan_t plan, void *u, void *workspace, int64_t step0, int
             return plan->persistent
                        ? ge::launch_sdc_persistent(plan->prec, plan->sdc, plan->waves, la, st)
                        : ge::launch_sdc(plan->prec, plan->sdc, plan->waves, la, st);
+        if (plan->block)
+            return ge::launch_block(plan->prec, plan->tile, plan->waves, src, la, st);
         if (plan->persistent && !plan->single)
             return ge::launch_tiles_persistent(plan->prec, plan->tile, src, la, st);
         return ge::launch_tiles(plan->prec, plan->tile, plan->waves, src, la, st, side);

@@ -138,15 +138,15 @@ __device__ __forceinline__ void rod_levels(const BatchArgs &a, const BatchRod &r
             T lone = T(0);
             if constexpr (TWO_STAGE) {
                 if constexpr (P == 0) exchange(lev, xl, xr);
-                explicit_stage<T, K, P, false>(s, xl[0], xr[0], cf);
+                explicit_stage<T, K, P, false, false>(s, xl[0], xr[0], cf);
                 if constexpr (P == 1) exchange(lev, xl, xr);
                 if (WALL && single) lone = lone_point(get_at<T, K>(s, kS, T(0)), gr_hi, cf.cs);
-                solve_stage<T, K, P, false>(s, xl[0], xr[0], cf, kl, kr);
+                solve_stage<T, K, P, false, false>(s, xl[0], xr[0], cf, kl, kr);
             } else {
                 exchange(lev, xl, xr);
                 if (WALL && single)
                     lone = lone_increment<T, K, false>(s, s, T(0), kS, xl[0], gr_hi, cf.cs);
-                increment_level<T, K, false, P, false>(s, s, T(0), xl[0], xl[E - 1], xr[0],
+                increment_level<T, K, false, P, false, false>(s, s, T(0), xl[0], xl[E - 1], xr[0],
                                                        xr[E - 1], cf, cl, pl, cr, pr);
             }
             if (WALL && single) put_at<T, K>(s, kS, lane == lS, lone);
@@ -292,15 +292,15 @@ __device__ __forceinline__ void rod_block(const BatchRod &rd, T (&s)[K], T (&e)[
             const T kl = lane_l ? cf.cs : cf.k, kr = lane_r ? cf.cs : cf.k;
             for_levels(level0, nlev, [&](auto par, int) {
                 constexpr int P = decltype(par)::value;
-                explicit_stage<T, K, P, END == 0>(s, g, g, cf);
-                solve_stage<T, K, P, END == 0>(s, g, g, cf, kl, kr);
+                explicit_stage<T, K, P, END != 1, END != 2>(s, g, g, cf);
+                solve_stage<T, K, P, END != 1, END != 2>(s, g, g, cf, kl, kr);
             });
         } else {
             const T cl = lane_l ? cf.cs : cf.c1, cr = lane_r ? cf.cs : cf.c1;
             const T pl = lane_l ? T(0) : cf.cs, pr = lane_r ? T(0) : cf.cs;
             for_levels(level0, nlev, [&](auto par, int) {
-                increment_level<T, K, false, decltype(par)::value, END == 0>(s, s, T(0), g, g, g, g,
-                                                                             cf, cl, pl, cr, pr);
+                increment_level<T, K, false, decltype(par)::value, END != 1, END != 2>(
+                    s, s, T(0), g, g, g, g, cf, cl, pl, cr, pr);
             });
         }
     } else {

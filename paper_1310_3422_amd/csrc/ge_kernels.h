@@ -63,6 +63,16 @@ struct SideStream {
 hipError_t launch_tiles(int prec, int k, int nw, bool src, const TileArgs &a,
                         hipStream_t stream, const SideStream *side = nullptr);
 
+// Windows of nw overlapping waves of 64 k points (block_kernel, FP64 and
+// FP32): core and halo of `a` count points, every window holds at most
+// block_capacity points, and n >= 64 k.
+constexpr int kBlockOverlap = 24;   // half the points neighbouring waves share
+constexpr int block_capacity(int k, int nw)
+{
+    return 64 * k + (nw - 1) * (64 * k - 2 * kBlockOverlap);
+}
+hipError_t launch_block(int prec, int k, int nw, bool src, const TileArgs &a, hipStream_t stream);
+
 // Persistent single-wave form (tile_persistent_kernel): interior tiles
 // round-robin with the next tile's load overlapping the current sweep.
 bool persistent_supported(int prec, int k);

@@ -374,12 +374,12 @@ __device__ __forceinline__ PairCoef<T> lane_coef(PairCoef<T> c)
 // The lane's K points (K even) in place.  Parity P couples (2q, 2q+1) inside
 // the lane when P = 0 and across lanes when P = 1; the explicit stage runs
 // over the other parity's pairs.  xl, xr: the values left of lane 0 and right
-// of lane 63 (unused when OPEN: both are open window edges).
-template <typename T, int K, int P, bool OPEN>
+// of lane 63 (OL, OR: that side is an open window edge and takes no value).
+template <typename T, int K, int P, bool OL, bool OR>
 __device__ __forceinline__ void explicit_stage(T (&u)[K], T xl, T xr, const Coef<T> &c)
 {
     if constexpr (P == 0) {
-        const T ul = edge_left<OPEN>(xl, u[K - 1]), ur = edge_right<OPEN>(xr, u[0]);
+        const T ul = edge_left<OL>(xl, u[K - 1]), ur = edge_right<OR>(xr, u[0]);
         u[0] = fmaT(-c.r, u[0] - ul, u[0]);
 #pragma unroll
         for (int j = 1; j + 1 < K; j += 2) {
@@ -400,7 +400,7 @@ __device__ __forceinline__ void explicit_stage(T (&u)[K], T xl, T xr, const Coef
 
 // kl, kr: the coefficient of the lane's first and last point at P = 1 (k, or
 // cs in the lane whose point stands alone beside a wall).
-template <typename T, int K, int P, bool OPEN>
+template <typename T, int K, int P, bool OL, bool OR>
 __device__ __forceinline__ void solve_stage(T (&v)[K], T xl, T xr, const Coef<T> &c, T kl, T kr)
 {
     if constexpr (P == 0) {
@@ -411,7 +411,7 @@ __device__ __forceinline__ void solve_stage(T (&v)[K], T xl, T xr, const Coef<T>
             v[j + 1] = fmaT(-c.k, w, v[j + 1]);
         }
     } else {
-        const T vl = edge_left<OPEN>(xl, v[K - 1]), vr = edge_right<OPEN>(xr, v[0]);
+        const T vl = edge_left<OL>(xl, v[K - 1]), vr = edge_right<OR>(xr, v[0]);
         v[0] = fmaT(-kl, v[0] - vl, v[0]);
 #pragma unroll
         for (int j = 1; j + 1 < K; j += 2) {
@@ -454,15 +454,15 @@ __device__ __forceinline__ void increment_source(const T (&b)[K], T bl, T br, T 
 }
 
 // One level of parity P of the lane's K points.  xl, xl2, xr, xr2: u_{-1},
-// u_{-2}, u_K, u_{K+1} for lanes 0 / 63 (unused when OPEN).  Beside a wall xl
+// u_{-2}, u_K, u_{K+1} for lanes 0 / 63 (unused on an open side).  Beside a wall xl
 // (xr) is its old value at P = 0 and its new one at P = 1, xl2 (xr2) any
 // finite value, and cl, pl (cr, pr), the factors of the lane's first (last)
 // point at P = 1, are cs and 0 in place of c1 and cs.
-template <typename T, int K, bool SRC, int P, bool OPEN>
+template <typename T, int K, bool SRC, int P, bool OL, bool OR>
 __device__ __forceinline__ void increment_level(T (&u)[K], const T (&B)[K], T an, T xl, T xl2, T xr,
                                                 T xr2, const Coef<T> &c, T cl, T pl, T cr, T pr)
 {
-    const T ul = edge_left<OPEN>(xl, u[K - 1]), ur = edge_right<OPEN>(xr, u[0]);
+    const T ul = edge_left<OL>(xl, u[K - 1]), ur = edge_right<OR>(xr, u[0]);
     // u_j from the factors f, g of its own and its partner's second difference
     auto upd = [&](int j, T D, T Dq, T f, T g) {
         T x = fmaT(g, Dq, D);
@@ -487,11 +487,9 @@ __device__ __forceinline__ void increment_level(T (&u)[K], const T (&B)[K], T an
         const T dk = u[K - 1] - u[K - 2], dr = ur - u[K - 1];
         const T D0 = d0 - dm, DK = dr - dk;
         T fl = T(0), fr = T(0);
-        if constexpr (!OPEN) {
-            fl = dm - (xl - xl2);
-            fr = (xr2 - xr) - dr;
-        }
-        const T Dl = edge_left<OPEN>(fl, DK), Dr = edge_right<OPEN>(fr, D0);
+        if constexpr (!OL) fl = dm - (xl - xl2);
+        if constexpr (!OR) fr = (xr2 - xr) - dr;
+        const T Dl = edge_left<OL>(fl, DK), Dr = edge_right<OR>(fr, D0);
         T dprev = d0;
 #pragma unroll
         for (int j = 1; j + 1 < K; j += 2) {

@@ -50,34 +50,36 @@ __device__ __forceinline__ void load_window(const T *__restrict__ p, int64_t g0,
     }
 }
 
-// Wall values of consecutive levels, each loaded a level ahead of its use
-// (a scalar load's latency would otherwise stand in every level): now() and
-// next() are g(t_m) and g(t_{m+1}); step() moves to the next level.  A lone
-// point reads entering(), g(t_{m+1}) made NaN by an infinite or NaN g(t_m):
-// the levels' formulas read one wall value in two, and an unusable value
+// The wall value each level reads, 64 levels at a time: a level of the
+// window's parity 0 reads g(t_m), one of parity 1 (a lone point) g(t_{m+1}).
+// Lane l holds level base + l's, so a level takes its value with a lane read
+// and waits for no load.  At parity 1 the value is NaN when g(t_m) is
+// infinite or NaN: the levels read one wall value in two, and an unusable one
 // between them is to show in the result as well.
-struct WallWalk {
-    const double *p;      // g(t_m) of the launch's levels, or null: constant
-    double g0, g1, g2;
-    int at, last;
-    __device__ __forceinline__ WallWalk(const double *p_, double c, int nlev) : p(p_), at(2), last(nlev)
+template <typename T> struct WallFeed {
+    T v;
+    // levels base .. base+63 of a launch of nlev levels whose first has
+    // window parity p0; g: g(t_m) of the launch's levels, or null: constant c
+    __device__ __forceinline__ void fill(const double *g, double c, int base, int nlev, int p0)
     {
-        g0 = g1 = g2 = c;
-        if (p) {
-            g0 = p[0];
-            g1 = p[1];
-            g2 = p[nlev > 1 ? 2 : 1];
+        double x = c;
+        if (g) {
+            const int lev = min(base + (int)(threadIdx.x & (kWave - 1)), nlev - 1);
+            const double g0 = g[lev];
+            x = ((lev + p0) & 1) == 0 ? g0 : __builtin_fma(0.0, g0, g[lev + 1]);
         }
+        v = (T)x;
     }
-    __device__ __forceinline__ double now() const { return g0; }
-    __device__ __forceinline__ double next() const { return g1; }
-    __device__ __forceinline__ double entering() const { return __builtin_fma(0.0, g0, g1); }
-    __device__ __forceinline__ void step()
+    __device__ __forceinline__ T at(int lev) const
     {
-        g0 = g1;
-        g1 = g2;
-        ++at;
-        if (p) g2 = p[at < last ? at : last];
+        if constexpr (sizeof(T) == 8) {
+            const long long b = __double_as_longlong(v);
+            const int lo = __builtin_amdgcn_readlane((int)(b & 0xffffffffll), lev & (kWave - 1));
+            const int hi = __builtin_amdgcn_readlane((int)(b >> 32), lev & (kWave - 1));
+            return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+        } else {
+            return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lev & (kWave - 1)));
+        }
     }
 };
 
@@ -122,8 +124,10 @@ __device__ __forceinline__ void sweep_plain(const TileArgs &a, int tid, int64_t 
     const T kl = lane_l ? cf.cs : cf.k, kr = lane_r ? cf.cs : cf.k;
     const T cl = lane_l ? cf.cs : cf.c1, cr = lane_r ? cf.cs : cf.c1;
     const T pl = lane_l ? T(0) : cf.cs, pr = lane_r ? T(0) : cf.cs;
-    WallWalk wl(WALL ? a.gl_t : nullptr, a.gl0, a.nlev), wr(WALL ? a.gr_t : nullptr, a.gr0, a.nlev);
-    double an = SRC ? a.src_a[0] : 0.0;             // likewise a level ahead
+    const bool flux = WALL && a.flux != nullptr;   // uniform
+    WallFeed<T> wl, wr;
+    const int par0 = (int)((a.level0 + ws) & 1);   // the first level's parity in the window
+    double an = SRC ? a.src_a[0] : 0.0;            // each loaded a level ahead of its use
 
     // FP32: the source weights of both parities, formed once per launch
     constexpr int KB = SRC && !TWO_STAGE ? K : 1;
@@ -171,27 +175,36 @@ __device__ __forceinline__ void sweep_plain(const TileArgs &a, int tid, int64_t 
     // a window starting at an odd point pairs its points the other way round
     for_levels(a.level0 + (ws & 1), a.nlev, [&](auto par, int lev) {
         constexpr int P = decltype(par)::value;
-        const T glo = (T)wl.now(), gln = (T)wl.entering();
-        const T gro = (T)wr.now(), grn = (T)wr.entering();
+        T gl = T(0), gr = T(0);
+        if constexpr (WALL) {
+            if ((lev & (kWave - 1)) == 0) {
+                wl.fill(a.gl_t, a.gl0, lev, a.nlev, par0);
+                // a wall node inside the window is read by the levels at
+                // which the point beside it is not alone
+                wr.fill(a.gr_t, a.gr0, lev, a.nlev, KIND == kInside ? par0 + (int)n : par0);
+            }
+            gl = wl.at(lev);
+            gr = wr.at(lev);
+        }
         const bool single = KIND == kInside && (((int)n - 1 + P) & 1) == 0;
         T xl[E] = {}, xr[E] = {};
         T lone = T(0);
         if constexpr (TWO_STAGE) {
-            if constexpr (KIND == kInside) put_at<T, K>(u, kR, tid == lR, gro);
-            if constexpr (P == 0) exchange(lev & 1, glo, gro, xl, xr);
-            explicit_stage<T, K, P, OPEN>(u, xl[0], xr[0], cf);
+            if (KIND == kInside && !single) put_at<T, K>(u, kR, tid == lR, gr);
+            if constexpr (P == 0) exchange(lev & 1, gl, gr, xl, xr);
+            explicit_stage<T, K, P, OPEN, OPEN>(u, xl[0], xr[0], cf);
             if constexpr (SRC) source_stage<T, K>(u, b, (T)(a.tau * an));
-            if constexpr (P == 1) exchange(lev & 1, gln, grn, xl, xr);
+            if constexpr (P == 1) exchange(lev & 1, gl, gr, xl, xr);
             if (KIND == kInside && single)
-                lone = lone_point(get_at<T, K>(u, kS, T(0)), grn, cf.cs);
-            solve_stage<T, K, P, OPEN>(u, xl[0], xr[0], cf, kl, kr);
+                lone = lone_point(get_at<T, K>(u, kS, T(0)), gr, cf.cs);
+            solve_stage<T, K, P, OPEN, OPEN>(u, xl[0], xr[0], cf, kl, kr);
         } else {
-            if constexpr (KIND == kInside) put_at<T, K>(u, kR, tid == lR, single ? grn : gro);
-            exchange(lev & 1, P == 0 ? glo : gln, P == 0 ? gro : grn, xl, xr);
+            if constexpr (KIND == kInside) put_at<T, K>(u, kR, tid == lR, gr);
+            exchange(lev & 1, gl, gr, xl, xr);
             auto level = [&](const T (&B)[K]) {
                 if (KIND == kInside && single)
-                    lone = lone_increment<T, K, SRC>(u, B, (T)an, kS, xl[0], grn, cf.cs);
-                increment_level<T, K, SRC, P, OPEN>(u, B, (T)an, xl[0], xl[E - 1], xr[0], xr[E - 1],
+                    lone = lone_increment<T, K, SRC>(u, B, (T)an, kS, xl[0], gr, cf.cs);
+                increment_level<T, K, SRC, P, OPEN, OPEN>(u, B, (T)an, xl[0], xl[E - 1], xr[0], xr[E - 1],
                                                     cf, cl, pl, cr, pr);
             };
             if constexpr (!SRC) level(b);
@@ -200,15 +213,15 @@ __device__ __forceinline__ void sweep_plain(const TileArgs &a, int tid, int64_t 
         }
         if (KIND == kInside && single) put_at<T, K>(u, kS, tid == lS, lone);
         if constexpr (SRC) an = a.src_a[lev + 1 < a.nlev ? lev + 1 : lev];
-        if constexpr (WALL) {
+        if (WALL && flux) {
             // wall first differences at the new level, accumulated in FP64
-            if (own_L && tid == 0) acc = acc + a.tau * ((double)u[0] - wl.next()) / a.h;
+            if (own_L && tid == 0)
+                acc = acc + a.tau * ((double)u[0] - (a.gl_t ? a.gl_t[lev + 1] : a.gl0)) / a.h;
             if (own_R) {
                 const T v = KIND == kInside ? get_at<T, K>(u, kS, T(0)) : u[K - 1];
-                if (tid == lS) accR = accR + a.tau * ((double)v - wr.next()) / a.h;
+                if (tid == lS)
+                    accR = accR + a.tau * ((double)v - (a.gr_t ? a.gr_t[lev + 1] : a.gr0)) / a.h;
             }
-            wl.step();
-            wr.step();
         }
     });
 
