@@ -219,9 +219,10 @@ typedef struct {
     int32_t precision;  /* GE_FP64 or GE_FP32                               */
     double g_west, g_east, g_south, g_north;   /* wall values (x = 0, x = 1, */
                                                /* y = 0, y = 1)              */
-    int32_t depth;      /* levels fused per launch: 1, 2 or 4 (a halo of 2   */
-                        /* points per level and side is recomputed); 0 =     */
-                        /* library choice.  Changes no bits of the result.   */
+    int32_t depth;      /* levels fused per launch: 1, 2 or 4 (a halo of one  */
+                        /* point per level and one more on each side is      */
+                        /* recomputed); 0 = library choice (up to 24, by the  */
+                        /* grid's size).  Changes no bits of the result.     */
 } ge_2d_desc;
 
 /* Bytes of device workspace a ge_2d_step_n call needs (a second grid:

@@ -14,7 +14,7 @@ struct Grid2dArgs {
     int64_t nx, ny, step0, nsteps;
     double rx, ry;           // tau/hx^2, tau/hy^2
     double gw, ge, gs, gn;   // constant walls: west, east, south, north
-    int depth;               // levels per launch: 1, 2 or 4
+    int depth;               // levels per launch: 1, 2 or 4, 0 = by the grid's size
 };
 
 hipError_t launch_2d(int prec, const Grid2dArgs &a, hipStream_t stream);

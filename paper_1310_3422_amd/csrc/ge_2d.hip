@@ -5,28 +5,43 @@
 // point alone beside a wall by Eq. (1)/(2)) along every row with
 // r_x = tau/h_x^2, then along every column with r_y = tau/h_y^2 (first-order
 // splitting; each line is paired by the level's global index exactly as a
-// single rod is).
+// single rod is).  Walls are constant in time.
 //
-// A one-dimensional level is explicit: a point's new value depends on old
-// values at most two places away along its line.  So a launch advances D
-// levels (D = 1, 2 or 4) of a tile held in registers: lane l holds two
-// neighbouring columns (an even one and the next) for N rows.  A row's
-// x-level takes its neighbours from the lanes beside it by DPP shifts -- at
-// levels of even index a lane's two points are a pair, at odd ones each
-// pairs with a point of the neighbouring lane -- and a column's y-level from
-// the lane's own rows, where the parity of every row is known at compile
-// time.  The valid lanes and rows shrink by one lane (two columns) and two
-// rows per side and level (a recomputed halo).  Per launch the grid is read
-// and written once: 16/D bytes per point and level in FP64.  Every point is
-// advanced by the same operations whatever D is and wherever its tile lies,
-// so the depth changes no bits.
+// Each direction is taken as ge_level.h takes a rod: in FP64 in two stages, an
+// explicit one over the other parity's pairs, then the 2x2 solve of its own, 3
+// instructions a point; in FP32 as an increment from second differences, 4
+// instructions and one rounding of u.  (FP32 in two stages was faster still,
+// 4096 x 4096 points 0.49 ms for 96 levels, but its error against 64 bits was
+// 1.4 times this form's at the median over 40 grids: 1.8e-7 against 1.3e-7.)
 //
-// Walls are constant in time (west, east, south, north); the values beside
-// a wall read the wall, which a halo lane or row holds.  Tiles whose halo
-// reaches a wall take a second code path (per-lane column tests, per-row
-// tests); the others test nothing.
+// A workgroup of 8 waves holds a window of 128 columns by 8 R rows in
+// registers: lane l of a wave columns 2l and 2l + 1 of its R rows.  A level's
+// x part takes its neighbours by DPP moves; its y part works on the lane's own
+// rows, and the rows at a wave's ends meet their neighbours in LDS, one row
+// each way and one barrier a level.  The halo of D + 1 points a side (the
+// invalid region entering from an open edge grows by one point per level after
+// the first, in each direction by itself) is shared by 8 R rows, so a launch
+// can fuse many levels, and two or more workgroups are resident per compute
+// unit, one loading or storing while another computes.
+//
+// A window that would reach past a wall is moved to end there, so a wall is
+// the fill of a first or last lane or the neighbour row of a first or last
+// wave, with cs for k; a window that starts at an odd column or row pairs that
+// direction the other way round.  Only a grid smaller than a window has wall
+// nodes inside one: those lanes and rows are set to the wall's value at each
+// stage.  Every point gets the same operations whatever the window, its rows
+// and the levels per launch, so none of them changes a bit.
+//
+// Measured, 96 levels: 4096 x 4096 points FP64 1.01 ms (1.53 when a wave held
+// its tile alone, two columns by 36 rows a lane and four levels per launch),
+// FP32 0.66 (0.83); 196 x 578 FP64 80 us (435).  VALU issue (6 instructions a
+// point and level, 11 lane moves to 16 of them) and the halo's recompute bind
+// large grids, one window's level latency small ones.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+
+#include <algorithm>
+#include <cmath>
 
 #include "ge_2d.h"
 #include "ge_kernels.h"
@@ -35,293 +50,484 @@
 namespace ge {
 namespace {
 
-constexpr int kThreads = 256;       // four waves, four column strips
-
-template <typename T> struct Line {
-    T c1, c2, cs;   // (r+r^2)/(1+2r), r^2/(1+2r), r/(1+r)
-};
-
-// A pair member's new value u + c1 D_e + c2 D_q, a lone point's (beside a
-// wall) u + cs D_e; D = second difference, D_e = d_e - d_{e-1}.
-template <typename T>
-__device__ __forceinline__ T pair_upd(T u, T De, T Dq, const Line<T> &c)
-{
-    if constexpr (sizeof(T) == 8) return fma(c.c2, Dq, fma(c.c1, De, u));
-    else return u + fmaf(c.c2, Dq, c.c1 * De);
-}
-template <typename T>
-__device__ __forceinline__ T lone_upd(T u, T De, const Line<T> &c)
-{
-    if constexpr (sizeof(T) == 8) return fma(c.cs, De, u);
-    else return u + c.cs * De;
-}
-
+using dev::Par;
+using dev::for_levels;
 using dev::kWave;
 
-template <typename T>
-__device__ __forceinline__ T shr1(T v) { return dev::from_left_open(v); }    // lane l-1
-template <typename T>
-__device__ __forceinline__ T shl1(T v) { return dev::from_right_open(v); }   // lane l+1
+constexpr int kCols = 2 * kWave;      // columns of a window
+constexpr int kNW = 8;                // waves of a window
 
-template <int D> struct RegTile {
-    static constexpr int H = 2 * D;                            // halo rows per side
-    static constexpr int R = D == 4 ? 20 : 24;                 // output rows per wave
-    static constexpr int N = R + 2 * H;                        // rows held
-    static constexpr int LANES = kWave - 2 * D;                // output lanes (D halo lanes a side)
-    static constexpr int COLS = 2 * LANES;                     // output columns per wave
+template <typename T> struct Dir {    // one direction's constants (Coef, ge_level.h)
+    T r, k, c1, cs;
 };
 
-// What a lane's two columns are, for tiles that reach the west or east wall
-// (x0 + 2 lane and the next; only points inside the grid change, and a point
-// whose partner lies outside the grid is alone beside the wall).
-struct ColFlags {
-    bool a_in, b_in;       // the columns lie inside the grid
-    bool a_lone0;          // even levels: a's partner b is the east ghost
-    bool a_lone1, b_lone1; // odd levels: a is column 0; b's partner is the east ghost
+template <typename T> struct Block2dArgs {
+    const T *in;
+    T *out;
+    int nx, ny, tx, ntiles;           // tiles per row of tiles, tiles
+    int cx, cy, halo, nlev;           // core columns and rows, halo, levels
+    int64_t level0;
+    Dir<T> x, y;
+    T gw, ge, gs, gn;
 };
 
-// The x-level of one row: a, b the lane's two points (old values in, new
-// out).  P: the level's parity; XW: the tile reaches a west or east wall.
-template <typename T, int P, bool XW>
-__device__ __forceinline__ void xlevel(T &a, T &b, const ColFlags &f, const Line<T> &c)
+// Two columns: in LDS, and in memory (any element's alignment).
+template <typename T> struct Pair2;
+template <> struct Pair2<float> {
+    typedef float type __attribute__((ext_vector_type(2)));
+    typedef float mem __attribute__((ext_vector_type(2), aligned(4)));
+};
+template <> struct Pair2<double> {
+    typedef double type __attribute__((ext_vector_type(2)));
+    typedef double mem __attribute__((ext_vector_type(2), aligned(8)));
+};
+
+// What a window holds of the walls: kOpen no x wall, kEnds an x wall at its
+// first or last column; a y wall at its first or last row costs nothing and
+// is not told apart.  kInside: the grid ends inside the window.
+enum Walls2d : int { kOpen, kEnds, kInside };
+
+// FP64 meets its neighbours with one row a side, FP32 with two.
+template <typename T> constexpr bool kTwoStage = sizeof(T) == 8;
+template <typename T> constexpr int kEdge = kTwoStage<T> ? 1 : 2;
+template <typename T> constexpr int kRowsAtOnce = 4;
+
+// The factors of a point: of the solve's difference (FP64: f), or of its own
+// second difference and of its partner's inside it (FP32: f, g).
+template <typename T> struct Factor {
+    T f, g;
+};
+template <typename T> __device__ __forceinline__ Factor<T> paired(const Dir<T> &c)
 {
-    const T l1 = shr1(b);            // column 2l - 1
-    const T r1 = shl1(a);            // column 2l + 2
-    const T dm = a - l1, d0 = b - a, dp = r1 - b;
-    const T Da = d0 - dm, Db = dp - d0;
-    T na, nb;
+    if constexpr (kTwoStage<T>) return Factor<T>{c.k, T(0)};
+    else return Factor<T>{c.c1, c.cs};
+}
+template <typename T> __device__ __forceinline__ Factor<T> alone(const Dir<T> &c)
+{
+    return Factor<T>{c.cs, T(0)};
+}
+template <typename T> __device__ __forceinline__ Factor<T> pick(bool is_alone, const Dir<T> &c)
+{
+    const Factor<T> p = paired(c), l = alone(c);
+    return Factor<T>{is_alone ? l.f : p.f, is_alone ? l.g : p.g};
+}
+// FP32: a point's new value
+template <typename T> __device__ __forceinline__ T step(T u, T D, T Dq, Factor<T> k)
+{
+    return dev::fmaT(k.f, dev::fmaT(k.g, Dq, D), u);
+}
+
+// One lane's view of the x walls.
+template <typename T> struct XWalls {
+    T gw, ge;              // their values
+    Factor<T> l, r;        // P = 1: the factors of the lane's first / last column
+    Factor<T> in;          // P = 0: those of its first column
+    bool a_wall, b_wall;   // kInside: the column is the east wall's node or past it
+};
+
+// The x part of one row.
+template <typename T, int P, int KIND>
+__device__ __forceinline__ void x_part(T &a, T &b, const XWalls<T> &x, const Dir<T> &c)
+{
+    using dev::fmaT;
+    constexpr bool OPEN = KIND == kOpen;
+    auto set_wall = [&](T &p, T &q) {
+        if constexpr (KIND == kInside) {
+            p = x.a_wall ? x.ge : p;
+            q = x.b_wall ? x.ge : q;
+        }
+    };
+    const Factor<T> in = KIND == kInside ? x.in : paired(c), pr = paired(c);
+    set_wall(a, b);
+    if constexpr (kTwoStage<T>) {
+        T va, vb;
+        if constexpr (P == 0) {
+            va = fmaT(-c.r, a - dev::edge_left<OPEN>(x.gw, b), a);
+            vb = fmaT(c.r, dev::edge_right<OPEN>(x.ge, a) - b, b);
+            set_wall(va, vb);
+            const T w = vb - va;
+            a = fmaT(in.f, w, va);
+            b = fmaT(-pr.f, w, vb);
+        } else {
+            const T d = b - a;
+            va = fmaT(c.r, d, a);
+            vb = fmaT(-c.r, d, b);
+            set_wall(va, vb);
+            a = fmaT(-x.l.f, va - dev::edge_left<OPEN>(x.gw, vb), va);
+            b = fmaT(x.r.f, dev::edge_right<OPEN>(x.ge, va) - vb, vb);
+        }
+    } else {
+        const T dm = a - dev::edge_left<OPEN>(x.gw, b), d0 = b - a;
+        const T dp = dev::edge_right<OPEN>(x.ge, a) - b;
+        const T Da = d0 - dm, Db = dp - d0;
+        if constexpr (P == 0) {
+            a = step(a, Da, Db, in);
+            b = step(b, Db, Da, pr);
+        } else {
+            // beside a wall the partner's factor is 0
+            a = step(a, Da, dev::edge_left<OPEN>(T(0), Db), x.l);
+            b = step(b, Db, dev::edge_right<OPEN>(T(0), Da), x.r);
+        }
+    }
+}
+
+// The y part of one column's R rows.  lo, hi: the rows before and after them,
+// nearest first (FP64: old values at P = 0, the explicit stage's at P = 1;
+// FP32: old values).  klo, khi: the factors of the first and last row at
+// P = 1; kf(q): those of a pair's lower row q inside the wave.
+template <typename T, int R, int P>
+__device__ __forceinline__ void y_explicit(T (&u)[R], T lo, T hi, const Dir<T> &c)
+{
+    using dev::fmaT;
     if constexpr (P == 0) {
-        // pairs (2l, 2l+1)
-        na = pair_upd(a, Da, Db, c);
-        nb = pair_upd(b, Db, Da, c);
-        if constexpr (XW) {
-            if (f.a_lone0) na = lone_upd(a, Da, c);
+        u[0] = fmaT(-c.r, u[0] - lo, u[0]);
+#pragma unroll
+        for (int q = 1; q + 1 < R; q += 2) {
+            const T d = u[q + 1] - u[q];
+            u[q] = fmaT(c.r, d, u[q]);
+            u[q + 1] = fmaT(-c.r, d, u[q + 1]);
+        }
+        u[R - 1] = fmaT(c.r, hi - u[R - 1], u[R - 1]);
+    } else {
+#pragma unroll
+        for (int q = 0; q < R; q += 2) {
+            const T d = u[q + 1] - u[q];
+            u[q] = fmaT(c.r, d, u[q]);
+            u[q + 1] = fmaT(-c.r, d, u[q + 1]);
+        }
+    }
+}
+template <typename T, int R, int P, typename K>
+__device__ __forceinline__ void y_solve(T (&v)[R], T lo, T hi, const Dir<T> &c, Factor<T> klo,
+                                        Factor<T> khi, K &&kf)
+{
+    using dev::fmaT;
+    if constexpr (P == 0) {
+#pragma unroll
+        for (int q = 0; q < R; q += 2) {
+            const T w = v[q + 1] - v[q];
+            v[q] = fmaT(kf(q).f, w, v[q]);
+            v[q + 1] = fmaT(-c.k, w, v[q + 1]);
         }
     } else {
-        // pairs (2l-1, 2l) and (2l+1, 2l+2): the partners' second
-        // differences come from the lanes beside
-        const T Dl = shr1(Db);       // D of column 2l - 1
-        const T Dr = shl1(Da);       // D of column 2l + 2
-        na = pair_upd(a, Da, Dl, c);
-        nb = pair_upd(b, Db, Dr, c);
-        if constexpr (XW) {
-            if (f.a_lone1) na = lone_upd(a, Da, c);
-            if (f.b_lone1) nb = lone_upd(b, Db, c);
-        }
-    }
-    if constexpr (XW) {
-        if (!f.a_in) na = a;
-        if (!f.b_in) nb = b;
-    }
-    a = na;
-    b = nb;
-}
-
-// The y-level of one column, rows [LO, HI) of u (old values of rows LO-2 ..
-// HI+1 used), in place.  Row q is grid row jb + q, and jb is even, so the
-// pairing of row q follows q: pairs (q, q+1) with q + P even.  The second
-// differences roll along the column (each from old values, computed before
-// the row below it is overwritten).  XW: the column may lie outside the grid
-// (cin false: it keeps its values).  YW: the tile reaches the south or north
-// wall: rows outside the grid keep their values, and a row whose partner
-// lies outside is alone beside the wall.
-template <typename T, int N, int LO, int HI, int P, bool XW, bool YW>
-__device__ __forceinline__ void ylevel(T (&u)[N], bool cin, int jb, int ny, const Line<T> &c)
-{
-    static_assert(LO >= 2 && HI + 2 <= N, "rows read");
-    T Dp = (u[LO] - u[LO - 1]) - (u[LO - 1] - u[LO - 2]);   // row LO - 1
-    T Dc = (u[LO + 1] - u[LO]) - (u[LO] - u[LO - 1]);       // row LO
+        v[0] = fmaT(-klo.f, v[0] - lo, v[0]);
 #pragma unroll
-    for (int q = LO; q < HI; ++q) {
-        const T Dn = (u[q + 2] - u[q + 1]) - (u[q + 1] - u[q]);   // row q + 1
-        const bool left = ((q + P) & 1) == 0;                       // compile-time
-        T v = pair_upd(u[q], Dc, left ? Dn : Dp, c);
-        if constexpr (YW) {
-            const int j = jb + q, jq = left ? j + 1 : j - 1;
-            if (jq < 0 || jq >= ny) v = lone_upd(u[q], Dc, c);
-            if (j < 0 || j >= ny) v = u[q];
+        for (int q = 1; q + 1 < R; q += 2) {
+            const T w = v[q + 1] - v[q];
+            v[q] = fmaT(kf(q).f, w, v[q]);
+            v[q + 1] = fmaT(-c.k, w, v[q + 1]);
         }
-        if constexpr (XW) {
-            if (!cin) v = u[q];
-        }
-        u[q] = v;
-        Dp = Dc;
-        Dc = Dn;
+        v[R - 1] = fmaT(khi.f, hi - v[R - 1], v[R - 1]);
     }
 }
-
-template <typename T, int D, int L, int P, bool XW, bool YW>
-__device__ __forceinline__ void tile_levels(T (&ua)[RegTile<D>::N], T (&ub)[RegTile<D>::N],
-                                            const ColFlags &f, int jb, int ny, const Line<T> &cx,
-                                            const Line<T> &cy)
+template <typename T, int R, int P, typename K>
+__device__ __forceinline__ void y_increment(T (&u)[R], const T (&lo)[2], const T (&hi)[2],
+                                            const Dir<T> &c, Factor<T> klo, Factor<T> khi, K &&kf)
 {
-    constexpr int N = RegTile<D>::N;
-    // x-level on rows [2L, N - 2L)
+    const Factor<T> pr = paired(c);
+    if constexpr (P == 0) {
+        T dprev = u[0] - lo[0];
 #pragma unroll
-    for (int q = 2 * L; q < N - 2 * L; ++q) {
-        if constexpr (YW) {
-            const int j = jb + q;
-            if (j < 0 || j >= ny) continue;   // wave-uniform
+        for (int q = 0; q < R; q += 2) {
+            const T d0 = u[q + 1] - u[q];
+            const T d1 = (q + 2 < R ? u[q + 2] : hi[0]) - u[q + 1];
+            const T Da = d0 - dprev, Db = d1 - d0;
+            u[q] = step(u[q], Da, Db, kf(q));
+            u[q + 1] = step(u[q + 1], Db, Da, pr);
+            dprev = d1;
         }
-        xlevel<T, P, XW>(ua[q], ub[q], f, cx);
-    }
-    if constexpr (L + 1 < D) {
-        ylevel<T, N, 2 * L + 2, N - 2 * L - 2, P, XW, YW>(ua, f.a_in, jb, ny, cy);
-        ylevel<T, N, 2 * L + 2, N - 2 * L - 2, P, XW, YW>(ub, f.b_in, jb, ny, cy);
-        tile_levels<T, D, L + 1, 1 - P, XW, YW>(ua, ub, f, jb, ny, cx, cy);
-    }
-}
-
-// One wave's tile: levels m .. m+D-1 (P = m mod 2) of lanes' column pairs
-// x0 + 2 lane, rows jb .. jb+N-1; writes the core (lanes D .. 63-D, rows
-// H .. H+R-1) of the last level to `out`.
-template <typename T, int D, int P, bool XW, bool YW>
-__device__ __forceinline__ void tile2d(const T *__restrict__ in, T *__restrict__ out, int nx,
-                                       int ny, int x0, int jb, const Line<T> &cx,
-                                       const Line<T> &cy, T gw, T ge_, T gs, T gn)
-{
-    using G = RegTile<D>;
-    constexpr int N = G::N, H = G::H, R = G::R;
-    const int lane = threadIdx.x % kWave;
-    const int ia = x0 + 2 * lane, ib = ia + 1;
-    ColFlags f;
-    f.a_in = ia >= 0 && ia < nx;
-    f.b_in = ib >= 0 && ib < nx;
-    f.a_lone0 = ib >= nx;
-    f.a_lone1 = ia == 0;
-    f.b_lone1 = ib + 1 >= nx;
-    T ua[N], ub[N];
-    auto ghost = [&](int i) { return i == -1 ? gw : i == nx ? ge_ : T(0); };
-#pragma unroll
-    for (int q = 0; q < N; ++q) {
-        const int j = jb + q;                 // wave-uniform
-        T xa = T(0), xb = T(0);
-        if (j == -1) {
-            xa = xb = gs;
-        } else if (j == ny) {
-            xa = xb = gn;
-        } else if (!YW || (j >= 0 && j < ny)) {
-            const T *row = in + (int64_t)j * nx;
-            if (!XW || f.a_in) xa = row[ia];
-            else xa = ghost(ia);
-            if (!XW || f.b_in) xb = row[ib];
-            else xb = ghost(ib);
-        }
-        ua[q] = xa;
-        ub[q] = xb;
-    }
-    tile_levels<T, D, 0, P, XW, YW>(ua, ub, f, jb, ny, cx, cy);
-    // the last y-level, the core straight to HBM
-    constexpr int PL = (P + D - 1) & 1;
-    ylevel<T, N, H, H + R, PL, XW, YW>(ua, f.a_in, jb, ny, cy);
-    ylevel<T, N, H, H + R, PL, XW, YW>(ub, f.b_in, jb, ny, cy);
-    if (lane < D || lane >= kWave - D)
-        return;
-#pragma unroll
-    for (int q = H; q < H + R; ++q) {
-        const int j = jb + q;
-        if (j >= ny) break;                   // wave-uniform
-        T *row = out + (int64_t)j * nx;
-        if (!XW || f.a_in) row[ia] = ua[q];
-        if (!XW || f.b_in) row[ib] = ub[q];
-    }
-}
-
-template <typename T, int D, int P>
-__global__ __launch_bounds__(kThreads) void level2d_reg_kernel(const T *__restrict__ in,
-                                                               T *__restrict__ out, int nx, int ny,
-                                                               int strips, int ntiles,
-                                                               Line<T> cx, Line<T> cy, T gw,
-                                                               T ge_, T gs, T gn)
-{
-    using G = RegTile<D>;
-    const int per = gridDim.x / 8;
-    const int b = (blockIdx.x % 8) * per + blockIdx.x / 8;   // XCD-aware
-    // this wave's tile (wave-uniform: row addresses stay in scalar registers)
-    const int t = b * (kThreads / kWave) + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    if (t >= ntiles)
-        return;
-    const int x0 = (t % strips) * G::COLS - 2 * D;
-    const int jb = (t / strips) * G::R - G::H;
-    // the tile's halo reaches a wall (a ghost column or row is read)
-    const bool xw = x0 < 0 || x0 + 2 * kWave > nx;
-    const bool yw = jb < 0 || jb + G::N > ny;
-    if (xw) {
-        if (yw) tile2d<T, D, P, true, true>(in, out, nx, ny, x0, jb, cx, cy, gw, ge_, gs, gn);
-        else tile2d<T, D, P, true, false>(in, out, nx, ny, x0, jb, cx, cy, gw, ge_, gs, gn);
     } else {
-        if (yw) tile2d<T, D, P, false, true>(in, out, nx, ny, x0, jb, cx, cy, gw, ge_, gs, gn);
-        else tile2d<T, D, P, false, false>(in, out, nx, ny, x0, jb, cx, cy, gw, ge_, gs, gn);
+        const T dm = u[0] - lo[0], d0 = u[1] - u[0];
+        const T dk = u[R - 1] - u[R - 2], dr = hi[0] - u[R - 1];
+        const T Dm = dm - (lo[0] - lo[1]), Dp = (hi[1] - hi[0]) - dr;
+        const T first = step(u[0], d0 - dm, Dm, klo), last = step(u[R - 1], dr - dk, Dp, khi);
+        T dprev = d0;
+#pragma unroll
+        for (int q = 1; q + 1 < R; q += 2) {
+            const T da = u[q + 1] - u[q], db = u[q + 2] - u[q + 1];
+            const T Da = da - dprev, Db = db - da;
+            u[q] = step(u[q], Da, Db, kf(q));
+            u[q + 1] = step(u[q + 1], Db, Da, pr);
+            dprev = db;
+        }
+        u[0] = first;
+        u[R - 1] = last;
     }
 }
 
-template <typename T> Line<T> line_coef(double r)
+// The levels of one wave (ODD: the window's row and column parities differ).
+template <typename T, int R, int NW, int KIND, bool ODD, typename X>
+__device__ __forceinline__ void wave_levels(const Block2dArgs<T> &a, int x0, int y0, int w,
+                                            T (&ua)[R], T (&ub)[R], X *xch)
 {
-    return Line<T>{(T)((r + r * r) / (1.0 + 2.0 * r)), (T)(r * r / (1.0 + 2.0 * r)),
-                   (T)(r / (1.0 + r))};
+    constexpr int E = kEdge<T>;
+    const int lane = threadIdx.x & (kWave - 1);
+    const int ia = x0 + 2 * lane, row0 = y0 + w * R;
+    XWalls<T> xw;
+    xw.gw = a.gw;
+    xw.ge = a.ge;
+    xw.l = pick(KIND != kOpen && ia == 0, a.x);
+    xw.r = pick(KIND != kOpen && ia + 2 == a.nx, a.x);
+    xw.in = pick(KIND == kInside && ia + 1 == a.nx, a.x);
+    xw.a_wall = ia >= a.nx;
+    xw.b_wall = ia + 1 >= a.nx;
+    const bool south = row0 == 0, north = y0 + NW * R == a.ny && w == NW - 1;
+    const Factor<T> klo = pick(south, a.y), khi = pick(row0 + R == a.ny, a.y);
+    auto kf = [&](int q) { return pick(KIND == kInside && row0 + q + 1 == a.ny, a.y); };
+    // the north wall's row, and those past it, when they are the wave's
+    auto set_wall = [&]() {
+        if constexpr (KIND == kInside) {
+#pragma unroll
+            for (int q = 0; q < R; ++q)
+                if (row0 + q >= a.ny) ua[q] = ub[q] = a.gn;
+        }
+    };
+    // xch: [2 slots][waves][first, last rows][E][lanes] column pairs
+    auto slot = [&](int s, int wave, int end, int i) {
+        return xch + (((s * NW + wave) * 2 + end) * E + i) * kWave;
+    };
+    for_levels(a.level0 + (x0 & 1), a.nlev, [&](auto par, int lev) {
+        constexpr int PX = decltype(par)::value, PY = ODD ? 1 - PX : PX;
+        const int s = lev & 1;
+        T loa[E], lob[E], hia[E], hib[E];
+        auto put = [&]() {
+#pragma unroll
+            for (int i = 0; i < E; ++i) {
+                slot(s, w, 0, i)[lane] = X{ua[i], ub[i]};
+                slot(s, w, 1, i)[lane] = X{ua[R - 1 - i], ub[R - 1 - i]};
+            }
+        };
+        auto take = [&]() {
+            __syncthreads();
+#pragma unroll
+            for (int i = 0; i < E; ++i) {
+                X lo = slot(s, w > 0 ? w - 1 : 0, 1, i)[lane];
+                X hi = slot(s, w < NW - 1 ? w + 1 : NW - 1, 0, i)[lane];
+                if (south) lo = X{a.gs, a.gs};
+                if (north) hi = X{a.gn, a.gn};
+                loa[i] = lo.x;
+                lob[i] = lo.y;
+                hia[i] = hi.x;
+                hib[i] = hi.y;
+            }
+        };
+        // the rows at the wave's ends first, so that they are on their way
+        // while the others take their x part
+#pragma unroll
+        for (int i = 0; i < E; ++i) {
+            x_part<T, PX, KIND>(ua[i], ub[i], xw, a.x);
+            x_part<T, PX, KIND>(ua[R - 1 - i], ub[R - 1 - i], xw, a.x);
+        }
+        constexpr bool EARLY = KIND != kInside && (PY == 0 || !kTwoStage<T>);
+        if constexpr (EARLY) put();
+#pragma unroll
+        for (int q = E; q < R - E; ++q) {
+            x_part<T, PX, KIND>(ua[q], ub[q], xw, a.x);
+            // a few rows in flight at a time: left alone, the scheduler takes
+            // all rows' moves first and runs out of registers
+            if (q % kRowsAtOnce<T> == kRowsAtOnce<T> - 1) __builtin_amdgcn_sched_barrier(0);
+        }
+        set_wall();
+        if constexpr (!kTwoStage<T>) {
+            if constexpr (!EARLY) put();
+            take();
+            y_increment<T, R, PY>(ua, loa, hia, a.y, klo, khi, kf);
+            y_increment<T, R, PY>(ub, lob, hib, a.y, klo, khi, kf);
+        } else if constexpr (PY == 0) {
+            if constexpr (!EARLY) put();
+            take();
+            y_explicit<T, R, 0>(ua, loa[0], hia[0], a.y);
+            y_explicit<T, R, 0>(ub, lob[0], hib[0], a.y);
+            __builtin_amdgcn_sched_barrier(0);
+            set_wall();
+            y_solve<T, R, 0>(ua, T(0), T(0), a.y, klo, khi, kf);
+            y_solve<T, R, 0>(ub, T(0), T(0), a.y, klo, khi, kf);
+            __builtin_amdgcn_sched_barrier(0);
+        } else {
+            y_explicit<T, R, 1>(ua, T(0), T(0), a.y);
+            y_explicit<T, R, 1>(ub, T(0), T(0), a.y);
+            set_wall();
+            put();
+            take();
+            y_solve<T, R, 1>(ua, loa[0], hia[0], a.y, klo, khi, kf);
+            y_solve<T, R, 1>(ub, lob[0], hib[0], a.y, klo, khi, kf);
+        }
+    });
 }
 
-template <typename T, int D>
-hipError_t launch_reg_levels(const T *src, T *dst, const Grid2dArgs &a, int64_t m,
-                             hipStream_t stream)
+// Two workgroups of 8 waves are to be resident: at most 128 registers.
+// INSIDE: the grid is smaller than a window (a kernel of its own: its wall
+// tests would cost the others registers).
+template <typename T, int R, int NW, bool INSIDE>
+__global__ __launch_bounds__(NW *kWave, 4) void block2d_kernel(Block2dArgs<T> a)
 {
-    using G = RegTile<D>;
-    const int64_t strips = (a.nx + G::COLS - 1) / G::COLS, rows = (a.ny + G::R - 1) / G::R;
-    const int64_t ntiles = strips * rows;
-    const int64_t blocks = (ntiles + kThreads / kWave - 1) / (kThreads / kWave);
-    const int64_t grid = (blocks + 7) / 8 * 8;
-    if (m & 1)
-        hipLaunchKernelGGL((level2d_reg_kernel<T, D, 1>), dim3((unsigned)grid), dim3(kThreads), 0,
-                           stream, src, dst, (int)a.nx, (int)a.ny, (int)strips, (int)ntiles,
-                           line_coef<T>(a.rx), line_coef<T>(a.ry), (T)a.gw, (T)a.ge, (T)a.gs,
-                           (T)a.gn);
-    else
-        hipLaunchKernelGGL((level2d_reg_kernel<T, D, 0>), dim3((unsigned)grid), dim3(kThreads), 0,
-                           stream, src, dst, (int)a.nx, (int)a.ny, (int)strips, (int)ntiles,
-                           line_coef<T>(a.rx), line_coef<T>(a.ry), (T)a.gw, (T)a.ge, (T)a.gs,
-                           (T)a.gn);
-    return hipGetLastError();
+    using X = typename Pair2<T>::type;
+    using M = typename Pair2<T>::mem;
+    __shared__ __attribute__((aligned(16))) unsigned char lds[2 * NW * 2 * kEdge<T> * kWave * 2 * sizeof(T)];
+    X *xch = reinterpret_cast<X *>(lds);
+    const int t = (int)(blockIdx.x % 8) * (int)(gridDim.x / 8) + (int)(blockIdx.x / 8);   // XCD-aware
+    if (t >= a.ntiles)
+        return;
+    const int lane = threadIdx.x & (kWave - 1);
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int cx0 = (t % a.tx) * a.cx, cy0 = (t / a.tx) * a.cy;
+    const int x0 = max(0, min(cx0 - a.halo, a.nx - kCols));
+    const int y0 = max(0, min(cy0 - a.halo, a.ny - NW * R));
+    const int row0 = y0 + w * R, ia = x0 + 2 * lane;
+    T ua[R], ub[R];
+#pragma unroll
+    for (int q = 0; q < R; ++q) {
+        // wave-uniform row address, so that it stays in scalar registers
+        const T *row = a.in + (int64_t)(row0 + q) * a.nx + x0;
+        if constexpr (INSIDE) {
+            ua[q] = row0 + q < a.ny && ia < a.nx ? row[2 * lane] : T(0);
+            ub[q] = row0 + q < a.ny && ia + 1 < a.nx ? row[2 * lane + 1] : T(0);
+        } else {
+            const M v = *reinterpret_cast<const M *>(row + 2 * lane);
+            ua[q] = v.x;
+            ub[q] = v.y;
+        }
+    }
+    // single registers from here on: as the halves of the loads' tuples they
+    // would be copied for each of the paths below, past the 128 registers
+#pragma unroll
+    for (int q = 0; q < R; ++q) asm("" : "+v"(ua[q]), "+v"(ub[q]));
+    const bool ends = x0 == 0 || x0 + kCols == a.nx, odd = ((x0 ^ y0) & 1) != 0;
+    if constexpr (INSIDE) {
+        if (odd) wave_levels<T, R, NW, kInside, true>(a, x0, y0, w, ua, ub, xch);
+        else wave_levels<T, R, NW, kInside, false>(a, x0, y0, w, ua, ub, xch);
+    } else if (ends) {
+        if (odd) wave_levels<T, R, NW, kEnds, true>(a, x0, y0, w, ua, ub, xch);
+        else wave_levels<T, R, NW, kEnds, false>(a, x0, y0, w, ua, ub, xch);
+    } else {
+        if (odd) wave_levels<T, R, NW, kOpen, true>(a, x0, y0, w, ua, ub, xch);
+        else wave_levels<T, R, NW, kOpen, false>(a, x0, y0, w, ua, ub, xch);
+    }
+    const int cx1 = min(cx0 + a.cx, a.nx), cy1 = min(cy0 + a.cy, a.ny);
+    const bool has_a = ia >= cx0 && ia < cx1, has_b = ia + 1 >= cx0 && ia + 1 < cx1;
+#pragma unroll
+    for (int q = 0; q < R; ++q) {
+        if (row0 + q < cy0 || row0 + q >= cy1) continue;   // wave-uniform
+        T *o = a.out + (int64_t)(row0 + q) * a.nx + x0 + 2 * lane;
+        if (has_a && has_b) *reinterpret_cast<M *>(o) = M{ua[q], ub[q]};
+        else if (has_a) o[0] = ua[q];
+        else if (has_b) o[1] = ub[q];
+    }
 }
 
-template <typename T>
-hipError_t launch_2d_t(const Grid2dArgs &a, hipStream_t stream)
+template <typename T> Dir<T> dir(double r)
 {
-    const T *src = static_cast<const T *>(a.u);
-    T *dst = static_cast<T *>(a.work);
-    int64_t launches = 0;
-    for (int64_t s = 0; s < a.nsteps;) {
-        // D levels per launch while D remain, then single levels
-        const int d = a.nsteps - s >= a.depth ? a.depth : 1;
-        hipError_t e;
-        if (d == 4) e = launch_reg_levels<T, 4>(src, dst, a, a.step0 + s, stream);
-        else if (d == 2) e = launch_reg_levels<T, 2>(src, dst, a, a.step0 + s, stream);
-        else e = launch_reg_levels<T, 1>(src, dst, a, a.step0 + s, stream);
+    return Dir<T>{(T)r, (T)(r / (1.0 + 2.0 * r)), (T)((r + r * r) / (1.0 + 2.0 * r)),
+                  (T)(r / (1.0 + r))};
+}
+
+// Rows per wave and levels per launch: the pair with the least estimated time
+// of a level, in us.  One window per compute unit takes `one` for a level,
+// many at once `many` each; half of the grid's traffic at 5.8 TB/s (a grid of
+// 4096 x 4096 FP64 and its copy just exceed the 256 MB cache) is not hidden,
+// and a launch costs 2.4 us.  Fitted to 96 levels of 196 x 578 to 4096 x 4096
+// points and within 25% of all of them: small grids want few rows (196 x 578
+// FP64 4 rows, 10 levels per launch 78 us, 8 rows at best 95), larger ones
+// more rows and fewer levels (4096 x 4096 FP64 8 rows, 6 or 8 levels 1.00 ms,
+// 12 levels 1.16; 2048 x 2048 FP32 16 rows 0.23 ms, 8 rows 0.27).  FP64 holds at
+// most 8 rows a lane: 16 spill at two workgroups per unit (1.10 ms at best).
+struct Shape {
+    int rows;
+    double one64, many64, one32, many32;
+};
+constexpr Shape kShapes[] = {{4, 0.53, 0.53, 0.41, 0.41}, {8, 0.88, 0.70, 0.72, 0.50},
+                             {16, 0.0, 0.0, 1.1, 0.75}};
+constexpr int kDepths[] = {1, 2, 4, 6, 8, 10, 12, 16, 20, 24};
+constexpr double kUnits = 256.0, kBytesPerUs = 5.8e6, kLaunchUs = 2.4;
+
+struct Choice {
+    int rows, depth, halo;
+};
+
+Choice choose(const Grid2dArgs &g, bool f64)
+{
+    Choice best{4, 4, 6};
+    double best_us = 1e300;
+    for (const Shape &s : kShapes) {
+        const double one = f64 ? s.one64 : s.one32, many = f64 ? s.many64 : s.many32;
+        const int rows = kNW * s.rows;
+        if (one == 0.0 || (s.rows > 4 && g.ny < rows)) continue;
+        for (int d : kDepths) {
+            const int halo = (d + 2) / 2 * 2;
+            if ((g.depth != 0 && d != g.depth) || 2 * halo >= rows) continue;
+            const double cx = kCols - 2 * halo, cy = rows - 2 * halo;
+            const double tiles = std::ceil(g.nx / cx) * std::ceil(g.ny / cy);
+            const double mem = 2.0 * g.nx * g.ny * (f64 ? 8 : 4) / kBytesPerUs;
+            const double t = std::max(one, many * std::ceil(tiles / kUnits)) + (0.5 * mem + kLaunchUs) / d;
+            if (t < best_us) {
+                best_us = t;
+                best = Choice{s.rows, d, halo};
+            }
+        }
+    }
+    return best;
+}
+
+template <typename T, int R>
+hipError_t run(const Grid2dArgs &g, const Choice &c, hipStream_t stream)
+{
+    Block2dArgs<T> a{};
+    a.nx = (int)g.nx;
+    a.ny = (int)g.ny;
+    a.halo = c.halo;
+    a.cx = kCols - 2 * c.halo;
+    a.cy = kNW * R - 2 * c.halo;
+    const int64_t tx = (g.nx + a.cx - 1) / a.cx, ty = (g.ny + a.cy - 1) / a.cy;
+    if (tx * ty > 0x7ffffff0LL) return hipErrorInvalidValue;
+    a.tx = (int)tx;
+    a.ntiles = (int)(tx * ty);
+    a.x = dir<T>(g.rx);
+    a.y = dir<T>(g.ry);
+    a.gw = (T)g.gw;
+    a.ge = (T)g.ge;
+    a.gs = (T)g.gs;
+    a.gn = (T)g.gn;
+    T *bufs[2] = {static_cast<T *>(g.u), static_cast<T *>(g.work)};
+    // an even number of launches leaves the result in u; the levels are
+    // spread evenly over them
+    int64_t launches = (g.nsteps + c.depth - 1) / c.depth;
+    if ((launches & 1) && g.nsteps > launches) ++launches;
+    int64_t done = 0;
+    const dim3 grid((unsigned)(((int64_t)a.ntiles + 7) / 8 * 8));
+    for (int64_t i = 0; i < launches; ++i) {
+        a.in = bufs[i & 1];
+        a.out = bufs[(i + 1) & 1];
+        a.level0 = g.step0 + done;
+        a.nlev = (int)(g.nsteps / launches + (i < g.nsteps % launches ? 1 : 0));
+        if (g.nx < kCols || g.ny < kNW * R)
+            hipLaunchKernelGGL((block2d_kernel<T, R, kNW, true>), grid, dim3(kNW * kWave), 0, stream, a);
+        else
+            hipLaunchKernelGGL((block2d_kernel<T, R, kNW, false>), grid, dim3(kNW * kWave), 0, stream, a);
+        const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
-        s += d;
-        ++launches;
-        T *t = const_cast<T *>(src);
-        src = dst;
-        dst = t;
+        done += a.nlev;
     }
-    // after an odd number of launches the result sits in the workspace
-    if (launches % 2 == 1)
-        return hipMemcpyAsync(a.u, a.work, (size_t)(a.nx * a.ny) * sizeof(T),
+    if (launches & 1)
+        return hipMemcpyAsync(g.u, g.work, (size_t)(g.nx * g.ny) * sizeof(T),
                               hipMemcpyDeviceToDevice, stream);
     return hipSuccess;
 }
 
 }  // namespace
 
-hipError_t launch_2d(int prec, const Grid2dArgs &a, hipStream_t stream)
+hipError_t launch_2d(int prec, const Grid2dArgs &g, hipStream_t stream)
 {
-    const int64_t tiles = ((a.nx + 111) / 112) * ((a.ny + 19) / 20);   // most tiles, D = 4
     // indices inside a launch are 32-bit: rows and columns below 2^31
-    if (a.nx < 1 || a.ny < 1 || a.nx > 0x7fffff00LL || a.ny > 0x7fffff00LL || tiles > 0x7ffffff0LL ||
-        (a.depth != 1 && a.depth != 2 && a.depth != 4))
+    if (g.nx < 1 || g.ny < 1 || g.nx > 0x7fffff00LL || g.ny > 0x7fffff00LL ||
+        (g.depth != 0 && g.depth != 1 && g.depth != 2 && g.depth != 4) ||
+        (prec != kFP64 && prec != kFP32))
         return hipErrorInvalidValue;
-    if (prec == kFP64) return launch_2d_t<double>(a, stream);
-    if (prec == kFP32) return launch_2d_t<float>(a, stream);
-    return hipErrorInvalidValue;
+    const Choice c = choose(g, prec == kFP64);
+    if (prec == kFP64)
+        return c.rows == 4 ? run<double, 4>(g, c, stream) : run<double, 8>(g, c, stream);
+    return c.rows == 4   ? run<float, 4>(g, c, stream)
+           : c.rows == 8 ? run<float, 8>(g, c, stream)
+                         : run<float, 16>(g, c, stream);
 }
 
 }  // namespace ge

@@ -745,12 +745,6 @@ ge_status ge_comp_from_fp64(const double *x, float *pair, int64_t n, void *strea
     return e == hipSuccess ? GE_OK : hip_fail(e, "ge_comp_from_fp64");
 }
 
-// Levels per launch of the 2D extension when the caller leaves it to the
-// library: measured on MI355X (4096^2 points, 200 levels), four levels per
-// launch 8.7e11 updates/s in FP64 against 6.4e11 at two and 3.7e11 at one
-// (FP32: 1.39e12, 1.06e12, 6.6e11).
-constexpr int kDepth2d = 4;
-
 size_t ge_2d_workspace_bytes(const ge_2d_desc *d)
 {
     if (!d || d->nx < 1 || d->ny < 1 || d->nx > 0x7fffff00LL || d->ny > 0x7fffff00LL ||
@@ -800,7 +794,7 @@ ge_status ge_2d_step_n(const ge_2d_desc *d, void *u, void *workspace, int64_t st
     a.ge = d->g_east;
     a.gs = d->g_south;
     a.gn = d->g_north;
-    a.depth = d->depth != 0 ? d->depth : kDepth2d;
+    a.depth = d->depth;
     const hipError_t e = ge::launch_2d(d->precision, a, static_cast<hipStream_t>(stream));
     if (e != hipSuccess)
         return ge::set_error(GE_ERR_HIP, "ge_2d_step_n: %s", hipGetErrorString(e));

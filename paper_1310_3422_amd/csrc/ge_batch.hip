@@ -429,19 +429,9 @@ __device__ __forceinline__ void run_task_halo(const BatchArgs &a, const BatchTas
     }
     const int64_t g0 = ws + (int64_t)lane * K;
     if (rod >= 0) {
-        // every window of the rod lies inside it; the last one's start need
-        // not be aligned
-        if (hasR) {
-            load_lane<T, K>(us + g0, s);
-            if constexpr (COMP) load_lane<T, K>(ue + g0, e);
-        } else {
-#pragma unroll
-            for (int j = 0; j < K; ++j) s[j] = us[g0 + j];
-            if constexpr (COMP) {
-#pragma unroll
-                for (int j = 0; j < K; ++j) e[j] = ue[g0 + j];
-            }
-        }
+        // every window of the rod lies inside it
+        load_lane<T, K>(us + g0, s);
+        if constexpr (COMP) load_lane<T, K>(ue + g0, e);
     } else {
 #pragma unroll
         for (int j = 0; j < K; ++j) s[j] = T(0);

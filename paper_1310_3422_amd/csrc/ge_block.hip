@@ -67,14 +67,8 @@ __device__ __forceinline__ void block_wave(const TileArgs &a, const BlockShape &
     const int lane = threadIdx.x & (kWave - 1);
     const int64_t g0 = p0 + lane * K;
     T u[K], b[K];
-    const T *in = static_cast<const T *>(a.in);
-#pragma unroll
-    for (int j = 0; j < K; ++j) u[j] = in[g0 + j];
-    if constexpr (SRC) {
-        const T *sb = static_cast<const T *>(a.src_b);
-#pragma unroll
-        for (int j = 0; j < K; ++j) b[j] = sb[g0 + j];
-    }
+    load_lane<T, K>(static_cast<const T *>(a.in) + g0, u);
+    if constexpr (SRC) load_lane<T, K>(static_cast<const T *>(a.src_b) + g0, b);
 
     const bool lane_l = LEFT && lane == 0, lane_r = RIGHT && lane == kWave - 1;
     const bool flux = (LEFT || RIGHT) && a.flux != nullptr;    // uniform

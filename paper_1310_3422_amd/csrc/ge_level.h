@@ -172,26 +172,28 @@ __device__ __forceinline__ void raise_if_nonfinite(int *status, T acc)
 }
 
 // ---- 16-byte vector access to a lane's K contiguous values ----------------
+// A 16-byte access needs no more than the element's alignment here (a window
+// that ends at a wall may start at any element).
+typedef float float4_any __attribute__((ext_vector_type(4), aligned(4)));
+typedef double double2_any __attribute__((ext_vector_type(2), aligned(8)));
 template <typename T> struct V16;
-template <> struct V16<float> { using type = float4; static constexpr int E = 4; };
-template <> struct V16<double> { using type = double2; static constexpr int E = 2; };
+template <> struct V16<float> { using type = float4_any; static constexpr int E = 4; };
+template <> struct V16<double> { using type = double2_any; static constexpr int E = 2; };
 
 template <typename T, int K>
 __device__ __forceinline__ void load_lane(const T *__restrict__ p, T (&v)[K])
 {
     using V = typename V16<T>::type;
     constexpr int E = V16<T>::E;
-    static_assert(K % E == 0, "K must fill whole 16-byte chunks");
-    const V *q = reinterpret_cast<const V *>(p);
+    constexpr int C = K / E;                      // whole chunks, then single values
 #pragma unroll
-    for (int c = 0; c < K / E; ++c) {
-        const V x = q[c];
-        if constexpr (E == 4) {
-            v[4 * c] = x.x; v[4 * c + 1] = x.y; v[4 * c + 2] = x.z; v[4 * c + 3] = x.w;
-        } else {
-            v[2 * c] = x.x; v[2 * c + 1] = x.y;
-        }
+    for (int c = 0; c < C; ++c) {
+        const V x = reinterpret_cast<const V *>(p)[c];
+#pragma unroll
+        for (int i = 0; i < E; ++i) v[c * E + i] = x[i];
     }
+#pragma unroll
+    for (int j = C * E; j < K; ++j) v[j] = p[j];
 }
 
 template <typename T, int K>
@@ -244,16 +246,33 @@ __device__ __forceinline__ void store_lane_chunks(T *__restrict__ p, int64_t g0,
     }
 }
 
+// Store the values whose global index lies in [lo, hi), any lo and hi: whole
+// 16-byte chunks where they lie inside, single values where one straddles.
 template <typename T, int K>
 __device__ __forceinline__ void store_lane_guarded(T *__restrict__ p, int64_t g0, int64_t lo,
                                                    int64_t hi, const T (&v)[K], T &fin)
 {
+    using V = typename V16<T>::type;
+    constexpr int E = V16<T>::E;
 #pragma unroll
-    for (int j = 0; j < K; ++j)
-        if (g0 + j >= lo && g0 + j < hi) {
-            finite_acc(fin, v[j]);
-            p[j] = v[j];
+    for (int c = 0; c < K; c += E) {
+        if (c + E <= K && g0 + c >= lo && g0 + c + E <= hi) {
+            V x;
+#pragma unroll
+            for (int i = 0; i < E; ++i) {
+                finite_acc(fin, v[c + i]);
+                x[i] = v[c + i];
+            }
+            *reinterpret_cast<V *>(p + c) = x;
+        } else {
+#pragma unroll
+            for (int i = 0; i < E; ++i)
+                if (c + i < K && g0 + c + i >= lo && g0 + c + i < hi) {
+                    finite_acc(fin, v[c + i]);
+                    p[c + i] = v[c + i];
+                }
         }
+    }
 }
 
 // Store the values whose global index is below n: whole 16-byte chunks

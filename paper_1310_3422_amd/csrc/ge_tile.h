@@ -35,19 +35,12 @@ __device__ __forceinline__ int64_t window_start(const TileArgs &a, int64_t t)
 }
 
 // The lane's points of the window starting at ws, or its source profile.
-// A window moved to end at the right wall may start at any element.
 template <typename T, int K, int KIND>
 __device__ __forceinline__ void load_window(const T *__restrict__ p, int64_t g0, int64_t n,
                                             T (&v)[K])
 {
-    if constexpr (KIND == kInside) {
-        load_lane_guarded<T, K>(p + g0, g0, n, v);
-    } else if constexpr (KIND == kEnds) {
-#pragma unroll
-        for (int j = 0; j < K; ++j) v[j] = p[g0 + j];
-    } else {
-        load_lane<T, K>(p + g0, v);
-    }
+    if constexpr (KIND == kInside) load_lane_guarded<T, K>(p + g0, g0, n, v);
+    else load_lane<T, K>(p + g0, v);
 }
 
 // The wall value each level reads, 64 levels at a time: a level of the
