@@ -243,7 +243,9 @@ ge_status ge_2d_step_n(const ge_2d_desc *desc, void *u, void *workspace, int64_t
 /* ------------------------------------------------------------------------
  * Batch of independent rods: the same scheme (Section 2) for every rod, each
  * rod with its own n, r and constant wall values, all advanced by the same
- * levels in one persistent launch that a hipGraph captures.
+ * levels: in one persistent launch that a hipGraph captures (the pair, sync
+ * other than 0, ge_solve_batch_static), or split into windows over the whole
+ * chip (ge_solve_batch in FP64 and FP32 with sync = 0).  Same bits either way.
  *
  * Layout of the packed state u: rod i occupies elements
  * offsets[i] .. offsets[i] + n[i] - 1 (double for GE_FP64, float for the two
@@ -252,13 +254,15 @@ ge_status ge_2d_step_n(const ge_2d_desc *desc, void *u, void *workspace, int64_t
  * the buffer length in elements.  Every offsets[i] must be a multiple of 4 and
  * offsets[i+1] >= offsets[i] + n[i].
  *
- * A rod of up to 65536 (GE_FP32) or 32768 (GE_FP64, GE_FP32_COMP) points is
- * held in registers of one workgroup for all levels, so it is read and
+ * Persistent form: a rod of up to 65536 (GE_FP32) or 32768 (GE_FP64,
+ * GE_FP32_COMP) points is held in registers of one workgroup for all levels, so it is read and
  * written once per call.  A longer rod takes a workgroup of its own and is
  * swept the way ge_step_n sweeps a rod: in passes of up to 32 levels over
  * windows with recomputed halos, ping-ponging between u and its own second
  * level buffer in the workspace (an even number of passes, so the result
- * lands in u).  Every rod gets the same bits as ge_step_n gives it.
+ * lands in u).  Windows: a rod of up to 4464 points is one workgroup's, in
+ * place; a longer one is swept in passes over many.  Every rod gets the same
+ * bits as ge_step_n gives it.
  * ---------------------------------------------------------------------- */
 typedef struct ge_batch_s *ge_batch_t;
 
@@ -276,7 +280,8 @@ typedef struct {
                              /* ~/.cache/libge/batch_tune.txt); 0: use the    */
                              /* stored measurement, or built-in defaults      */
     int32_t sync;            /* how the waves of a rod exchange edge values:  */
-                             /* 0 = library choice, 1 = every level, at a     */
+                             /* 0 = library choice (FP64 and FP32: windows;   */
+                             /* the pair: 3), 1 = every level, at a     */
                              /* workgroup barrier, 2 = every level, each wave */
                              /* waiting for its two neighbours only (level    */
                              /* flags in LDS), 3 = neighbouring waves overlap */
@@ -301,9 +306,10 @@ void ge_batch_destroy(ge_batch_t batch);
 int64_t ge_batch_state_elems(ge_batch_t batch);
 
 /* Bytes of device workspace ge_solve_batch needs: 256 (the task queue head),
- * plus, when rods are above the on-chip limit, their second level buffers
- * from byte 256 on (each rod's points rounded up to 64 elements, twice for
- * GE_FP32_COMP). */
+ * plus the second level buffers of the rods swept in passes from byte 256 on
+ * (each rod's points rounded up to 64 elements, twice for GE_FP32_COMP): rods
+ * above 4464 points when the plan splits into windows, else rods above the
+ * on-chip limit. */
 size_t ge_batch_workspace_bytes(ge_batch_t batch);
 
 /* Number of polls (each a short sleep, about 30 ns) a wave's wait for a
@@ -333,10 +339,11 @@ ge_status ge_batch_info(ge_batch_t batch, int32_t *ntasks, int32_t *grid,
 /* Advance every rod from level step0 by nsteps levels, in place in u
  * (device, packed as above, 16-byte aligned).  workspace: device,
  * ge_batch_workspace_bytes() bytes, 256-byte aligned; it must not be used
- * by another run at the same time.  The first call for a given (u,
- * workspace, parity of step0, nsteps) captures the queue reset and the
- * persistent launch in a hipGraph; later calls with the same key replay it
- * on `stream`.  Errors: GE_ERR_INVALID, GE_ERR_SYNC or GE_ERR_NONFINITE (an
+ * by another run at the same time.  A plan split into windows launches its
+ * kernels on `stream` and on a stream of its own that it forks from and joins
+ * back into it.  Otherwise the first call for a given (u, workspace, parity of
+ * step0, nsteps) captures the queue reset and the persistent launch in a
+ * hipGraph; later calls with the same key replay it on `stream`.  Errors: GE_ERR_INVALID, GE_ERR_SYNC or GE_ERR_NONFINITE (an
  * earlier run, finished by now, raised it; nothing is enqueued), GE_ERR_HIP. */
 ge_status ge_solve_batch(ge_batch_t batch, void *u, void *workspace,
                          int64_t step0, int64_t nsteps, void *stream);
@@ -352,7 +359,7 @@ ge_status ge_solve_batch(ge_batch_t batch, void *u, void *workspace,
  * streams, or from two threads) race and give undefined results.
  * Errors: GE_ERR_INVALID (as ge_solve_batch), GE_ERR_UNSUPPORTED (the plan's
  * rods above the on-chip limit need more than 32 MiB - 256 B of second
- * level buffers, ge_batch_workspace_bytes() > 32 MiB), GE_ERR_SYNC /
+ * level buffers), GE_ERR_SYNC /
  * GE_ERR_NONFINITE (as ge_solve_batch), GE_ERR_HIP. */
 ge_status ge_solve_batch_static(ge_batch_t batch, void *u, int64_t step0, int64_t nsteps,
                                 void *stream);

@@ -96,6 +96,35 @@ struct HaloLayout {
     }
 };
 
+// ---- rods in windows (ge_batch_windows.hip) ---------------------------------
+// One window: tile `tile` of rod `rod`, k points per lane; woff: element offset
+// of the rod's second level buffer in u2.
+struct BatchWindow {
+    int32_t rod, tile, k, pad;
+    int64_t woff;
+};
+struct BatchWinArgs {
+    void *u, *u2;
+    const BatchRod *rods;
+    const BatchWindow *list;
+    int64_t level0;
+    int32_t count, nlev, pass;
+    int32_t core, halo;       // of a pass's windows; core = 0: whole rods, in place
+    int *status;
+};
+// kWinTiny: rods below kBatchTiny points, one wave each; kWinBlock: windows of
+// kBatchBlockWaves overlapping waves, all of one launch with at most
+// kBatchNarrowK points per lane (k = kBatchNarrowK or less) or all with more;
+// kWinWave: single-wave windows of 16 or 32 points per lane.
+enum BatchWinKind : int { kWinTiny = 0, kWinBlock = 1, kWinWave = 2 };
+constexpr int kBatchTiny = 256;
+constexpr int kBatchBlockWaves = 4;
+constexpr int kBatchBlockShapes = 5;
+constexpr int kBatchBlockKs[kBatchBlockShapes] = {4, 6, 8, 12, 18};
+constexpr int kBatchNarrowK = 8;      // the widest of the narrow kernel's
+hipError_t launch_batch_windows(int prec, BatchWinKind kind, int k, const BatchWinArgs &a,
+                                hipStream_t stream);
+
 hipError_t launch_batch(int prec, const BatchArgs &a, int grid, hipStream_t stream);
 
 // Library-owned scratch of the allocation-free entry point: a file-scope

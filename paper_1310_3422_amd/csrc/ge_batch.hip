@@ -96,6 +96,8 @@ __device__ __forceinline__ void rod_levels(const BatchArgs &a, const BatchRod &r
             __syncthreads();
         }
     };
+    // a rod of one wave meets nobody (barrier mode: every wave meets)
+    const bool alone = NBR && wr == 0 && !hasR;
     const int wl = w > 0 ? w - 1 : 0, wrr = w < kWaves - 1 ? w + 1 : kWaves - 1;
     T gl_hi, gl_lo, gr_hi, gr_lo;
     split_wall<T, COMP>(rd.gl, gl_hi, gl_lo);
@@ -113,16 +115,20 @@ __device__ __forceinline__ void rod_levels(const BatchArgs &a, const BatchRod &r
         const T pl = lane_l ? T(0) : cf.cs, pr = lane_r ? T(0) : cf.cs;
         auto exchange = [&](int lev, T (&xl)[E], T (&xr)[E]) {
             const int pb = lev & 1;
+            if (!alone) {
 #pragma unroll
-            for (int i = 0; i < E; ++i) {
-                if (lane == 0) xs[pb][w][i] = s[i];
-                if (lane == kWave - 1) xs[pb][w][2 + i] = s[K - 1 - i];
+                for (int i = 0; i < E; ++i) {
+                    if (lane == 0) xs[pb][w][i] = s[i];
+                    if (lane == kWave - 1) xs[pb][w][2 + i] = s[K - 1 - i];
+                }
+                meet(lev);
             }
-            meet(lev);
 #pragma unroll
             for (int i = 0; i < E; ++i) {
-                xl[i] = xs[pb][wl][2 + i];
-                xr[i] = xs[pb][wrr][i];
+                if (!alone) {
+                    xl[i] = xs[pb][wl][2 + i];
+                    xr[i] = xs[pb][wrr][i];
+                }
                 if constexpr (WALL) {
                     if (left_wall) xl[i] = gl_hi;
                     if (ghost_edge) xr[i] = gr_hi;
@@ -233,6 +239,10 @@ __device__ __forceinline__ void run_task(const BatchArgs &a, const BatchTask &tk
 #pragma unroll
         for (int j = 0; j < K; ++j) e[j] = T(0);
     }
+    // single registers from here on: as parts of the loads' tuples they would be
+    // copied for each of the paths below
+#pragma unroll
+    for (int j = 0; j < K; ++j) asm("" : "+v"(s[j]));
     const int64_t w0 = (int64_t)wr * kWave * K;
     const bool wall = (rod >= 0) && (wr == 0 || rd.n - w0 <= (int64_t)kWave * K);
     if (!NBR || rod >= 0) {
@@ -445,6 +455,10 @@ __device__ __forceinline__ void run_task_halo(const BatchArgs &a, const BatchTas
     // K levels pass no other barrier).
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
+    // single registers from here on: as parts of the loads' tuples they would be
+    // copied for each of the paths below
+#pragma unroll
+    for (int j = 0; j < K; ++j) asm("" : "+v"(s[j]));
     switch (__builtin_amdgcn_readfirstlane(mode)) {
     case 1: halo_blocks<T, K, COMP, 1>(a, rd, w, ws, aL, aR, hasL, hasR, s, e, hx, he); break;
     case 2: halo_blocks<T, K, COMP, 2>(a, rd, w, ws, aL, aR, hasL, hasR, s, e, hx, he); break;

@@ -287,6 +287,103 @@ Plan make_plan(const std::vector<int64_t> &n, int prec, const CostModel &cm, int
     return P;
 }
 
+// A batch split into windows (ge_batch_windows.hip).
+struct Windows {
+    bool on = false;
+    std::vector<ge::BatchWindow> list;   // tiny, wide and narrow whole rods, passes' windows
+    std::vector<int> rod_k;
+    int ntiny = 0, nwide = 0, nnarrow = 0, npass = 0;
+    ge::BatchWinKind kind = ge::kWinWave;   // of the passes' windows
+    int k = 0, core = 0, halo = 0, depth = 1;
+    int64_t elems = 0;                   // second level buffers of the longer rods
+    double est_us = 0;
+};
+
+// One level of a window of four overlapping waves, us, per shape (k = 4, 6, 8,
+// 12, 18), and the fixed cost of a launch: as for single rods (ge_api.hip).
+constexpr double kWinLevelUs[ge::kBatchBlockShapes] = {0.087, 0.101, 0.115, 0.145, 0.19};
+constexpr double kWinLaunchUs = 6.0;
+
+// The longer rods' points decide how they are cut, as a single rod's length
+// does: up to 768000 points block windows, about one per compute unit; then
+// waves of 16 points a lane, 64 levels per pass, and from 6 million on of 32
+// points and 96 levels.
+constexpr int64_t kWinBlockMax = 768000, kWinWideMin = 6000000;
+
+Windows make_windows(const std::vector<int64_t> &n, int prec, int units)
+{
+    Windows w;
+    const int nr = (int)n.size();
+    w.on = true;
+    w.rod_k.assign(nr, 0);
+    auto cap = [](int shape) {
+        return (int64_t)ge::block_capacity(ge::kBatchBlockKs[shape], ge::kBatchBlockWaves);
+    };
+    const int64_t whole = cap(ge::kBatchBlockShapes - 1);
+    std::vector<int> order(nr);
+    for (int i = 0; i < nr; ++i) order[i] = i;
+    // the longest first: the last to start are the shortest to run
+    std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return n[a] > n[b]; });
+    for (int r : order)
+        if (n[r] < ge::kBatchTiny) {
+            w.list.push_back({r, 0, 4, 0, 0});
+            w.rod_k[r] = 4;
+            ++w.ntiny;
+        }
+    for (int r : order)
+        if (n[r] >= ge::kBatchTiny && n[r] <= whole) {
+            int s = 0;
+            while (n[r] > cap(s)) ++s;
+            w.list.push_back({r, 0, ge::kBatchBlockKs[s], 0, 0});
+            w.rod_k[r] = ge::kBatchBlockKs[s];
+            ++(ge::kBatchBlockKs[s] > ge::kBatchNarrowK ? w.nwide : w.nnarrow);
+        }
+    int64_t points = 0, all = 0;
+    for (int64_t m : n) {
+        all += m;
+        if (m > whole) points += m;
+    }
+    if (points > 0) {
+        if (points <= kWinBlockMax) {
+            w.kind = ge::kWinBlock;
+            double best = 1e300;
+            // rods end in short cores: leave room for some more than one
+            // window per unit
+            const int64_t core = (points + units * 7 / 8 - 1) / (units * 7 / 8) / 2 * 2 + 2;
+            for (int s = 0; s < ge::kBatchBlockShapes; ++s) {
+                const int64_t halo = (cap(s) - core) / 4 * 2;
+                if (halo < 65) continue;
+                const double us = kWinLevelUs[s] + kWinLaunchUs / (halo - 1);
+                if (us < best) {
+                    best = us;
+                    w.k = ge::kBatchBlockKs[s];
+                    w.core = (int)core;
+                    w.halo = (int)halo;
+                }
+            }
+            w.depth = w.halo - 1;
+        } else {
+            w.kind = ge::kWinWave;
+            w.k = points < kWinWideMin ? 16 : 32;
+            w.depth = points < kWinWideMin ? 64 : 96;
+            const int align = prec == ge::kFP64 ? 2 : 4;
+            w.halo = (w.depth + 1 + align - 1) / align * align;
+            w.core = 64 * w.k - 2 * w.halo;
+        }
+        for (int r : order) {
+            if (n[r] <= whole) continue;
+            const int tiles = (int)((n[r] + w.core - 1) / w.core);
+            for (int t = 0; t < tiles; ++t) w.list.push_back({r, t, w.k, 0, w.elems});
+            w.npass += tiles;
+            w.rod_k[r] = w.k;
+            w.elems += (n[r] + 63) / 64 * 64;
+        }
+    }
+    // a level at the chip's rate, or one window's latency
+    w.est_us = std::max(0.1, (double)all / (prec == ge::kFP64 ? 8.0e6 : 9.0e6));
+    return w;
+}
+
 int device_grid()
 {
     int dev = 0, cus = 0;
@@ -318,7 +415,11 @@ struct ge_batch_s {
     ge::StatusWords status; // words raised by the kernels
     BatchRod *d_rods;
     BatchTask *d_tasks;
+    Windows win;            // the split ge_solve_batch runs, when win.on
+    ge::BatchWindow *d_win; // its windows: tiny, whole rods, passes' windows
     hipStream_t cap;        // private stream used only for capture
+    hipStream_t side;       // of win's runs, with the events that fork and join it
+    hipEvent_t fork, join;
     // instantiated graphs, one per (state, workspace, parity, level count),
     // the least recently used replaced when all slots are taken
     struct Graph {
@@ -362,6 +463,14 @@ ge_status take_status(ge_batch_s *b, const char *who)
     return GE_OK;
 }
 
+// Workspace of a run: the queue head, then second level buffers of `elems`
+// elements from byte 256 on.
+size_t work_bytes(const ge_batch_s *b, int64_t elems)
+{
+    const size_t u2 = (size_t)elems * (b->prec == ge::kFP32C ? 2 : 1) * (b->prec == ge::kFP64 ? 8 : 4);
+    return 256 + (u2 + 255) / 256 * 256;
+}
+
 // Drop the instantiated graphs (their kernel arguments are out of date).
 void drop_graphs(ge_batch_s *b)
 {
@@ -375,7 +484,11 @@ void free_batch(ge_batch_s *b)
     if (!b) return;
     drop_graphs(b);
     ge::status_free(b->status);
+    if (b->fork) (void)hipEventDestroy(b->fork);
+    if (b->join) (void)hipEventDestroy(b->join);
+    if (b->side) (void)hipStreamDestroy(b->side);
     if (b->cap) (void)hipStreamDestroy(b->cap);
+    if (b->d_win) (void)hipFree(b->d_win);
     if (b->d_rods) (void)hipFree(b->d_rods);
     if (b->d_tasks) (void)hipFree(b->d_tasks);
     delete b;
@@ -599,6 +712,13 @@ ge_status ge_batch_plan(ge_batch_t *out, const ge_batch_desc *d)
     b->est_us = P.est_us;
     b->has_long = P.has_long;
     b->wait_polls = kDefaultWaitPolls;
+    // the library's choice in FP64 and FP32: windows (the persistent form then
+    // serves ge_solve_batch_static, which has no room for second buffers)
+    if (d->sync == 0 && prec != ge::kFP32C) {
+        b->win = make_windows(b->n, prec, b->grid);
+        b->rod_k = b->win.rod_k;
+        b->est_us = b->win.est_us;
+    }
     hipError_t e;
     if ((e = hipMalloc((void **)&b->d_rods, sizeof(BatchRod) * rods.size())) != hipSuccess ||
         (e = hipMalloc((void **)&b->d_tasks, sizeof(BatchTask) * P.tasks.size())) != hipSuccess) {
@@ -613,6 +733,21 @@ ge_status ge_batch_plan(ge_batch_t *out, const ge_batch_desc *d)
         free_batch(b);
         return hip_fail(e, "ge_batch_plan: setup");
     }
+    if (b->win.on) {
+        const size_t bytes = sizeof(ge::BatchWindow) * b->win.list.size();
+        if ((e = hipMalloc((void **)&b->d_win, bytes)) != hipSuccess) {
+            free_batch(b);
+            return fail(GE_ERR_NOMEM, "ge_batch_plan: device tables: %s", hipGetErrorString(e));
+        }
+        if ((e = hipMemcpy(b->d_win, b->win.list.data(), bytes, hipMemcpyHostToDevice)) != hipSuccess ||
+            (e = hipStreamCreateWithFlags(&b->side, hipStreamNonBlocking)) != hipSuccess ||
+            (e = hipEventCreateWithFlags(&b->fork, hipEventDisableTiming)) != hipSuccess ||
+            (e = hipEventCreateWithFlags(&b->join, hipEventDisableTiming)) != hipSuccess) {
+            free_batch(b);
+            return hip_fail(e, "ge_batch_plan: setup");
+        }
+        std::vector<ge::BatchWindow>().swap(b->win.list);
+    }
     if (!ge::status_alloc(b->status)) {
         free_batch(b);
         return fail(GE_ERR_NOMEM, "ge_batch_plan: status words could not be allocated");
@@ -626,10 +761,7 @@ void ge_batch_destroy(ge_batch_t b) { free_batch(b); }
 size_t ge_batch_workspace_bytes(ge_batch_t b)
 {
     if (!b) return 0;
-    if (!b->has_long) return 256;
-    const size_t u2 = (size_t)b->long_elems * (b->prec == ge::kFP32C ? 2 : 1) *
-                      (b->prec == ge::kFP64 ? 8 : 4);
-    return 256 + (u2 + 255) / 256 * 256;
+    return b->win.on ? work_bytes(b, b->win.elems) : work_bytes(b, b->long_elems);
 }
 
 ge_status ge_batch_set_wait_polls(ge_batch_t b, int64_t polls)
@@ -692,6 +824,61 @@ ge::BatchArgs run_args(const ge_batch_s *b, void *u, void *work, int64_t step0, 
     return a;
 }
 
+// One run of the split into windows: the rods that one wave or window holds on
+// the plan's side stream beside the passes, forked from and joined back into
+// the caller's stream.  Launched as they are: a graph of these few kernels took
+// 0.2-1.1 ms to instantiate (for every new state) and saved nothing after.
+hipError_t run_windows(ge_batch_s *b, void *u, void *work, int parity, int64_t nsteps,
+                       hipStream_t main)
+{
+    const Windows &w = b->win;
+    ge::BatchWinArgs a{};
+    a.u = u;
+    a.u2 = static_cast<char *>(work) + 256;
+    a.rods = b->d_rods;
+    a.level0 = parity;
+    a.nlev = (int32_t)nsteps;
+    a.status = b->status.dev;
+    // what runs on the side branch, and what before the passes
+    const int whole = w.nwide + w.nnarrow + w.ntiny;
+    const bool beside = w.npass > 0 ? whole > 0 : w.nwide > 0 && w.nnarrow + w.ntiny > 0;
+    hipStream_t side = beside ? b->side : main, rest = w.npass > 0 ? side : main;
+    hipError_t e = hipSuccess;
+    if (beside) {
+        if ((e = hipEventRecord(b->fork, main)) != hipSuccess) return e;
+        if ((e = hipStreamWaitEvent(side, b->fork, 0)) != hipSuccess) return e;
+    }
+    a.list = b->d_win + w.ntiny;
+    a.count = w.nwide;
+    e = ge::launch_batch_windows(b->prec, ge::kWinBlock, ge::kBatchNarrowK + 1, a, side);
+    if (e != hipSuccess) return e;
+    a.list += w.nwide;
+    a.count = w.nnarrow;
+    e = ge::launch_batch_windows(b->prec, ge::kWinBlock, ge::kBatchNarrowK, a, rest);
+    if (e != hipSuccess) return e;
+    a.list = b->d_win;
+    a.count = w.ntiny;
+    e = ge::launch_batch_windows(b->prec, ge::kWinTiny, 4, a, rest);
+    if (e != hipSuccess) return e;
+    if (beside && (e = hipEventRecord(b->join, side)) != hipSuccess) return e;
+    if (w.npass > 0) {
+        a.list = b->d_win + whole;
+        a.count = w.npass;
+        a.core = w.core;
+        a.halo = w.halo;
+        int64_t passes = (nsteps + w.depth - 1) / w.depth, done = 0;
+        passes += passes & 1;                // the result lands in u
+        for (int64_t p = 0; p < passes; ++p) {
+            a.pass = (int32_t)(p & 1);
+            a.level0 = parity + done;
+            a.nlev = (int32_t)(nsteps / passes + (p < nsteps % passes ? 1 : 0));
+            if ((e = ge::launch_batch_windows(b->prec, w.kind, w.k, a, main)) != hipSuccess) return e;
+            done += a.nlev;
+        }
+    }
+    return beside ? hipStreamWaitEvent(main, b->join, 0) : hipSuccess;
+}
+
 // Checks shared by both run entry points; reports what earlier runs raised.
 ge_status check_run(ge_batch_s *b, void *u, int64_t step0, int64_t nsteps, const char *who)
 {
@@ -744,6 +931,10 @@ ge_status ge_solve_batch(ge_batch_t b, void *u, void *workspace, int64_t step0, 
         return GE_OK;
     hipStream_t st = static_cast<hipStream_t>(stream);
     const int parity = (int)(step0 & 1);
+    if (b->win.on) {
+        const hipError_t e = run_windows(b, u, workspace, parity, nsteps, st);
+        return e == hipSuccess ? GE_OK : hip_fail(e, "ge_solve_batch: launch");
+    }
     ge_batch_s::Graph *slot = nullptr;
     for (int i = 0; i < b->ngraphs; ++i) {
         ge_batch_s::Graph &g = b->graphs[i];
@@ -793,7 +984,7 @@ ge_status ge_solve_batch_static(ge_batch_t b, void *u, int64_t step0, int64_t ns
         const ge_status rs = check_run(b, u, step0, nsteps, "ge_solve_batch_static");
         if (rs != GE_OK) return rs;
     }
-    const size_t need = ge_batch_workspace_bytes(b);
+    const size_t need = work_bytes(b, b->long_elems);
     if (need > ge::kBatchScratchBytes)
         return fail(GE_ERR_UNSUPPORTED,
                     "ge_solve_batch_static: the plan needs %zu bytes of scratch (its rods above "
