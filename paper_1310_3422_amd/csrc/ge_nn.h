@@ -14,6 +14,7 @@ struct ConvArgs {
     const void *w;        // bf16 [5][cout][cin]
     const float *bias;    // [cout] or null
     int width;            // points per rod, a multiple of 128
+    int batch;            // rods (set by launch_conv)
     int dil;              // tap spacing d: taps at offsets (k - 2) d, 1 <= d <= kMaxDil
     void *pre_out;        // bf16 [..][cout]  (kEpiGelu*; null: not stored)
     void *act_out;        // bf16 [..][cout]  (kEpiGelu*)
@@ -54,7 +55,7 @@ constexpr int kMaxWgradBlocks = 256;
 constexpr int kMaxDil = 16;         // largest tap spacing of a layer
 constexpr int kWgradSegment = 128;  // positions a half workgroup reduces at a time
 
-hipError_t launch_conv(int cin, int cout, int epi, const ConvArgs &a, int batch, hipStream_t s);
+hipError_t launch_conv(int cin, int cout, int epi, ConvArgs a, int batch, hipStream_t s);
 // Weight gradients (ge_nn_wgrad.hip): the workgroups of a launch, the floats
 // one of them writes for a layer of ci and co real channels, the products, and
 // the sums of up to six layers in one launch.

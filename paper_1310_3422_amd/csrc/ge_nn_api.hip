@@ -272,12 +272,18 @@ ge_status ge_nn_create(ge_nn_t *out, int32_t width, int32_t max_batch, uint64_t 
     ok = ok && dalloc(n, &n->save, M * 4) && dalloc(n, &n->unn, M * 4) &&
          dalloc(n, &n->gev, M * 8) && dalloc(n, &n->flag, (size_t)max_batch * 4) &&
          dalloc(n, &n->count, 256);
+    // the weight-gradient sums of the six layers in one buffer
+    size_t wfloats = 0;
+    for (const Layer &L : kLayers)
+        wfloats += wgrad_blocks(width, max_batch) * (size_t)wgrad_part_floats(L.ci, L.co);
+    ok = ok && dalloc(n, &n->wpart[0], wfloats * 4);
+    for (int l = 1; ok && l < 6; ++l)
+        n->wpart[l] = n->wpart[l - 1] + wgrad_blocks(width, max_batch) *
+                                            wgrad_part_floats(kLayers[l - 1].ci, kLayers[l - 1].co);
     ok = ok && hipHostMalloc((void **)&n->h_count, sizeof(int), hipHostMallocDefault) == hipSuccess;
     for (int l = 0; ok && l < 6; ++l) {
         const Layer &L = kLayers[l];
-        ok = dalloc(n, &n->wpart[l],
-                    wgrad_blocks(width, max_batch) * (size_t)wgrad_part_floats(L.ci, L.co) * 4);
-        ok = ok && dalloc(n, &n->wf[l], 5LL * L.cop * L.cip * 2) && dalloc(n, &n->bf[l], L.cop * 4);
+        ok = dalloc(n, &n->wf[l], 5LL * L.cop * L.cip * 2) && dalloc(n, &n->bf[l], L.cop * 4);
         if (ok && l > 0) ok = dalloc(n, &n->wd[l], 5LL * L.cip * L.cod * 2);
     }
     if (!ok) {
