@@ -21,7 +21,7 @@
 // its first node, which the lane to the left holds; A through the even one).
 // The pairs take Eq. (3)/(4) with denominator 1 + 2r in second-difference
 // form; a sweep step is fma(c, v_prev, fma(ca, w, c w_other)), c = r/(1+r),
-// ca = (1-r)/(1+r), taken two nodes at a time (see sweep_run).
+// ca = (1-r)/(1+r).
 //
 // Temporal blocking: a launch advances `nlev` levels of a window of NW x 64
 // SDCs (NW waves of one workgroup) and writes back its core; the window
@@ -42,19 +42,22 @@ namespace {
 
 using namespace dev;
 
+// 16-byte chunks, aligned (LDS rows and windows of whole couples)
+template <typename T> struct Chunk;
+template <> struct Chunk<float> { using type = float4; };
+template <> struct Chunk<double> { using type = double2; };
+
 template <typename T> struct SdcCoef {
     T c, ca;      // r/(1+r), (1-r)/(1+r): the sweep step
     T c1, c2;     // (r+r^2)/(1+2r), r^2/(1+2r): the pair
-    T cc;         // c * c: two sweep steps at once
 };
 
 // in vector registers for FP32 (see lane_coef)
 template <typename T>
 __device__ __forceinline__ SdcCoef<T> sdc_lane_coef(SdcCoef<T> k)
 {
-    k.cc = k.c * k.c;
     if constexpr (sizeof(T) == 4)
-        asm("" : "+v"(k.c), "+v"(k.ca), "+v"(k.c1), "+v"(k.c2), "+v"(k.cc));
+        asm("" : "+v"(k.c), "+v"(k.ca), "+v"(k.c1), "+v"(k.c2));
     return k;
 }
 
@@ -78,34 +81,26 @@ __device__ __forceinline__ T sweep(T v, T w, T wo, const SdcCoef<T> &k)
 }
 
 // A sweep through elements FROM..TO (in either direction) of the lane's
-// registers, starting from the new value v of the node before FROM.  The
-// recurrence v_e = c v_prev + t_e, t_e = ca w_e + c wo_e, is a chain of
-// dependent FMAs; two steps are taken at once, v_{e+1} = c^2 v + (c t_e +
-// t_{e+1}), with v_e off the chain, which halves its length.  other(e) is
-// the old value of e's neighbour on the far side (read before anything is
-// written over it).  Returns the value of the last node.
+// registers, starting from the new value v of the node before FROM:
+// v_e = c v_prev + t_e, t_e = ca w_e + c wo_e, a chain of dependent FMAs
+// with two more instructions a node beside it, which fill the chain's
+// latency.  (Two steps at once, v_{e+1} = c^2 v + (c t_e + t_{e+1}), halve
+// the chain for 3.5 instructions a node; with two or more waves on a SIMD
+// the issue slots count for more: FP64 k = 16 on 2^24 - 1 points 5.03e12
+// against 5.32e12 updates/s here, k = 8 5.78e12 against 6.13e12, FP32 k = 16
+// 9.5e12 against 10.1e12; within 1% at k = 2.)  other(e) is the old value of
+// e's neighbour on the far side (read before anything is written over it).
 template <typename T, int K, int FROM, int TO, typename Other>
-__device__ __forceinline__ T sweep_run(T (&s)[K], T v, const SdcCoef<T> &k, Other other)
+__device__ __forceinline__ void sweep_run(T (&s)[K], T v, const SdcCoef<T> &k, Other other)
 {
     constexpr int step = FROM <= TO ? 1 : -1;
     constexpr int len = (TO - FROM) * step + 1;
 #pragma unroll
-    for (int j = 0; j + 1 < len; j += 2) {
-        const int e0 = FROM + j * step, e1 = e0 + step;
-        const T t0 = fmaT(k.ca, s[e0], k.c * other(e0));
-        const T t1 = fmaT(k.ca, s[e1], k.c * other(e1));
-        const T u = fmaT(k.c, t0, t1);
-        const T v0 = fmaT(k.c, v, t0);
-        v = fmaT(k.cc, v, u);
-        s[e0] = v0;
-        s[e1] = v;
-    }
-    if constexpr (len % 2 == 1) {
-        constexpr int e = TO;
-        v = fmaT(k.c, v, fmaT(k.ca, s[e], k.c * other(e)));
+    for (int j = 0; j < len; ++j) {
+        const int e = FROM + j * step;
+        v = sweep(v, s[e], other(e), k);
         s[e] = v;
     }
-    return v;
 }
 
 // Values that cross a wave's edges.  A level needs, besides its own lanes,
@@ -116,7 +111,9 @@ __device__ __forceinline__ T sweep_run(T (&s)[K], T v, const SdcCoef<T> &k, Othe
 // Each of the two mid-level values is also the other side's start value of
 // the next level, so a window of NW waves exchanges its waves' edge lanes
 // through LDS once per level (one barrier), plus once when a window is
-// loaded.  Lanes 0 and 63 of the window's outer waves take zeros, which
+// loaded.  A value is posted as soon as it is known and taken after the
+// level's other sweep, which hides part of the wait (persistent, four waves,
+// FP64 k = 16: 5.32e12 -> 5.47e12 updates/s).  Lanes 0 and 63 of the window's outer waves take zeros, which
 // reach only the halo; a single-wave window (NW = 1) exchanges nothing.
 template <typename T, int NW>
 struct SdcEdge {
@@ -137,11 +134,16 @@ struct SdcEdge {
             xl63 = w > 0 ? slot[2][w - 1][1] : T(0);
         }
     }
-    // even level, mid-way: lane 63's new pair value to the right wave
-    __device__ __forceinline__ T mid_left(int lane, int buf, T pb)
+    // even level, mid-way: lane 63's new pair value to the right wave ...
+    __device__ __forceinline__ void post_left(int lane, int buf, T pb)
+    {
+        if constexpr (NW > 1)
+            if (lane == kWave - 1) slot[buf][w][1] = pb;
+    }
+    // ... and the left wave's
+    __device__ __forceinline__ T take_left(int buf)
     {
         if constexpr (NW > 1) {
-            if (lane == kWave - 1) slot[buf][w][1] = pb;
             __syncthreads();
             xl63 = w > 0 ? slot[buf][w - 1][1] : T(0);
             return xl63;
@@ -149,11 +151,16 @@ struct SdcEdge {
             return T(0);
         }
     }
-    // odd level, at its end: lane 0's new element 0 to the left wave
-    __device__ __forceinline__ T end_right(int lane, int buf, T s0)
+    // odd level: lane 0's new element 0 to the left wave ...
+    __device__ __forceinline__ void post_right(int lane, int buf, T s0)
+    {
+        if constexpr (NW > 1)
+            if (lane == 0) slot[buf][w][0] = s0;
+    }
+    // ... and the right wave's
+    __device__ __forceinline__ T take_right(int buf)
     {
         if constexpr (NW > 1) {
-            if (lane == 0) slot[buf][w][0] = s0;
             __syncthreads();
             xr0 = w < NW - 1 ? slot[buf][w + 1][0] : T(0);
             return xr0;
@@ -185,15 +192,16 @@ __device__ __forceinline__ void sdc_level(T (&s)[K], const SdcCoef<T> &cf, bool 
             pA = sweep(gr_new, s[K - 2], s[K - 3], cf);
             pB = gr_new;
         }
+        edge.post_left(lane, buf, pB);
+        const T o_even_first = s[k - 1];
+        // scheme B through the even sub-domain, from its last node
+        sweep_run<T, K, K - 3, k - 1>(s, pA, cf, [&](int e) { return s[e - 1]; });
         // scheme A through the odd sub-domain, from its first node (the
         // left lane's pair value, or the left wall)
-        T v = from_left(edge.mid_left(lane, buf, pB), pB);
+        T v = from_left(edge.take_left(buf), pB);
         if (first) v = gl_new;
-        const T o_odd_last = s[k - 2];
-        sweep_run<T, K, 0, k - 2>(s, v, cf, [&](int e) { return s[e + 1]; });
-        // scheme B through the even sub-domain, from its last node
-        sweep_run<T, K, K - 3, k - 1>(s, pA, cf,
-                                      [&](int e) { return e - 1 == k - 2 ? o_odd_last : s[e - 1]; });
+        sweep_run<T, K, 0, k - 2>(s, v, cf,
+                                  [&](int e) { return e == k - 2 ? o_even_first : s[e + 1]; });
         s[K - 2] = pA;
         s[K - 1] = pB;
     } else {
@@ -207,13 +215,16 @@ __device__ __forceinline__ void sdc_level(T (&s)[K], const SdcCoef<T> &cf, bool 
         // scheme B down the odd sub-domain
         if constexpr (k >= 3)
             sweep_run<T, K, k - 3, 0>(s, qA, cf, [&](int e) { return e >= 1 ? s[e - 1] : oL; });
+        else
+            s[0] = qA;
+        edge.post_right(lane, buf, s[0]);
         // scheme A up the even sub-domain
         sweep_run<T, K, k, K - 2>(s, qB, cf, [&](int e) { return s[e + 1]; });
         s[k - 2] = qA;
         s[k - 1] = qB;
         // element K-1 is the first node of the next SDC, the end of its
         // scheme-B sweep: it needs that lane's new element 0
-        const T r0 = from_right(edge.end_right(lane, buf, s[0]), s[0]);
+        const T r0 = from_right(edge.take_right(buf), s[0]);
         const T nk = sweep(r0, o_last, o_prev, cf);
         s[K - 1] = last ? gr_new : nk;
     }
@@ -238,7 +249,7 @@ __device__ __forceinline__ void stage_load(const T *__restrict__ in, int64_t bas
                                            T *lds, T (&s)[K])
 {
     using S = Stage<T, K>;
-    using V = typename V16<T>::type;
+    using V = typename Chunk<T>::type;
     const int lane = threadIdx.x % kWave;
 #pragma unroll
     for (int j = 0; j < S::CH / kWave; ++j) {
@@ -278,7 +289,7 @@ __device__ __forceinline__ void stage_store(T *__restrict__ out, int64_t base, i
                                             int hi, T *lds, const T (&s)[K], T &fin)
 {
     using S = Stage<T, K>;
-    using V = typename V16<T>::type;
+    using V = typename Chunk<T>::type;
     const int lane = threadIdx.x % kWave;
     V *row = reinterpret_cast<V *>(&lds[lane * S::P]);
 #pragma unroll
@@ -426,7 +437,7 @@ __device__ __forceinline__ void wait_vmem() { asm volatile("s_waitcnt vmcnt(0)" 
 __device__ __forceinline__ void wait_lds() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
 
 template <typename T, int K>
-__device__ __forceinline__ void unpack(const typename V16<T>::type &x, T (&s)[K], int q)
+__device__ __forceinline__ void unpack(const typename Chunk<T>::type &x, T (&s)[K], int q)
 {
     if constexpr (V16<T>::E == 4) {
         s[4 * q] = x.x; s[4 * q + 1] = x.y; s[4 * q + 2] = x.z; s[4 * q + 3] = x.w;
@@ -436,9 +447,9 @@ __device__ __forceinline__ void unpack(const typename V16<T>::type &x, T (&s)[K]
 }
 
 template <typename T, int K>
-__device__ __forceinline__ typename V16<T>::type pack(const T (&s)[K], int q)
+__device__ __forceinline__ typename Chunk<T>::type pack(const T (&s)[K], int q)
 {
-    using V = typename V16<T>::type;
+    using V = typename Chunk<T>::type;
     if constexpr (V16<T>::E == 4) return V{s[4 * q], s[4 * q + 1], s[4 * q + 2], s[4 * q + 3]};
     else return V{s[2 * q], s[2 * q + 1]};
 }
@@ -448,7 +459,7 @@ template <typename T, int K>
 __device__ __forceinline__ void rows_read(const T *lds, T (&s)[K])
 {
     using S = Swz<T, K>;
-    using V = typename V16<T>::type;
+    using V = typename Chunk<T>::type;
     const int lane = threadIdx.x % kWave;
 #pragma unroll
     for (int q = 0; q < S::Q; ++q)
@@ -460,7 +471,7 @@ template <typename T, int K>
 __device__ __forceinline__ void rows_write(T *lds, const T (&s)[K])
 {
     using S = Swz<T, K>;
-    using V = typename V16<T>::type;
+    using V = typename Chunk<T>::type;
     const int lane = threadIdx.x % kWave;
 #pragma unroll
     for (int q = 0; q < S::Q; ++q)
@@ -473,7 +484,7 @@ template <typename T, int K>
 __device__ __forceinline__ void rows_swap(T *lds, T (&s)[K])
 {
     using S = Swz<T, K>;
-    using V = typename V16<T>::type;
+    using V = typename Chunk<T>::type;
     const int lane = threadIdx.x % kWave;
 #pragma unroll
     for (int q = 0; q < S::Q; ++q) {
@@ -490,7 +501,7 @@ __device__ __forceinline__ void chunks_store(T *__restrict__ out, int64_t base, 
                                              int hi, const T *lds, T &fin)
 {
     using S = Swz<T, K>;
-    using V = typename V16<T>::type;
+    using V = typename Chunk<T>::type;
     const int lane = threadIdx.x % kWave;
 #pragma unroll
     for (int j = 0; j < S::Q; ++j) {
