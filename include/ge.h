@@ -129,9 +129,13 @@ typedef struct {
                         /* next window from HBM into LDS while the current    */
                         /* one advances (used from 3 windows on; at most 64   */
                         /* levels per launch, else GE_ERR_INVALID);           */
-                        /* the library's choice takes it for GE_FP64 with     */
-                        /* k = 16 from 64 windows on, at 24 levels per launch */
-                        /* (20 otherwise).                                    */
+                        /* the library's choice of waves, depth and schedule  */
+                        /* goes by the length: the longest rods 8 waves at 48 */
+                        /* levels (4 at 40, schedule 2, for GE_FP64, k = 16), */
+                        /* shorter ones fewer waves and up to 96 levels; with */
+                        /* some of the three given, schedule 2 for GE_FP64    */
+                        /* with k = 16 from 64 windows on, 24 levels in       */
+                        /* single-wave windows (20 otherwise).                */
 } ge_desc;
 
 /* Bytes of device workspace a ge_step_n call on this problem needs (the

@@ -290,13 +290,6 @@ bool side_create(ge::SideStream &ss)
     return ok;
 }
 
-// The persistent form pays where one couple fills 32 FP64 registers per
-// node pair (k = 16): two waves per SIMD, so the per-tile form leaves its
-// loads exposed.  Measured there 2-9% faster; at k <= 8, or in FP32, the
-// per-tile form is as fast or faster.
-bool sdc_persistent_pays(int prec, int k) { return prec == ge::kFP64 && k == 16; }
-constexpr int64_t kSdcPersistentMinTiles = 64;
-
 // Halo, in sub-domain couples, for D levels: a wrong value at an open window
 // edge moves at most k + 1 nodes per level, two more for the pair stencil.
 int sdc_halo(int depth, int k) { return (depth * (k + 1) + 2 + 2 * k - 1) / (2 * k); }
@@ -319,22 +312,84 @@ int sdc_default_depth(int prec, int k, int waves)
     }
 }
 
-// Waves per window when the caller leaves them to the library: the widest
-// window measured fastest on 2^24 - 1 points (FP64 with k = 16: four waves
-// at 40 levels, persistent, 4.7e12 updates/s against 3.7e12 single-wave;
-// otherwise eight at 48 levels, per tile: FP64 k = 8 5.2e12 against 3.7e12,
-// FP32 k = 16 9.1e12 against 6.0e12), as long as the rod gives that launch
-// at least 8192 waves (4 per SIMD at two resident); shorter rods keep
-// single-wave windows, whose many small tiles spread over the chip.
-int sdc_default_waves(int prec, int k, int64_t nsdc, int depth_given)
+// Windows, depth and schedule of the sub-domain scheme.
+struct SdcShape {
+    int waves, depth;
+    bool persistent;
+};
+
+// waves of a launch over nsdc couples in windows of `waves` waves and
+// `depth` levels (0: such a window has no core)
+int64_t sdc_launch_waves(int64_t nsdc, int k, int waves, int depth)
+{
+    const int64_t core = 64 * waves - 2 * (int64_t)sdc_halo(depth, k);
+    return core < 16 ? 0 : (nsdc + core - 1) / core * waves;
+}
+
+// The widest window measured fastest on 2^24 - 1 points (FP64 with k = 16:
+// four waves at 40 levels, persistent, 5.4e12 updates/s against 4.0e12
+// single-wave; otherwise eight at 48 levels, per tile: FP64 k = 8 6.1e12
+// against 3.8e12, FP32 k = 16 10.1e12 against 6.6e12), as long as the rod
+// gives that launch at least 8192 waves (4 per SIMD at two resident).
+bool sdc_fills_wide(int prec, int k, int64_t nsdc, int depth)
 {
     const int wide = (prec == ge::kFP64 && k == 16) ? 4 : 8;
-    const int depth = depth_given ? depth_given : sdc_default_depth(prec, k, wide);
-    const int64_t core = 64 * wide - 2 * (int64_t)sdc_halo(depth, k);
-    if (core < 16)
-        return 1;
-    const int64_t tiles = (nsdc + core - 1) / core;
-    return tiles * wide >= 8192 ? wide : 1;
+    if (depth == 0) depth = sdc_default_depth(prec, k, wide);
+    return sdc_launch_waves(nsdc, k, wide, depth) >= 8192;
+}
+
+// What the library takes where the caller leaves waves, depth and schedule
+// to it.  Rods that fill the chip take the widest windows; below that a
+// launch is bound by its own latency (launch, first loads, the chain of a
+// level's sweeps), so it should run as many levels as the halo allows while
+// every window still gets a SIMD of its own.  Measured, us per level, against
+// single-wave windows of 20 levels (24 persistent for FP64 with k = 16):
+//   one wave per SIMD: one wave, 32 levels (FP64 k = 8, 2^17 points: 0.267
+//   against 0.365; k = 16: 0.383 against 0.433); k = 2 has no core there and
+//   takes two waves, 64 levels (FP32, 2^15: 0.199 against 0.218);
+//   up to four waves per SIMD (FP64 with k = 16, whose registers leave room
+//   for two: two): four waves, 64 levels, persistent (FP64 k = 4, 2^20: 0.353
+//   against 0.534; FP32 k = 16, 2^21: 0.429 against 0.622);
+//   between those and the wide ones: eight waves, 96 levels, per tile (FP64
+//   k = 8, 2^22: 0.954 against 1.413; FP32 k = 16, 2^23: 0.982 against
+//   1.527); k = 2, 64 levels, persistent (FP64, 2^20: 0.387 against 0.620).
+SdcShape sdc_shape(int prec, int k, int64_t nsdc)
+{
+    const bool wide64 = prec == ge::kFP64 && k == 16;
+    const int64_t simds = 1024;
+    if (nsdc <= 64)
+        return {1, 20, false};            // one window, all levels
+    const int w0 = k == 2 ? 2 : 1, d0 = k == 2 ? 64 : 32;
+    if (sdc_launch_waves(nsdc, k, w0, d0) <= simds)
+        return {w0, d0, true};
+    if (sdc_launch_waves(nsdc, k, 4, 64) <= (wide64 ? 2 : 4) * simds)
+        return {4, 64, true};
+    if (sdc_fills_wide(prec, k, nsdc, 0)) {
+        const int wide = wide64 ? 4 : 8;
+        return {wide, sdc_default_depth(prec, k, wide), wide64};
+    }
+    return k == 2 ? SdcShape{8, 64, true} : SdcShape{8, 96, false};
+}
+
+// The same where the caller gives some of the three.  The persistent form
+// is the library's own choice there for FP64 with k = 16 alone (one couple
+// fills 32 FP64 registers per node pair: two waves per SIMD leave a
+// per-tile launch's loads exposed).
+SdcShape sdc_shape_given(const ge_desc *d, int k, int64_t nsdc)
+{
+    const int prec = d->precision;
+    const bool wide64 = prec == ge::kFP64 && k == 16;
+    const bool pers = d->schedule == 2 || (d->schedule == 0 && wide64);
+    int waves = d->waves;
+    if (waves == 0)
+        waves = sdc_fills_wide(prec, k, nsdc, d->depth) ? (wide64 ? 4 : 8) : 1;
+    int depth = d->depth;
+    if (depth == 0) {
+        depth = sdc_default_depth(prec, k, waves);
+        // single-wave per-tile launches keep 20 levels (24 is the persistent one's)
+        if (waves == 1 && !pers) depth = 20;
+    }
+    return {waves, depth, pers};
 }
 
 ge_status plan_sdc(ge_plan_t *out, const ge_desc *d)
@@ -359,15 +414,10 @@ ge_status plan_sdc(ge_plan_t *out, const ge_desc *d)
         return fail(GE_ERR_INVALID, "ge_plan: schedule = %d, need 0, 1 or 2", d->schedule);
     if (d->depth < 0)
         return fail(GE_ERR_INVALID, "ge_plan: depth = %d, need depth >= 1", d->depth);
-    const bool auto_persistent = d->schedule == 0 && sdc_persistent_pays(prec, k);
     const int64_t nsdc = (d->n + 1) / (2 * k);
-    const int waves = d->waves != 0 ? d->waves : sdc_default_waves(prec, k, nsdc, d->depth);
-    int depth = d->depth;
-    if (depth == 0) {
-        depth = sdc_default_depth(prec, k, waves);
-        // single-wave per-tile launches keep 20 levels (24 is the persistent one's)
-        if (waves == 1 && !auto_persistent && d->schedule != 2) depth = 20;
-    }
+    const bool automatic = d->waves == 0 && d->depth == 0 && d->schedule == 0;
+    const SdcShape shape = automatic ? sdc_shape(prec, k, nsdc) : sdc_shape_given(d, k, nsdc);
+    const int waves = shape.waves, depth = shape.depth;
     if (d->schedule == 2 && depth > ge::kSdcMaxLevels)
         return fail(GE_ERR_INVALID,
                     "ge_plan: the persistent sub-domain form takes at most %d levels per launch",
@@ -397,9 +447,9 @@ ge_status plan_sdc(ge_plan_t *out, const ge_desc *d)
     p->halo = single ? 0 : halo;          // in couples
     p->core = single ? nsdc : wsdc - 2 * halo;
     p->ntiles = (nsdc + p->core - 1) / p->core;
-    p->persistent = !single && p->ntiles >= 3 &&
-                    (d->schedule == 2 || (auto_persistent && p->ntiles >= kSdcPersistentMinTiles &&
-                                          depth <= ge::kSdcMaxLevels));
+    // a persistent launch given by the options' defaults wants 64 tiles
+    p->persistent = !single && p->ntiles >= 3 && shape.persistent && depth <= ge::kSdcMaxLevels &&
+                    (automatic || d->schedule == 2 || p->ntiles >= 64);
     const double r = d->r;
     p->h = 1.0 / (double)(p->n + 1);
     p->tau = r * p->h * p->h;
