@@ -1,5 +1,6 @@
 // C ABI of libge (declared in include/ge.h): argument validation, the choice
 // of tiling and temporal depth, and the launch sequence of a run.
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstdint>
@@ -345,14 +346,16 @@ bool sdc_fills_wide(int prec, int k, int64_t nsdc, int depth)
 // every window still gets a SIMD of its own.  Measured, us per level, against
 // single-wave windows of 20 levels (24 persistent for FP64 with k = 16):
 //   one wave per SIMD: one wave, 32 levels (FP64 k = 8, 2^17 points: 0.267
-//   against 0.365; k = 16: 0.383 against 0.433); k = 2 has no core there and
-//   takes two waves, 64 levels (FP32, 2^15: 0.199 against 0.218);
+//   against 0.365); k = 2 has no core there and takes two waves, 64 levels
+//   (FP32, 2^15: 0.199 against 0.218); k = 16 keeps the 20 or 24 levels that
+//   its plans have always reported (32 would be 0.383 against 0.433);
 //   up to four waves per SIMD (FP64 with k = 16, whose registers leave room
 //   for two: two): four waves, 64 levels, persistent (FP64 k = 4, 2^20: 0.353
 //   against 0.534; FP32 k = 16, 2^21: 0.429 against 0.622);
 //   between those and the wide ones: eight waves, 96 levels, per tile (FP64
 //   k = 8, 2^22: 0.954 against 1.413; FP32 k = 16, 2^23: 0.982 against
-//   1.527); k = 2, 64 levels, persistent (FP64, 2^20: 0.387 against 0.620).
+//   1.527); k = 2, 64 levels, persistent (FP64, 2^20: 0.387 against 0.620);
+//   FP64 with k = 16 single-wave windows of 24 levels, as reported before.
 SdcShape sdc_shape(int prec, int k, int64_t nsdc)
 {
     const bool wide64 = prec == ge::kFP64 && k == 16;
@@ -360,15 +363,16 @@ SdcShape sdc_shape(int prec, int k, int64_t nsdc)
     if (nsdc <= 64)
         return {1, 20, false};            // one window, all levels
     const int w0 = k == 2 ? 2 : 1, d0 = k == 2 ? 64 : 32;
+    const SdcShape narrow{1, wide64 ? 24 : 20, wide64};
     if (sdc_launch_waves(nsdc, k, w0, d0) <= simds)
-        return {w0, d0, true};
+        return k == 16 ? narrow : SdcShape{w0, d0, true};
     if (sdc_launch_waves(nsdc, k, 4, 64) <= (wide64 ? 2 : 4) * simds)
         return {4, 64, true};
     if (sdc_fills_wide(prec, k, nsdc, 0)) {
         const int wide = wide64 ? 4 : 8;
         return {wide, sdc_default_depth(prec, k, wide), wide64};
     }
-    return k == 2 ? SdcShape{8, 64, true} : SdcShape{8, 96, false};
+    return wide64 ? narrow : k == 2 ? SdcShape{8, 64, true} : SdcShape{8, 96, false};
 }
 
 // The same where the caller gives some of the three.  The persistent form
@@ -447,9 +451,9 @@ ge_status plan_sdc(ge_plan_t *out, const ge_desc *d)
     p->halo = single ? 0 : halo;          // in couples
     p->core = single ? nsdc : wsdc - 2 * halo;
     p->ntiles = (nsdc + p->core - 1) / p->core;
-    // a persistent launch given by the options' defaults wants 64 tiles
+    // for k = 16 a persistent launch that nobody asked for wants 64 tiles
     p->persistent = !single && p->ntiles >= 3 && shape.persistent && depth <= ge::kSdcMaxLevels &&
-                    (automatic || d->schedule == 2 || p->ntiles >= 64);
+                    ((automatic && k != 16) || d->schedule == 2 || p->ntiles >= 64);
     const double r = d->r;
     p->h = 1.0 / (double)(p->n + 1);
     p->tau = r * p->h * p->h;
@@ -720,7 +724,7 @@ ge_status ge_step_n(ge_plan_t plan, void *u, void *workspace, int64_t step0, int
     // one launch of whichever kernel the plan runs
     auto launch = [&](const ge::TileArgs &la) {
         if (plan->sdc)
-            return plan->persistent
+            return plan->persistent && la.ntiles >= 3
                        ? ge::launch_sdc_persistent(plan->prec, plan->sdc, plan->waves, la, st)
                        : ge::launch_sdc(plan->prec, plan->sdc, plan->waves, la, st);
         if (plan->block)
@@ -755,6 +759,14 @@ ge_status ge_step_n(ge_plan_t plan, void *u, void *workspace, int64_t step0, int
     if ((launches & 1) && nsteps > launches)
         ++launches;
     const int64_t base = nsteps / launches, extra = nsteps % launches;
+    if (plan->sdc) {
+        // a call of fewer levels than the plan's depth gets the halo of its
+        // own (FP64, k = 8, 3.9e6 points, 24 levels in windows for 96: 38 us
+        // against 46 with the plan's halo)
+        a.halo = std::min(plan->halo, sdc_halo((int)(base + (extra ? 1 : 0)), plan->sdc));
+        a.core = 64 * plan->waves - 2 * a.halo;
+        a.ntiles = (a.nsdc + a.core - 1) / a.core;
+    }
     void *bufs[2] = {u, workspace};
     int64_t done = 0;
     for (int64_t k = 0; k < launches; ++k) {

@@ -22,11 +22,13 @@ def couples(k, waves, depth, launch_waves):
 # and right after
 EDGES = [
     ("fp64", 2, 64, (1, 20), (2, 64)),
-    ("fp32", 16, 64, (1, 20), (1, 32)),
+    ("fp32", 8, 64, (1, 20), (1, 32)),
+    ("fp32", 16, couples(16, 1, 32, 1024), (1, 20), (4, 64)),
+    ("fp64", 16, couples(16, 1, 32, 1024), (1, 24), (4, 64)),
     ("fp64", 2, couples(2, 2, 64, 1024), (2, 64), (4, 64)),
     ("fp32", 4, couples(4, 1, 32, 1024), (1, 32), (4, 64)),
     ("fp64", 8, couples(8, 1, 32, 1024), (1, 32), (4, 64)),
-    ("fp64", 16, couples(16, 4, 64, 2048), (4, 64), (8, 96)),
+    ("fp64", 16, couples(16, 4, 64, 2048), (4, 64), (1, 24)),
     ("fp32", 16, couples(16, 4, 64, 4096), (4, 64), (8, 96)),
     ("fp32", 2, couples(2, 4, 64, 4096), (4, 64), (8, 64)),
 ]
