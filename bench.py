@@ -63,11 +63,14 @@ VALU_LANE_OPS_BY_PREC = {"fp64": VALU_LANE_OPS, "fp32": 2 * VALU_LANE_OPS,
 # differences (2), u + c1 D_i + c2 D_q (two FMAs, 4); a source adds one FMA
 # a(t) B_i, B_i = e1 b_i + e2 b_q being fixed by the profile (2).  The pair
 # takes both differences for s and e and sums them (5), the increment (mul +
-# fma, 3), and Kahan's add (4).  VALU_PER_UPDATE: the fewest instructions the
-# form can be written in, the basis of the labelled instruction floor.
+# fma, 3), and Kahan's add (4).  VALU_PER_UPDATE: the instructions the kernels'
+# form takes, the basis of the labelled instruction floor: FP64 in two stages
+# 3 (the explicit right-hand side over the other parity's pairs, half the
+# difference and one FMA a point; the 2 x 2 solve likewise), FP32 4 (the two
+# differences and u + c1 (D_i + cs D_q) in two FMAs).
 FLOPS_PER_UPDATE = {"fp64": 6, "fp32": 6, "fp32c": 12}
 FLOPS_SRC = 2
-VALU_PER_UPDATE = {"fp64": 4, "fp32": 5, "fp32c": 11}
+VALU_PER_UPDATE = {"fp64": 3, "fp32": 4, "fp32c": 11}
 VALU_SRC = 1
 BYTES_PER_POINT = {"fp64": 8, "fp32": 4, "fp32c": 8}
 PROFILE_TRAFFIC = os.path.join(ROOT, "profiles", "moving_wall_c5_fp64_traffic.md")
@@ -286,11 +289,11 @@ def paper_e2_table(torch, stream, ge, inputs):
     return out
 
 
-def grid2d_extra(torch, stream, ge, inputs, nx=4096, ny=4096, levels=200, depth=4):
+def grid2d_extra(torch, stream, ge, inputs, nx=4096, ny=4096, levels=200, depth=0):
     """The 2D extension on an nx x ny grid (u0 = sine rod profiles in x times
-    a sine in y, seed 2), `depth` levels per launch (the library's choice):
-    updates/s and the kernel against HBM bandwidth (one read and one write of
-    the grid per launch)."""
+    a sine in y, seed 2), depth 0 = the library's choice of levels per launch:
+    updates/s and the algorithmic flops (6 per direction) against the FP64
+    vector peak."""
     fx = inputs.sine_rod(nx, seed=2)
     y = np.arange(1, ny + 1) / (ny + 1)
     u = torch.from_numpy(np.outer(np.sin(np.pi * y), fx)).cuda()
@@ -300,14 +303,12 @@ def grid2d_extra(torch, stream, ge, inputs, nx=4096, ny=4096, levels=200, depth=
         _, g = time_runs(torch, stream, lambda: ge.step2d_n(u, nx, ny, 2.0, 2.0, 0, levels,
                                                             workspace=ws, stream=stream,
                                                             depth=depth), 1, 3)
-    per_launch = g / (3 * levels / depth)
-    gbs = 16 * nx * ny / per_launch / 1e9
-    return {"updates_per_s": nx * ny * levels * 3 / g, "nx": nx, "ny": ny, "levels": levels,
-            "depth": depth,
-            "roofline": {"bound": "hbm", "achieved": round(gbs, 1), "peak": HBM_PEAK_GBS,
-                         "unit": "GB/s", "frac": round(gbs / HBM_PEAK_GBS, 4),
-                         "basis": "16 B per point and launch (FP64 read + write), "
-                                  f"{depth} levels per launch"}}
+    ups = nx * ny * levels * 3 / g
+    return {"updates_per_s": ups, "nx": nx, "ny": ny, "levels": levels, "depth": depth,
+            "roofline": {"bound": "alu", "achieved": round(ups * 12 / 1e12, 2),
+                         "peak": PEAK_TF["fp64"], "unit": "TFLOP/s",
+                         "frac": round(ups * 12 / 1e12 / PEAK_TF["fp64"], 4),
+                         "basis": "12 flops per point and level (6 per direction)"}}
 
 
 def surrogate_extra(torch, stream, train_steps, nrods=4096, width=4096, ntraj=200_000):
@@ -401,8 +402,9 @@ def kernel_name(prec, cfg, src):
     form = "comp" if prec == "fp32c" else "plain"
     if cfg["schedule"] == 2:
         return f"tile_persistent_kernel<{t},{cfg['tile']},{form},{'src' if src else 'nosrc'}>"
-    return (f"tile_kernel<{t},{cfg['tile']},{cfg['waves']},{form},{'src' if src else 'nosrc'},"
-            "interior>")
+    part = ",interior" if prec == "fp32c" else ""
+    return (f"tile_kernel<{t},{cfg['tile']},{cfg['waves']},{form},{'src' if src else 'nosrc'}"
+            f"{part}>")
 
 
 def roofline_of(prec, cfg, n, levels, steps, gpu_s, src, traffic=None):
@@ -429,15 +431,15 @@ def roofline_of(prec, cfg, n, levels, steps, gpu_s, src, traffic=None):
         "frac": round(ach / PEAK_TF[prec], 4), "traffic": traffic,
         "kernel": kernel_name(prec, cfg, src), "depth": cfg["depth"], "launches": nl,
         "avg_launch_us": round(kernel_s * 1e6, 2),
-        "avg_launch_basis": "per block of levels: the interior-tile kernel, the wall-tile "
-                            "kernel (beside it on a second stream for rods of many tiles, "
-                            "else before it) and the gaps (HIP events)",
+        "avg_launch_basis": "per block of levels: the tile kernel (for the pair the "
+                            "interior tiles' and, beside it, the wall tiles') and the gaps "
+                            "(HIP events)",
         "flops_per_update": fpu,
         "algorithmic_flops_per_launch": flops,
         "issue_floor": {"peak": round(floor, 2), "frac": round(ach / floor, 4),
                         "basis": f"VALU issue {VALU_LANE_OPS_BY_PREC[prec]:.3g} lane-ops/s x "
-                                 f"{fpu} flops / {vpu} VALU instructions per update (the "
-                                 "fewest the form can be written in)"},
+                                 f"{fpu} flops / {vpu} VALU instructions per update (what the "
+                                 "kernel's form takes)"},
         "hbm": {"algorithmic_bytes_per_launch": hbm, "gbs": round(gbs, 1),
                 "frac": round(gbs / HBM_PEAK_GBS, 4)},
     }
