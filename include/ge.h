@@ -99,9 +99,9 @@ typedef struct {
     int32_t depth;      /* levels fused per launch (>= 1; 0 = library choice) */
     int32_t waves;      /* waves per workgroup (1 or 4, with k >= 2 also 2    */
                         /* and 8; 0 = library choice).  With tile, depth,     */
-                        /* waves and schedule all 0, FP64 and FP32 rods of    */
-                        /* 256 to 768000 points run in windows of 4 or 8      */
-                        /* overlapping waves at a depth of their own.         */
+                        /* waves and schedule all 0, rods of 256 to 768000    */
+                        /* points (GE_FP32_COMP: 900000) run in windows of 4  */
+                        /* or 8 overlapping waves at a depth of their own.    */
     double g_left;      /* wall value g_L, used when a call gives no array    */
     double g_right;     /* wall value g_R, likewise                           */
     const void *src_b;  /* device, n values of the state's element type       */

@@ -181,6 +181,12 @@ struct BlockShape {
 };
 constexpr BlockShape kBlockShapes[] = {{4, 4, 0.087}, {6, 4, 0.101}, {8, 4, 0.115}, {10, 4, 0.13},
                                        {8, 8, 0.155}};
+// The pair, whose level is four times the instructions: 960 levels of 800
+// points 174 us (669 in tiles), of 131071 points 196 (533), of 262655 235
+// (576), of 760000 415 (966).  Up to 4096 points in one window, as ever.
+constexpr BlockShape kPairShapes[] = {{4, 4, 0.18}, {6, 4, 0.21}, {8, 4, 0.255}, {10, 4, 0.29},
+                                      {8, 8, 0.40}};
+constexpr int64_t kPairMax = 900000, kPairOneWindow = 4096;
 constexpr double kBlockLaunchUs = 6.0;
 constexpr int64_t kBlockMin = 256, kBlockOneWindow = 2048, kBlockMax = 768000;
 constexpr int64_t kComputeUnits = 256;
@@ -192,14 +198,16 @@ struct BlockChoice {
 
 bool block_choice(int prec, int64_t n, BlockChoice *out)
 {
-    if (prec == ge::kFP32C || n < kBlockMin || n > kBlockMax)
+    const bool pair = prec == ge::kFP32C;
+    const int64_t one_window = pair ? kPairOneWindow : kBlockOneWindow;
+    if (n < kBlockMin || n > (pair ? kPairMax : kBlockMax))
         return false;
     double best = 1e300;
-    for (const BlockShape &s : kBlockShapes) {
+    for (const BlockShape &s : pair ? kPairShapes : kBlockShapes) {
         const int64_t cap = ge::block_capacity(s.k, s.waves);
         if (n < 64 * s.k)
             continue;
-        if (n <= kBlockOneWindow) {
+        if (n <= one_window) {
             if (n > cap)
                 continue;
             *out = BlockChoice{s.k, s.waves, 1 << 16, 0, n};
@@ -223,14 +231,12 @@ bool block_choice(int prec, int64_t n, BlockChoice *out)
 // times over, so that it has enough waves (960 levels: 2e6 points FP64 20
 // points a lane 341 us, 32 points 480; FP32 16 points 374, 32 points 513; 6e6
 // points FP64 28 points 736 against 779, FP32 16 points at 64 levels 747
-// against 830; the pair at 262655 points 4 points a lane, one wave, 556
-// against 1212 with 16 points and four waves, at 6e6 8 points 2093 against
-// 2339).  A pair of up to 4096 points stays in one window.
+// against 830; the pair at 6e6 8 points a lane 2093 against 2339).  A pair of
+// up to 4096 points stays in one window.
 Choice default_for_length(int prec, int64_t n, bool src)
 {
     if (prec == ge::kFP32C) {
-        if (n <= 4096) return {n <= 1024 ? 4 : n <= 2048 ? 8 : 16, 4, 128};
-        if (n < 600000) return {4, 1, 48};
+        if (n <= kPairOneWindow) return {n < kBlockMin ? 4 : 16, 4, 128};
         if (n < 12000000) return {8, 4, 96};
     } else if (n < kBlockMin) {
         return {4, 1, 48};

@@ -1,5 +1,5 @@
-// A window of overlapping waves (FP64, FP32), shared by the single-rod kernel
-// (ge_block.hip) and the batch kernels (ge_batch_windows.hip).
+// A window of overlapping waves, shared by the single-rod kernel (ge_block.hip)
+// and, for FP64 and FP32, the batch kernels (ge_batch_windows.hip).
 //
 // The waves of a window overlap by 2 h points (h = kBlockOverlap) and advance
 // h - 1 levels on their own, each with open edges, before they refresh what
@@ -140,9 +140,123 @@ __device__ __forceinline__ void block_wave(const TileArgs &a, const BlockShape &
     raise_if_nonfinite(a.status, fin);
 }
 
+// A value of a given lane, in every lane.
+__device__ __forceinline__ double value_of_lane(double v, int lane)
+{
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_readlane((int)(b & 0xffffffffll), lane);
+    const int hi = __builtin_amdgcn_readlane((int)(b >> 32), lane);
+    return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+
+// The same for the compensated pair: s and e, each with its own half of the
+// buffers.  The walls' FP64 values between two refreshes are held one a lane.
+template <int K, bool SRC, bool LEFT, bool RIGHT>
+__device__ __forceinline__ void block_wave_pair(const TileArgs &a, const BlockShape &sh,
+                                                int64_t p0, int64_t own_lo, int64_t own_hi,
+                                                float *buf, int stride)
+{
+    using T = float;
+    constexpr bool WALL = LEFT || RIGHT;
+    constexpr int W = kWave * K, H = kBlockOverlap;
+    static_assert(H <= kWave, "a refresh's wall values fit one register");
+    const int lane = threadIdx.x & (kWave - 1);
+    const int64_t g0 = p0 + lane * K;
+    const T *in = static_cast<const T *>(a.in);
+    T *out = static_cast<T *>(a.out);
+    T s[K], e[K], b[K];
+    load_lane<T, K>(in + g0, s);
+    load_lane<T, K>(in + a.estride + g0, e);
+    if constexpr (SRC) load_lane<T, K>(static_cast<const T *>(a.src_b) + g0, b);
+    T bl = T(0), br = T(0);
+    if constexpr (SRC) {
+        bl = from_left(T(0), b[K - 1]);
+        br = from_right(T(0), b[0]);
+    }
+    const bool lane_l = LEFT && lane == 0, lane_r = RIGHT && lane == kWave - 1;
+    const bool own_L = lane_l && a.flux && sh.core_lo == 0;
+    const bool own_R = lane_r && a.flux && sh.core_hi == a.n;
+    double acc_r = own_R ? a.flux[1] : 0.0;
+    FluxTap ft{own_L, own_L ? a.flux[0] : 0.0, a.tau, a.h, 0.0};
+    const PairCoef<T> cf =
+        lane_coef(PairCoef<T>{(T)a.c1, (T)a.c2, (T)a.cs, (T)a.e1, (T)a.e2, (T)a.es});
+    const int par0 = (int)((a.level0 + p0) & 1);   // the first level's parity in the window
+    double an = SRC ? a.src_a[0] : 0.0;
+
+    int done = 0;
+    for (int blk = 0;; ++blk) {
+        const int nb = min(a.nlev - done, H - 1);
+        double wl = a.gl0, wr = a.gr0;             // lane l: level done + l
+        if (LEFT && a.gl_t) wl = a.gl_t[min(done + lane, a.nlev)];
+        if (RIGHT && a.gr_t) wr = a.gr_t[min(done + lane, a.nlev)];
+        for_levels(par0 + done, nb, [&](auto par, int lev) {
+            constexpr int P = decltype(par)::value;
+            T xl = T(0), yl = T(0), xr = T(0), yr = T(0), dgr = T(0);
+            double grn = 0.0;
+            WallLevel<T> wlv{false, T(0)};
+            if constexpr (LEFT) {
+                const double glo = value_of_lane(wl, lev), gln = value_of_lane(wl, lev + 1);
+                split_wall<T, true>(glo, xl, yl);
+                wlv.dgl = (T)(gln - glo);
+                wlv.isL = P == 1 && lane_l;
+                ft.gln = gln;
+            }
+            if constexpr (RIGHT) {
+                const double gro = value_of_lane(wr, lev);
+                grn = value_of_lane(wr, lev + 1);
+                split_wall<T, true>(gro, xr, yr);
+                dgr = (T)(grn - gro);
+            }
+            // the window ends at the wall: its last point is alone at parity 1
+            Lone<T> lone{T(0), T(0)};
+            if constexpr (RIGHT && P == 1)
+                lone = right_lone<T, K, SRC>(s, e, b, K - 1, T(0), T(0), xr, yr, dgr, cf, (T)an);
+            pair_level<T, K, SRC ? 1 : 0, WALL, P, !WALL>(s, e, b, bl, br, xl, T(0), xr, T(0), yl,
+                                                          T(0), yr, T(0), cf, (T)an, wlv, ft);
+            if constexpr (RIGHT && P == 1) {
+                s[K - 1] = lane_r ? lone.s : s[K - 1];
+                e[K - 1] = lane_r ? lone.e : e[K - 1];
+            }
+            if constexpr (SRC) an = a.src_a[min(done + lev + 1, a.nlev - 1)];
+            if (RIGHT && own_R)
+                acc_r = acc_r + a.tau * (((double)s[K - 1] + (double)e[K - 1]) - grn) / a.h;
+        });
+        done += nb;
+        if (done >= a.nlev)
+            break;
+        T *x = buf + (blk & 1) * 2 * stride;
+#pragma unroll
+        for (int j = 0; j < K; ++j)
+            if (g0 + j >= own_lo && g0 + j < own_hi) {
+                x[g0 + j - sh.lo] = s[j];
+                x[stride + g0 + j - sh.lo] = e[j];
+            }
+        __syncthreads();
+        if (lane * K < H || (lane + 1) * K > W - H) {
+#pragma unroll
+            for (int j = 0; j < K; ++j) {
+                s[j] = x[g0 + j - sh.lo];
+                e[j] = x[stride + g0 + j - sh.lo];
+            }
+        }
+    }
+    if (own_L) a.flux[0] = ft.accL;
+    if (own_R) a.flux[1] = acc_r;
+
+    // every load in before any store, as in block_wave
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    T fin = T(0);
+    const int64_t lo = max(own_lo, sh.core_lo), hi = min(own_hi, sh.core_hi);
+    store_lane_guarded<T, K>(out + g0, g0, lo, hi, s, fin);
+    store_lane_guarded<T, K>(out + a.estride_out + g0, g0, lo, hi, e, fin);
+    raise_if_nonfinite(a.status, fin);
+}
+
 // The whole workgroup: window t of the rod, advanced a.nlev levels.  buf: two
-// buffers of `stride` values, at least the window's points each.
-template <typename T, int K, bool SRC>
+// buffers of `stride` values (for the pair twice that), at least the window's
+// points each.
+template <typename T, int K, bool SRC, bool PAIR = false>
 __device__ __forceinline__ void block_window(const TileArgs &a, int64_t t, T *buf, int stride)
 {
     constexpr int W = kWave * K, STEP = W - 2 * kBlockOverlap;
@@ -162,6 +276,13 @@ __device__ __forceinline__ void block_window(const TileArgs &a, int64_t t, T *bu
     const int64_t own_lo = w == 0 ? sh.lo : p0 + kBlockOverlap;
     const int64_t own_hi = is_last ? sh.hi : next + kBlockOverlap;
     const bool left = p0 == 0, right = p0 + W == a.n;
+    if constexpr (PAIR) {
+        if (left && right) block_wave_pair<K, SRC, true, true>(a, sh, p0, own_lo, own_hi, buf, stride);
+        else if (left) block_wave_pair<K, SRC, true, false>(a, sh, p0, own_lo, own_hi, buf, stride);
+        else if (right) block_wave_pair<K, SRC, false, true>(a, sh, p0, own_lo, own_hi, buf, stride);
+        else block_wave_pair<K, SRC, false, false>(a, sh, p0, own_lo, own_hi, buf, stride);
+        return;
+    }
     if (left && right) block_wave<T, K, SRC, true, true>(a, sh, p0, own_lo, own_hi, buf, stride);
     else if (left) block_wave<T, K, SRC, true, false>(a, sh, p0, own_lo, own_hi, buf, stride);
     else if (right) block_wave<T, K, SRC, false, true>(a, sh, p0, own_lo, own_hi, buf, stride);

@@ -63,8 +63,8 @@ struct SideStream {
 hipError_t launch_tiles(int prec, int k, int nw, bool src, const TileArgs &a,
                         hipStream_t stream, const SideStream *side = nullptr);
 
-// Windows of nw overlapping waves of 64 k points (block_kernel, FP64 and
-// FP32): core and halo of `a` count points, every window holds at most
+// Windows of nw overlapping waves of 64 k points (block_kernel: FP64,
+// FP32 and the pair): core and halo of `a` count points, every window holds at most
 // block_capacity points, and n >= 64 k.
 constexpr int kBlockOverlap = 24;   // half the points neighbouring waves share
 constexpr int block_capacity(int k, int nw)
