@@ -247,9 +247,9 @@ ge_status ge_2d_step_n(const ge_2d_desc *desc, void *u, void *workspace, int64_t
 /* ------------------------------------------------------------------------
  * Batch of independent rods: the same scheme (Section 2) for every rod, each
  * rod with its own n, r and constant wall values, all advanced by the same
- * levels: in one persistent launch that a hipGraph captures (the pair, sync
- * other than 0, ge_solve_batch_static), or split into windows over the whole
- * chip (ge_solve_batch in FP64 and FP32 with sync = 0).  Same bits either way.
+ * levels: split into windows over the whole chip (ge_solve_batch with sync =
+ * 0), or in one persistent launch that a hipGraph captures (sync other than 0,
+ * ge_solve_batch_static).  Same bits either way.
  *
  * Layout of the packed state u: rod i occupies elements
  * offsets[i] .. offsets[i] + n[i] - 1 (double for GE_FP64, float for the two
@@ -284,13 +284,13 @@ typedef struct {
                              /* ~/.cache/libge/batch_tune.txt); 0: use the    */
                              /* stored measurement, or built-in defaults      */
     int32_t sync;            /* how the waves of a rod exchange edge values:  */
-                             /* 0 = library choice (FP64 and FP32: windows;   */
-                             /* the pair: 3), 1 = every level, at a     */
-                             /* workgroup barrier, 2 = every level, each wave */
+                             /* 0 = library choice (windows), 1 = every level,*/
+                             /* at a workgroup barrier, 2 = each level, a wave*/
                              /* waiting for its two neighbours only (level    */
                              /* flags in LDS), 3 = neighbouring waves overlap */
                              /* by a lane or more, refreshed at a barrier     */
-                             /* every K-1 levels (the default; rods of one    */
+                             /* every K-1 levels (also the static call's */
+                             /* form of a plan with sync = 0; rods of one     */
                              /* wave and rods whose overlapping waves do not  */
                              /* fit a workgroup use 2 in the same launch)     */
 } ge_batch_desc;

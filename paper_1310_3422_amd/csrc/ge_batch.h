@@ -111,6 +111,7 @@ struct BatchWinArgs {
     int32_t count, nlev, pass;
     int32_t core, halo;       // of a pass's windows; core = 0: whole rods, in place
     int *status;
+    int64_t estride, estride2;   // FP32C: element offsets of the e blocks in u, u2
 };
 // kWinTiny: rods below kBatchTiny points, one wave each; kWinBlock: windows of
 // kBatchBlockWaves overlapping waves, all of one launch with at most

@@ -302,6 +302,7 @@ struct Windows {
 // One level of a window of four overlapping waves, us, per shape (k = 4, 6, 8,
 // 12, 18), and the fixed cost of a launch: as for single rods (ge_api.hip).
 constexpr double kWinLevelUs[ge::kBatchBlockShapes] = {0.087, 0.101, 0.115, 0.145, 0.19};
+constexpr double kPairWinLevelUs[ge::kBatchBlockShapes] = {0.18, 0.21, 0.255, 0.33, 0.45};
 constexpr double kWinLaunchUs = 6.0;
 
 // The longer rods' points decide how they are cut, as a single rod's length
@@ -353,7 +354,8 @@ Windows make_windows(const std::vector<int64_t> &n, int prec, int units)
             for (int s = 0; s < ge::kBatchBlockShapes; ++s) {
                 const int64_t halo = (cap(s) - core) / 4 * 2;
                 if (halo < 65) continue;
-                const double us = kWinLevelUs[s] + kWinLaunchUs / (halo - 1);
+                const double us = (prec == ge::kFP32C ? kPairWinLevelUs : kWinLevelUs)[s] +
+                                  kWinLaunchUs / (halo - 1);
                 if (us < best) {
                     best = us;
                     w.k = ge::kBatchBlockKs[s];
@@ -364,8 +366,9 @@ Windows make_windows(const std::vector<int64_t> &n, int prec, int units)
             w.depth = w.halo - 1;
         } else {
             w.kind = ge::kWinWave;
-            w.k = points < kWinWideMin ? 16 : 32;
-            w.depth = points < kWinWideMin ? 64 : 96;
+            const bool narrow = points < kWinWideMin || prec == ge::kFP32C;
+            w.k = narrow ? 16 : 32;
+            w.depth = narrow ? 64 : 96;
             const int align = prec == ge::kFP64 ? 2 : 4;
             w.halo = (w.depth + 1 + align - 1) / align * align;
             w.core = 64 * w.k - 2 * w.halo;
@@ -380,7 +383,7 @@ Windows make_windows(const std::vector<int64_t> &n, int prec, int units)
         }
     }
     // a level at the chip's rate, or one window's latency
-    w.est_us = std::max(0.1, (double)all / (prec == ge::kFP64 ? 8.0e6 : 9.0e6));
+    w.est_us = std::max(0.1, (double)all / (prec == ge::kFP64 ? 8.0e6 : prec == ge::kFP32 ? 9.0e6 : 3.3e6));
     return w;
 }
 
@@ -712,9 +715,9 @@ ge_status ge_batch_plan(ge_batch_t *out, const ge_batch_desc *d)
     b->est_us = P.est_us;
     b->has_long = P.has_long;
     b->wait_polls = kDefaultWaitPolls;
-    // the library's choice in FP64 and FP32: windows (the persistent form then
+    // the library's choice: windows (the persistent form then
     // serves ge_solve_batch_static, which has no room for second buffers)
-    if (d->sync == 0 && prec != ge::kFP32C) {
+    if (d->sync == 0) {
         b->win = make_windows(b->n, prec, b->grid);
         b->rod_k = b->win.rod_k;
         b->est_us = b->win.est_us;
@@ -839,6 +842,8 @@ hipError_t run_windows(ge_batch_s *b, void *u, void *work, int parity, int64_t n
     a.level0 = parity;
     a.nlev = (int32_t)nsteps;
     a.status = b->status.dev;
+    a.estride = b->estride;
+    a.estride2 = w.elems;
     // what runs on the side branch, and what before the passes
     const int whole = w.nwide + w.nnarrow + w.ntiny;
     const bool beside = w.npass > 0 ? whole > 0 : w.nwide > 0 && w.nnarrow + w.ntiny > 0;

@@ -1,4 +1,4 @@
-// A batch of rods in windows (FP64, FP32): every rod is split into as many
+// A batch of rods in windows: every rod is split into as many
 // workgroups or waves as it is worth, so no compute unit waits for another's
 // long rod and no rod's waves wait at the barriers of a stranger's.  (In the
 // persistent form of ge_batch.hip a rod is one workgroup's: 149 FP32 rods of up
@@ -20,7 +20,9 @@
 // updates/s; VALU issue binds, 4 instructions a point and the halos' recompute;
 // 12.6 in the persistent form); 1024 FP64 rods of 4096 points, 64 levels, 40 us
 // (120); the 149 rods above, 41 levels, 50 us (135); 768 FP32 rods of 1565
-// points, 715 levels, 138 us (1074).
+// points, 715 levels, 138 us (1074).  The compensated pair: 4096 rods of 256
+// to 65536 points, 200 levels, 3.22 ms (3.46); 300 of 1000 to 4000, 300
+// levels, 185 us (1043); 51 of 535 to 16585, 26 levels, 70 us (199).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -56,6 +58,8 @@ __device__ __forceinline__ TileArgs rod_args(const BatchWinArgs &a, const BatchR
     ta.gr0 = rd.gr;
     ta.h = 1.0;
     ta.status = a.status;
+    ta.estride = in == out || !(a.pass & 1) ? a.estride : a.estride2;
+    ta.estride_out = in == out || (a.pass & 1) ? a.estride : a.estride2;
     return ta;
 }
 
@@ -66,7 +70,7 @@ __device__ __forceinline__ int xcd_order(int waves)
     return b * waves + (waves > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x / kWave) : 0);
 }
 
-template <typename T>
+template <typename T, bool PAIR>
 __global__ __launch_bounds__(kPerGroup *kWave) void tiny_kernel(BatchWinArgs a)
 {
     const int i = xcd_order(kPerGroup);
@@ -77,18 +81,19 @@ __global__ __launch_bounds__(kPerGroup *kWave) void tiny_kernel(BatchWinArgs a)
     TileArgs ta = rod_args(a, rd, u, u);
     ta.core = rd.n;
     ta.ntiles = 1;
-    run_plain<T, 4, 1, false, kInside>(ta, threadIdx.x & (kWave - 1), 0, 0);
+    if constexpr (PAIR) run_pair<T, 4, 1, false, true>(ta, threadIdx.x & (kWave - 1), 0, 0);
+    else run_plain<T, 4, 1, false, kInside>(ta, threadIdx.x & (kWave - 1), 0, 0);
 }
 
 // Windows of four overlapping waves: whole rods in place (a.core = 0), or
 // windows of a pass.  Narrow (up to 8 points a lane) and wide ones are kernels
 // of their own: the wide ones' registers and LDS would halve the others'
 // workgroups per unit.
-template <typename T, bool WIDE>
+template <typename T, bool WIDE, bool PAIR>
 __global__ __launch_bounds__(kBatchBlockWaves *kWave) void block_windows_kernel(BatchWinArgs a)
 {
     constexpr int CAP = block_capacity(WIDE ? 18 : kBatchNarrowK, kBatchBlockWaves);
-    __shared__ T buf[2 * CAP];
+    __shared__ T buf[(PAIR ? 4 : 2) * CAP];
     const int i = xcd_order(1);
     if (i >= a.count)
         return;
@@ -101,16 +106,16 @@ __global__ __launch_bounds__(kBatchBlockWaves *kWave) void block_windows_kernel(
     ta.halo = a.core == 0 ? 0 : a.halo;
     ta.ntiles = (rd.n + ta.core - 1) / ta.core;
     if constexpr (WIDE) {
-        if (w.k == 12) block_window<T, 12, false>(ta, w.tile, buf, CAP);
-        else if (w.k == 18) block_window<T, 18, false>(ta, w.tile, buf, CAP);
+        if (w.k == 12) block_window<T, 12, false, PAIR>(ta, w.tile, buf, CAP);
+        else if (w.k == 18) block_window<T, 18, false, PAIR>(ta, w.tile, buf, CAP);
     } else {
-        if (w.k == 4) block_window<T, 4, false>(ta, w.tile, buf, CAP);
-        else if (w.k == 6) block_window<T, 6, false>(ta, w.tile, buf, CAP);
-        else if (w.k == 8) block_window<T, 8, false>(ta, w.tile, buf, CAP);
+        if (w.k == 4) block_window<T, 4, false, PAIR>(ta, w.tile, buf, CAP);
+        else if (w.k == 6) block_window<T, 6, false, PAIR>(ta, w.tile, buf, CAP);
+        else if (w.k == 8) block_window<T, 8, false, PAIR>(ta, w.tile, buf, CAP);
     }
 }
 
-template <typename T, int K>
+template <typename T, int K, bool PAIR>
 __global__ __launch_bounds__(kPerGroup *kWave) void wave_windows_kernel(BatchWinArgs a)
 {
     const int i = xcd_order(kPerGroup);
@@ -123,27 +128,27 @@ __global__ __launch_bounds__(kPerGroup *kWave) void wave_windows_kernel(BatchWin
     ta.core = a.core;
     ta.halo = a.halo;
     ta.ntiles = (rd.n + ta.core - 1) / ta.core;
-    run_tile<T, K, 1, false, false>(ta, threadIdx.x & (kWave - 1), w.tile);
+    run_tile<T, K, 1, PAIR, false>(ta, threadIdx.x & (kWave - 1), w.tile);
 }
 
-template <typename T>
+template <typename T, bool PAIR>
 hipError_t launch(BatchWinKind kind, int k, const BatchWinArgs &a, hipStream_t stream)
 {
     const int per = kind == kWinBlock ? 1 : kPerGroup;
     const unsigned groups = (unsigned)((a.count + per - 1) / per);
     const dim3 grid((groups + 7) / 8 * 8), waves(kPerGroup * kWave);
     if (kind == kWinTiny)
-        hipLaunchKernelGGL((tiny_kernel<T>), grid, waves, 0, stream, a);
+        hipLaunchKernelGGL((tiny_kernel<T, PAIR>), grid, waves, 0, stream, a);
     else if (kind == kWinBlock && k <= kBatchNarrowK)
-        hipLaunchKernelGGL((block_windows_kernel<T, false>), grid, dim3(kBatchBlockWaves * kWave), 0,
+        hipLaunchKernelGGL((block_windows_kernel<T, false, PAIR>), grid, dim3(kBatchBlockWaves * kWave), 0,
                            stream, a);
     else if (kind == kWinBlock)
-        hipLaunchKernelGGL((block_windows_kernel<T, true>), grid, dim3(kBatchBlockWaves * kWave), 0,
+        hipLaunchKernelGGL((block_windows_kernel<T, true, PAIR>), grid, dim3(kBatchBlockWaves * kWave), 0,
                            stream, a);
     else if (k == 16)
-        hipLaunchKernelGGL((wave_windows_kernel<T, 16>), grid, waves, 0, stream, a);
-    else if (k == 32)
-        hipLaunchKernelGGL((wave_windows_kernel<T, 32>), grid, waves, 0, stream, a);
+        hipLaunchKernelGGL((wave_windows_kernel<T, 16, PAIR>), grid, waves, 0, stream, a);
+    else if (k == 32 && !PAIR)
+        hipLaunchKernelGGL((wave_windows_kernel<T, PAIR ? 16 : 32, PAIR>), grid, waves, 0, stream, a);
     else
         return hipErrorInvalidValue;
     return hipGetLastError();
@@ -155,8 +160,9 @@ hipError_t launch_batch_windows(int prec, BatchWinKind kind, int k, const BatchW
                                 hipStream_t stream)
 {
     if (a.count < 1) return hipSuccess;
-    if (prec == kFP64) return launch<double>(kind, k, a, stream);
-    if (prec == kFP32) return launch<float>(kind, k, a, stream);
+    if (prec == kFP64) return launch<double, false>(kind, k, a, stream);
+    if (prec == kFP32) return launch<float, false>(kind, k, a, stream);
+    if (prec == kFP32C) return launch<float, true>(kind, k, a, stream);
     return hipErrorInvalidValue;
 }
 

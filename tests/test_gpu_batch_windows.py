@@ -24,7 +24,7 @@ def _batch(sizes, seed):
             rng.uniform(-1, 1, n.size), rng.standard_normal(int(offsets[-1])))
 
 
-@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("precision", ["fp64", "fp32", "fp32c"])
 @pytest.mark.parametrize("name,sizes", [("edges", EDGES), ("small", SMALL), ("large", LARGE),
                                         ("one", [5000]), ("tiny", [7])])
 def test_windows_give_the_bits_of_single_rods(name, sizes, precision):
@@ -49,10 +49,13 @@ def test_windows_give_the_bits_of_single_rods(name, sizes, precision):
         gap = np.ones(got.size, dtype=bool)
         for i in range(n.size):
             gap[offsets[i]:offsets[i] + n[i]] = False
+            if precision == "fp32c":
+                e = int(ge.lib().ge_comp_offset(int(offsets[-1]))) + offsets[i]
+                gap[e:e + n[i]] = False
         np.testing.assert_array_equal(got[gap], start.cpu().numpy()[gap])
 
 
-@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("precision", ["fp64", "fp32", "fp32c"])
 def test_replays_and_two_streams(precision):
     """The captured branches replay with eager work between them, and two runs
     of one plan on two streams, each with its own workspace, do not meet."""
