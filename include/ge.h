@@ -289,7 +289,7 @@ typedef struct {
                              /* waiting for its two neighbours only (level    */
                              /* flags in LDS), 3 = neighbouring waves overlap */
                              /* by a lane or more, refreshed at a barrier     */
-                             /* every K-1 levels (also the static call's */
+                             /* every K-1 levels (also the static call's      */
                              /* form of a plan with sync = 0; rods of one     */
                              /* wave and rods whose overlapping waves do not  */
                              /* fit a workgroup use 2 in the same launch)     */
