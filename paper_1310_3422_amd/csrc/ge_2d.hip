@@ -9,8 +9,8 @@
 //
 // Each direction is taken as ge_level.h takes a rod: in FP64 in two stages, an
 // explicit one over the other parity's pairs, then the 2x2 solve of its own, 3
-// instructions a point; in FP32 as an increment from second differences, 4
-// instructions and one rounding of u.  (FP32 in two stages was faster still,
+// instructions a point; in FP32 as an increment from second differences, 5
+// instructions and one rounding of u.  (FP32 in two stages was faster,
 // 4096 x 4096 points 0.49 ms for 96 levels, but its error against 64 bits was
 // 1.4 times this form's at the median over 40 grids: 1.8e-7 against 1.3e-7.)
 //
@@ -58,7 +58,7 @@ constexpr int kCols = 2 * kWave;      // columns of a window
 constexpr int kNW = 8;                // waves of a window
 
 template <typename T> struct Dir {    // one direction's constants (Coef, ge_level.h)
-    T r, k, c1, cs;
+    T r, k, c1, c2, cs;
 };
 
 template <typename T> struct Block2dArgs {
@@ -93,14 +93,14 @@ template <typename T> constexpr int kEdge = kTwoStage<T> ? 1 : 2;
 template <typename T> constexpr int kRowsAtOnce = 4;
 
 // The factors of a point: of the solve's difference (FP64: f), or of its own
-// second difference and of its partner's inside it (FP32: f, g).
+// second difference and of its partner's (FP32: f, g).
 template <typename T> struct Factor {
     T f, g;
 };
 template <typename T> __device__ __forceinline__ Factor<T> paired(const Dir<T> &c)
 {
     if constexpr (kTwoStage<T>) return Factor<T>{c.k, T(0)};
-    else return Factor<T>{c.c1, c.cs};
+    else return Factor<T>{c.c1, c.c2};
 }
 template <typename T> __device__ __forceinline__ Factor<T> alone(const Dir<T> &c)
 {
@@ -112,9 +112,10 @@ template <typename T> __device__ __forceinline__ Factor<T> pick(bool is_alone, c
     return Factor<T>{is_alone ? l.f : p.f, is_alone ? l.g : p.g};
 }
 // FP32: a point's new value
+// (rounded before it is added, see ge_level.h)
 template <typename T> __device__ __forceinline__ T step(T u, T D, T Dq, Factor<T> k)
 {
-    return dev::fmaT(k.f, dev::fmaT(k.g, Dq, D), u);
+    return u + dev::fmaT(k.g, Dq, k.f * D);
 }
 
 // One lane's view of the x walls.
@@ -418,7 +419,7 @@ __global__ __launch_bounds__(NW *kWave, 4) void block2d_kernel(Block2dArgs<T> a)
 template <typename T> Dir<T> dir(double r)
 {
     return Dir<T>{(T)r, (T)(r / (1.0 + 2.0 * r)), (T)((r + r * r) / (1.0 + 2.0 * r)),
-                  (T)(r / (1.0 + r))};
+                  (T)(r * r / (1.0 + 2.0 * r)), (T)(r / (1.0 + r))};
 }
 
 // Rows per wave and levels per launch: the pair with the least estimated time

@@ -107,12 +107,12 @@ __device__ __forceinline__ void rod_levels(const BatchArgs &a, const BatchRod &r
         // FP64 meets its neighbours with one value a side, FP32 with two
         constexpr bool TWO_STAGE = sizeof(T) == 8;
         constexpr int E = TWO_STAGE ? 1 : 2;
-        const Coef<T> cf = lane_coef(Coef<T>{(T)rd.r, (T)rd.k, (T)rd.c1, (T)rd.cs});
+        const Coef<T> cf = lane_coef(Coef<T>{(T)rd.r, (T)rd.k, (T)rd.c1, (T)rd.c2, (T)rd.cs});
         const bool lane_l = WALL && left_wall && lane == 0;
         const bool lane_r = WALL && ghost_edge && lane == kWave - 1;
         const T kl = lane_l ? cf.cs : cf.k, kr = lane_r ? cf.cs : cf.k;
         const T cl = lane_l ? cf.cs : cf.c1, cr = lane_r ? cf.cs : cf.c1;
-        const T pl = lane_l ? T(0) : cf.cs, pr = lane_r ? T(0) : cf.cs;
+        const T pl = lane_l ? T(0) : cf.c2, pr = lane_r ? T(0) : cf.c2;
         auto exchange = [&](int lev, T (&xl)[E], T (&xr)[E]) {
             const int pb = lev & 1;
             if (!alone) {
@@ -151,7 +151,7 @@ __device__ __forceinline__ void rod_levels(const BatchArgs &a, const BatchRod &r
             } else {
                 exchange(lev, xl, xr);
                 if (WALL && single)
-                    lone = lone_increment<T, K, false>(s, s, T(0), kS, xl[0], gr_hi, cf.cs);
+                    lone = lone_increment<T, K, false>(s, s, T(0), kS, xl[0], gr_hi, cf.cs, T(0));
                 increment_level<T, K, false, P, false, false>(s, s, T(0), xl[0], xl[E - 1], xr[0],
                                                        xr[E - 1], cf, cl, pl, cr, pr);
             }
@@ -296,7 +296,7 @@ __device__ __forceinline__ void rod_block(const BatchRod &rd, T (&s)[K], T (&e)[
     T g, gx;   // the wall's value, and its compensation
     split_wall<T, COMP>(END == 1 ? rd.gl : rd.gr, g, gx);
     if constexpr (!COMP) {
-        const Coef<T> cf = lane_coef(Coef<T>{(T)rd.r, (T)rd.k, (T)rd.c1, (T)rd.cs});
+        const Coef<T> cf = lane_coef(Coef<T>{(T)rd.r, (T)rd.k, (T)rd.c1, (T)rd.c2, (T)rd.cs});
         const bool lane_l = END == 1 && lane == 0, lane_r = END == 2 && lane == kWave - 1;
         if constexpr (sizeof(T) == 8) {
             const T kl = lane_l ? cf.cs : cf.k, kr = lane_r ? cf.cs : cf.k;
@@ -307,7 +307,7 @@ __device__ __forceinline__ void rod_block(const BatchRod &rd, T (&s)[K], T (&e)[
             });
         } else {
             const T cl = lane_l ? cf.cs : cf.c1, cr = lane_r ? cf.cs : cf.c1;
-            const T pl = lane_l ? T(0) : cf.cs, pr = lane_r ? T(0) : cf.cs;
+            const T pl = lane_l ? T(0) : cf.c2, pr = lane_r ? T(0) : cf.c2;
             for_levels(level0, nlev, [&](auto par, int) {
                 increment_level<T, K, false, decltype(par)::value, END != 1, END != 2>(
                     s, s, T(0), g, g, g, g, cf, cl, pl, cr, pr);

@@ -63,10 +63,10 @@ __device__ __forceinline__ void block_wave(const TileArgs &a, const BlockShape &
     const bool own_L = lane_l && a.flux && sh.core_lo == 0;
     const bool own_R = lane_r && a.flux && sh.core_hi == a.n;
     double acc_l = own_L ? a.flux[0] : 0.0, acc_r = own_R ? a.flux[1] : 0.0;
-    const Coef<T> cf = lane_coef(Coef<T>{(T)a.r, (T)a.k, (T)a.c1, (T)a.cs});
+    const Coef<T> cf = lane_coef(Coef<T>{(T)a.r, (T)a.k, (T)a.c1, (T)a.c2, (T)a.cs});
     const T kl = lane_l ? cf.cs : cf.k, kr = lane_r ? cf.cs : cf.k;
     const T cl = lane_l ? cf.cs : cf.c1, cr = lane_r ? cf.cs : cf.c1;
-    const T pl = lane_l ? T(0) : cf.cs, pr = lane_r ? T(0) : cf.cs;
+    const T pl = lane_l ? T(0) : cf.c2, pr = lane_r ? T(0) : cf.c2;
     WallFeed<T> wl, wr;
     const int par0 = (int)((a.level0 + p0) & 1);   // the first level's parity in the window
     double an = SRC ? a.src_a[0] : 0.0;
@@ -74,9 +74,9 @@ __device__ __forceinline__ void block_wave(const TileArgs &a, const BlockShape &
     T B0[KB], B1[KB];
     if constexpr (SRC && !TWO_STAGE) {
         const T bl = from_left(T(0), b[K - 1]), br = from_right(T(0), b[0]);
-        const T f1 = (T)(a.tau / a.r), f2 = (T)(a.tau / (1.0 + a.r));
-        increment_source<T, K, 0>(b, bl, br, f1, f2, B0);
-        increment_source<T, K, 1>(b, bl, br, f1, f2, B1);
+        const T e1 = (T)a.e1, e2 = (T)a.e2, es = (T)a.es;
+        increment_source<T, K, 0>(b, bl, br, e1, e2, e1, e1, B0);
+        increment_source<T, K, 1>(b, bl, br, e1, e2, lane_l ? es : e1, lane_r ? es : e1, B1);
     }
 
     int done = 0;

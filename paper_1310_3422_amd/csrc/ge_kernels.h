@@ -34,7 +34,7 @@ struct TileArgs {
     int32_t nlev;            // levels advanced by this launch
     double r, k, cs;         // r, r/(1+2r), r/(1+r)
     double c1, c2;           // (r+r^2)/(1+2r), r^2/(1+2r)
-    double e1, e2, es;       // pair: tau(1+r)/(1+2r), tau r/(1+2r), tau/(1+r)
+    double e1, e2, es;       // FP32 forms: tau(1+r)/(1+2r), tau r/(1+2r), tau/(1+r)
     double gl0, gr0;         // constant walls (used when gl_t / gr_t are null)
     double tau, h;           // for the wall-flux diagnostic
     // sub-domain scheme (launch_sdc): core and halo count sub-domain

@@ -24,15 +24,21 @@
 // FP32 rounds u once per level, so it forms the increment from second
 // differences, D_i = u_{i-1} - 2u_i + u_{i+1} = d_i - d_{i-1} from first
 // differences d_i = u_{i+1} - u_i (exact for smooth data, so the increment
-// carries a relative rounding error):
-//     u_i' = u_i + c1 (D_i + cs D_q),   c1 = (r+r^2)/(1+2r), cs = r/(1+r),
-// with q the partner of i, as two FMAs: 4 instructions a point (5 when the
-// increment was formed as c1 D_i + c2 D_q and added).  Two stages would take 3,
+// carries a relative rounding error), rounds it and adds it:
+//     u_i' = u_i + (c1 D_i + c2 D_q),   c1 = (r+r^2)/(1+2r), c2 = r^2/(1+2r),
+// with q the partner of i: 5 instructions a point.  The increment's own
+// rounding is needed: where c1, c2 are dyadic or thirds the exact increment often
+// lies half a unit of u from its neighbours, and one folded into the addition,
+// fma(c1, fma(cs, D_q, D_i), u) at 4 instructions, breaks every such tie the
+// way that the rounding of cs points.  Against extended precision that form's
+// error was 3.8 times this one's at r = 1 (300 points, 2000 levels), 1.4 to 1.9
+// times at r = 1/2 and 1.6 at r = 1/4.  Two stages would take 3 instructions,
 // but their roundings part from this form's by up to 4e-5 of u where
 // increments fall below half a unit of u (30000 points, r = 0.3, 6000
-// levels).  A point alone beside a wall is u_i' = u_i + cs D_i with the
-// wall's new value in D_i.  A source adds a(t_m + tau/2) (tau/r b_i +
-// tau/(1+r) b_q) inside the parentheses (no b_q for a lone point).
+// levels).  A point alone beside a wall is u_i' = u_i + cs D_i, cs = r/(1+r),
+// with the wall's new value in D_i.  A source adds a(t_m + tau/2) (e1 b_i +
+// e2 b_q) to the increment of a pair member and a(t_m + tau/2) es b_i to a lone
+// point's, e1 = tau(1+r)/(1+2r), e2 = tau r/(1+2r), es = tau/(1+r).
 //
 // The compensated FP32 pair (s, e), value s + e:
 //     u_i' = u_i + c1 D_i + c2 D_q,   c1 = (r+r^2)/(1+2r), c2 = r^2/(1+2r),
@@ -361,7 +367,7 @@ __device__ __forceinline__ void split_wall(double g, T &hi, T &lo)
 // Constants of the scheme in the state's type.
 template <typename T> struct Coef {
     T r, k;     // r, r/(1+2r): FP64
-    T c1;       // (r+r^2)/(1+2r): FP32
+    T c1, c2;   // (r+r^2)/(1+2r), r^2/(1+2r): FP32
     T cs;       // r/(1+r)
 };
 
@@ -373,7 +379,7 @@ template <typename T> struct Coef {
 template <typename T>
 __device__ __forceinline__ Coef<T> lane_coef(Coef<T> c)
 {
-    if constexpr (sizeof(T) == 4) asm("" : "+v"(c.c1), "+v"(c.cs));
+    if constexpr (sizeof(T) == 4) asm("" : "+v"(c.c1), "+v"(c.c2), "+v"(c.cs));
     return c;
 }
 
@@ -459,16 +465,18 @@ __device__ __forceinline__ T lone_point(T v, T g, T cs)
 }
 
 // ---- the increment form (FP32) ---------------------------------------------
-// The source weights of the lane's points at parity P, in units of c1:
-// (tau/r) b_i + (tau/(1+r)) b_q, q the partner of i (neighbouring lanes' points
-// through bl = b_{-1}, br = b_K: 0 at a wall, whose lone point has no partner).
+// The source weights of the lane's points at parity P, e1 b_i + e2 b_q, q the
+// partner of i (neighbouring lanes' points through bl = b_{-1}, br = b_K: 0 at a
+// wall, whose lone point has no partner).  el, er: e1 of the lane's first and
+// last point at P = 1, es in the lane whose point stands alone beside a wall.
 template <typename T, int K, int P>
-__device__ __forceinline__ void increment_source(const T (&b)[K], T bl, T br, T f1, T f2, T (&B)[K])
+__device__ __forceinline__ void increment_source(const T (&b)[K], T bl, T br, T e1, T e2, T el,
+                                                 T er, T (&B)[K])
 {
 #pragma unroll
     for (int j = 0; j < K; ++j) {
         const int q = ((j + P) & 1) == 0 ? j + 1 : j - 1;
-        B[j] = fmaT(f1, b[j], f2 * (q < 0 ? bl : q == K ? br : b[q]));
+        B[j] = fmaT(q < 0 ? el : q == K ? er : e1, b[j], e2 * (q < 0 ? bl : q == K ? br : b[q]));
     }
 }
 
@@ -476,7 +484,7 @@ __device__ __forceinline__ void increment_source(const T (&b)[K], T bl, T br, T 
 // u_{-2}, u_K, u_{K+1} for lanes 0 / 63 (unused on an open side).  Beside a wall xl
 // (xr) is its old value at P = 0 and its new one at P = 1, xl2 (xr2) any
 // finite value, and cl, pl (cr, pr), the factors of the lane's first (last)
-// point at P = 1, are cs and 0 in place of c1 and cs.
+// point at P = 1, are cs and 0 in place of c1 and c2.
 template <typename T, int K, bool SRC, int P, bool OL, bool OR>
 __device__ __forceinline__ void increment_level(T (&u)[K], const T (&B)[K], T an, T xl, T xl2, T xr,
                                                 T xr2, const Coef<T> &c, T cl, T pl, T cr, T pr)
@@ -484,9 +492,9 @@ __device__ __forceinline__ void increment_level(T (&u)[K], const T (&B)[K], T an
     const T ul = edge_left<OL>(xl, u[K - 1]), ur = edge_right<OR>(xr, u[0]);
     // u_j from the factors f, g of its own and its partner's second difference
     auto upd = [&](int j, T D, T Dq, T f, T g) {
-        T x = fmaT(g, Dq, D);
-        if constexpr (SRC) x = fmaT(an, B[j], x);
-        u[j] = fmaT(f, x, u[j]);
+        T inc = fmaT(f, D, g * Dq);
+        if constexpr (SRC) inc = fmaT(an, B[j], inc);
+        u[j] = u[j] + inc;
     };
     if constexpr (P == 0) {
         T dprev = u[0] - ul;
@@ -495,8 +503,8 @@ __device__ __forceinline__ void increment_level(T (&u)[K], const T (&B)[K], T an
             const T d0 = u[j + 1] - u[j];
             const T d1 = (j + 2 < K ? u[j + 2] : ur) - u[j + 1];
             const T Da = d0 - dprev, Db = d1 - d0;
-            upd(j, Da, Db, c.c1, c.cs);
-            upd(j + 1, Db, Da, c.c1, c.cs);
+            upd(j, Da, Db, c.c1, c.c2);
+            upd(j + 1, Db, Da, c.c1, c.c2);
             dprev = d1;
         }
     } else {
@@ -515,8 +523,8 @@ __device__ __forceinline__ void increment_level(T (&u)[K], const T (&B)[K], T an
             const T da = u[j + 1] - u[j], db = u[j + 2] - u[j + 1];
             const T Da = da - dprev, Db = db - da;
             if (j == 1) upd(0, D0, Dl, cl, pl);
-            upd(j, Da, Db, c.c1, c.cs);
-            upd(j + 1, Db, Da, c.c1, c.cs);
+            upd(j, Da, Db, c.c1, c.c2);
+            upd(j + 1, Db, Da, c.c1, c.c2);
             dprev = db;
         }
         if constexpr (K == 2) upd(0, D0, Dl, cl, pl);
@@ -526,16 +534,16 @@ __device__ __forceinline__ void increment_level(T (&u)[K], const T (&B)[K], T an
 
 // The point alone beside a right wall node at a run-time position: element
 // kS of its lane, u_{n-2} before it (xl: the fill of lane 0); g: the wall's
-// new value.
+// new value; b: the source profile.
 template <typename T, int K, bool SRC>
-__device__ __forceinline__ T lone_increment(const T (&u)[K], const T (&B)[K], T an, int kS, T xl,
-                                            T g, T cs)
+__device__ __forceinline__ T lone_increment(const T (&u)[K], const T (&b)[K], T an, int kS, T xl,
+                                            T g, T cs, T es)
 {
     const T ul = from_left(xl, u[K - 1]);
     const T u1 = get_at<T, K>(u, kS, T(0)), u0 = get_at<T, K>(u, kS - 1, ul);
-    T x = (g - u1) - (u1 - u0);
-    if constexpr (SRC) x = fmaT(an, get_at<T, K>(B, kS, T(0)), x);
-    return fmaT(cs, x, u1);
+    T inc = cs * ((g - u1) - (u1 - u0));
+    if constexpr (SRC) inc = fmaT(an, es * get_at<T, K>(b, kS, T(0)), inc);
+    return u1 + inc;
 }
 
 // ---- the compensated pair --------------------------------------------------

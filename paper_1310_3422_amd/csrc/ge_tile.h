@@ -112,11 +112,11 @@ __device__ __forceinline__ void sweep_plain(const TileArgs &a, int tid, int64_t 
     if (own_L) acc = a.flux[0];
     if (own_R) accR = a.flux[1];
 
-    const Coef<T> cf = lane_coef(Coef<T>{(T)a.r, (T)a.k, (T)a.c1, (T)a.cs});
+    const Coef<T> cf = lane_coef(Coef<T>{(T)a.r, (T)a.k, (T)a.c1, (T)a.c2, (T)a.cs});
     const bool lane_l = left && tid == 0, lane_r = right && tid == NW * kWave - 1;
     const T kl = lane_l ? cf.cs : cf.k, kr = lane_r ? cf.cs : cf.k;
     const T cl = lane_l ? cf.cs : cf.c1, cr = lane_r ? cf.cs : cf.c1;
-    const T pl = lane_l ? T(0) : cf.cs, pr = lane_r ? T(0) : cf.cs;
+    const T pl = lane_l ? T(0) : cf.c2, pr = lane_r ? T(0) : cf.c2;
     const bool flux = WALL && a.flux != nullptr;   // uniform
     WallFeed<T> wl, wr;
     const int par0 = (int)((a.level0 + ws) & 1);   // the first level's parity in the window
@@ -135,9 +135,9 @@ __device__ __forceinline__ void sweep_plain(const TileArgs &a, int tid, int64_t 
             if (lane == kWave - 1 && w < NW - 1) br = xs[0][w + 1][0];
             __syncthreads();
         }
-        const T f1 = (T)(a.tau / a.r), f2 = (T)(a.tau / (1.0 + a.r));
-        increment_source<T, K, 0>(b, bl, br, f1, f2, B0);
-        increment_source<T, K, 1>(b, bl, br, f1, f2, B1);
+        const T e1 = (T)a.e1, e2 = (T)a.e2, es = (T)a.es;
+        increment_source<T, K, 0>(b, bl, br, e1, e2, e1, e1, B0);
+        increment_source<T, K, 1>(b, bl, br, e1, e2, lane_l ? es : e1, lane_r ? es : e1, B1);
     }
 
     // values entering the wave at its edges: from the neighbouring waves
@@ -196,7 +196,7 @@ __device__ __forceinline__ void sweep_plain(const TileArgs &a, int tid, int64_t 
             exchange(lev & 1, gl, gr, xl, xr);
             auto level = [&](const T (&B)[K]) {
                 if (KIND == kInside && single)
-                    lone = lone_increment<T, K, SRC>(u, B, (T)an, kS, xl[0], gr, cf.cs);
+                    lone = lone_increment<T, K, SRC>(u, b, (T)an, kS, xl[0], gr, cf.cs, (T)a.es);
                 increment_level<T, K, SRC, P, OPEN, OPEN>(u, B, (T)an, xl[0], xl[E - 1], xr[0], xr[E - 1],
                                                     cf, cl, pl, cr, pr);
             };
