@@ -20,8 +20,8 @@
 // (iK+k-1, iK+k) = elements k-2, k-1; B through the odd sub-domain down to
 // its first node, which the lane to the left holds; A through the even one).
 // The pairs take Eq. (3)/(4) with denominator 1 + 2r in second-difference
-// form; a sweep step is fma(c, v_prev, fma(ca, w, c w_other)), c = r/(1+r),
-// ca = (1-r)/(1+r).
+// form; a sweep step takes w to w + c (v_prev - 2 w + w_other), c = r/(1+r)
+// (see sweep).
 //
 // Temporal blocking: a launch advances `nlev` levels of a window of NW x 64
 // SDCs (NW waves of one workgroup) and writes back its core; the window
@@ -48,7 +48,7 @@ template <> struct Chunk<float> { using type = float4; };
 template <> struct Chunk<double> { using type = double2; };
 
 template <typename T> struct SdcCoef {
-    T c, ca;      // r/(1+r), (1-r)/(1+r): the sweep step
+    T c, ca;      // r/(1+r), (1-r)/(1+r) (FP32): the sweep step
     T c1, c2;     // (r+r^2)/(1+2r), r^2/(1+2r): the pair
 };
 
@@ -73,23 +73,36 @@ __device__ __forceinline__ void sdc_pair(T um, T u0, T u1, T u2, const SdcCoef<T
 }
 
 // One Saul'yev step: (r v + (1-r) w + r wo) / (1+r), with v the new value
-// of the sweep predecessor and wo the old value of the other neighbour
+// of the sweep predecessor and wo the old value of the other neighbour, as
+// c v + t in three instructions of which one waits for v.
+//
+// FP64 forms t = w + c (wo - 2 w).  With t = ca w + c wo, ca = (1-r)/(1+r), the
+// rounded coefficients leave 2 c + ca off 1 by up to 1e-16, every node of every
+// level moves by that share of itself, and that is nearly all of the error:
+// against extended precision, 200 to 2000 levels, k = 2 to 16, r = 1/4 to 20,
+// the error here is 0.0 to 0.4 of that form's, also of its two steps at once
+// (k = 16, r = 2 0.15; the geometric mean over all 0.07), and the same near
+// 2e-16 at r = 1 (1.0 to 1.3), where ca is 0.  FP32 keeps ca w + c wo: results
+// stay within the differences of FP32 from what they have been.
 template <typename T>
 __device__ __forceinline__ T sweep(T v, T w, T wo, const SdcCoef<T> &k)
 {
-    return fmaT(k.c, v, fmaT(k.ca, w, k.c * wo));
+    if constexpr (sizeof(T) == 8) return fmaT(k.c, v, fmaT(k.c, fmaT(T(-2), w, wo), w));
+    else return fmaT(k.c, v, fmaT(k.ca, w, k.c * wo));
 }
 
 // A sweep through elements FROM..TO (in either direction) of the lane's
 // registers, starting from the new value v of the node before FROM:
-// v_e = c v_prev + t_e, t_e = ca w_e + c wo_e, a chain of dependent FMAs
+// v_e = c v_prev + t_e, a chain of dependent FMAs
 // with two more instructions a node beside it, which fill the chain's
 // latency.  (Two steps at once, v_{e+1} = c^2 v + (c t_e + t_{e+1}), halve
 // the chain for 3.5 instructions a node; with two or more waves on a SIMD
 // the issue slots count for more: FP64 k = 16 on 2^24 - 1 points 5.03e12
 // against 5.32e12 updates/s here, k = 8 5.78e12 against 6.13e12, FP32 k = 16
-// 9.5e12 against 10.1e12; within 1% at k = 2.)  other(e) is the old value of
-// e's neighbour on the far side (read before anything is written over it).
+// 9.5e12 against 10.1e12; within 1% at k = 2.  In FP32 the error of one at a
+// time is 0.7 of that form's over all, 0.1 to 0.2 at r = 4, though 1.7 to 2
+// times it at r = 1, where both are 1e-6 or below.)  other(e) is the old value
+// of e's neighbour on the far side (read before anything is written over it).
 template <typename T, int K, int FROM, int TO, typename Other>
 __device__ __forceinline__ void sweep_run(T (&s)[K], T v, const SdcCoef<T> &k, Other other)
 {
