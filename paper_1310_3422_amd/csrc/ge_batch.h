@@ -67,22 +67,23 @@ __host__ __device__ inline int halo_waves(int64_t n, int k)
 }
 
 // Where the waves of a halo task's rod start: wave j at 62 k j, except the
-// last, which ends at the right wall (its start may be any element: it reads
-// and writes its points one by one, and pairs them the other way round when
-// it starts at an odd one).  `fits`: the rod has two or more waves and the
-// last window does not reach into its neighbour's duplicated lane; only such
-// rods go to halo tasks.
+// last, which ends at the right wall (`exact`, FP64: its start may be any
+// element, and it pairs its points the other way round when it starts at an odd
+// one) or at the next multiple of 4 (FP32 and the pair).  `fits`: the rod has two
+// or more waves and the last window does not reach into its neighbour's
+// duplicated lane; only such rods go to halo tasks.
 struct HaloLayout {
     int64_t n;
     int k, m;
     int64_t last;
     bool fits;
-    __host__ __device__ HaloLayout(int64_t n_, int k_) : n(n_), k(k_), m(halo_waves(n_, k_))
+    __host__ __device__ HaloLayout(int64_t n_, int k_, bool exact)
+        : n(n_), k(k_), m(halo_waves(n_, k_))
     {
         last = (int64_t)(m - 1) * 62 * k;
         fits = false;
         if (m >= 2) {
-            const int64_t r = n - 64 * (int64_t)k;
+            const int64_t r = exact ? n - 64 * (int64_t)k : (n - 64 * (int64_t)k + 3) / 4 * 4;
             const int64_t need = m == 2 ? 0 : (int64_t)(m - 2) * 62 * k + k;
             if (r >= need) {
                 last = r;

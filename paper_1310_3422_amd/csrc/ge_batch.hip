@@ -96,65 +96,45 @@ __device__ __forceinline__ void rod_levels(const BatchArgs &a, const BatchRod &r
             __syncthreads();
         }
     };
-    // a rod of one wave meets nobody (barrier mode: every wave meets)
-    const bool alone = NBR && wr == 0 && !hasR;
     const int wl = w > 0 ? w - 1 : 0, wrr = w < kWaves - 1 ? w + 1 : kWaves - 1;
     T gl_hi, gl_lo, gr_hi, gr_lo;
     split_wall<T, COMP>(rd.gl, gl_hi, gl_lo);
     split_wall<T, COMP>(rd.gr, gr_hi, gr_lo);
 
-    if constexpr (!COMP) {
-        // FP64 meets its neighbours with one value a side, FP32 with two
-        constexpr bool TWO_STAGE = sizeof(T) == 8;
-        constexpr int E = TWO_STAGE ? 1 : 2;
+    // a rod of one wave meets nobody (barrier mode: every wave meets)
+    const bool alone = NBR && wr == 0 && !hasR;
+    if constexpr (sizeof(T) == 8) {
         const Coef<T> cf = lane_coef(Coef<T>{(T)rd.r, (T)rd.k, (T)rd.c1, (T)rd.c2, (T)rd.cs});
         const bool lane_l = WALL && left_wall && lane == 0;
         const bool lane_r = WALL && ghost_edge && lane == kWave - 1;
         const T kl = lane_l ? cf.cs : cf.k, kr = lane_r ? cf.cs : cf.k;
-        const T cl = lane_l ? cf.cs : cf.c1, cr = lane_r ? cf.cs : cf.c1;
-        const T pl = lane_l ? T(0) : cf.c2, pr = lane_r ? T(0) : cf.c2;
-        auto exchange = [&](int lev, T (&xl)[E], T (&xr)[E]) {
+        // one value a side
+        auto exchange = [&](int lev, T &xl, T &xr) {
             const int pb = lev & 1;
             if (!alone) {
-#pragma unroll
-                for (int i = 0; i < E; ++i) {
-                    if (lane == 0) xs[pb][w][i] = s[i];
-                    if (lane == kWave - 1) xs[pb][w][2 + i] = s[K - 1 - i];
-                }
+                if (lane == 0) xs[pb][w][0] = s[0];
+                if (lane == kWave - 1) xs[pb][w][2] = s[K - 1];
                 meet(lev);
+                xl = xs[pb][wl][2];
+                xr = xs[pb][wrr][0];
             }
-#pragma unroll
-            for (int i = 0; i < E; ++i) {
-                if (!alone) {
-                    xl[i] = xs[pb][wl][2 + i];
-                    xr[i] = xs[pb][wrr][i];
-                }
-                if constexpr (WALL) {
-                    if (left_wall) xl[i] = gl_hi;
-                    if (ghost_edge) xr[i] = gr_hi;
-                }
+            if constexpr (WALL) {
+                if (left_wall) xl = gl_hi;
+                if (ghost_edge) xr = gr_hi;
             }
         };
         for_levels(a.step0, a.nsteps, [&](auto par, int lev) {
             constexpr int P = decltype(par)::value;
-            T xl[E] = {}, xr[E] = {};
+            T xl = T(0), xr = T(0);
             if (WALL && ghost_in) put_at<T, K>(s, kR, lane == lR, gr_hi);
             // the point beside a wall node inside the wave, when it is alone
             const bool single = WALL && has_S && !ghost_edge && (((n - 1 + P) & 1) == 0);
             T lone = T(0);
-            if constexpr (TWO_STAGE) {
-                if constexpr (P == 0) exchange(lev, xl, xr);
-                explicit_stage<T, K, P, false, false>(s, xl[0], xr[0], cf);
-                if constexpr (P == 1) exchange(lev, xl, xr);
-                if (WALL && single) lone = lone_point(get_at<T, K>(s, kS, T(0)), gr_hi, cf.cs);
-                solve_stage<T, K, P, false, false>(s, xl[0], xr[0], cf, kl, kr);
-            } else {
-                exchange(lev, xl, xr);
-                if (WALL && single)
-                    lone = lone_increment<T, K, false>(s, s, T(0), kS, xl[0], gr_hi, cf.cs, T(0));
-                increment_level<T, K, false, P, false, false>(s, s, T(0), xl[0], xl[E - 1], xr[0],
-                                                       xr[E - 1], cf, cl, pl, cr, pr);
-            }
+            if constexpr (P == 0) exchange(lev, xl, xr);
+            explicit_stage<T, K, P, false, false>(s, xl, xr, cf);
+            if constexpr (P == 1) exchange(lev, xl, xr);
+            if (WALL && single) lone = lone_point(get_at<T, K>(s, kS, T(0)), gr_hi, cf.cs);
+            solve_stage<T, K, P, false, false>(s, xl, xr, cf, kl, kr);
             if (WALL && single) put_at<T, K>(s, kS, lane == lS, lone);
         });
         return;
@@ -167,32 +147,41 @@ __device__ __forceinline__ void rod_levels(const BatchArgs &a, const BatchRod &r
         constexpr int p = decltype(par)::value;
         if (WALL && ghost_in) {
             put_at<T, K>(s, kR, lane == lR, gr_hi);
-            put_at<T, K>(e, kR, lane == lR, gr_lo);
+            if constexpr (COMP) put_at<T, K>(e, kR, lane == lR, gr_lo);
         }
-        const int pb = lev & 1;
-        if (lane == 0) { xs[pb][w][0] = s[0]; xs[pb][w][1] = s[1]; }
-        if (lane == kWave - 1) { xs[pb][w][2] = s[K - 2]; xs[pb][w][3] = s[K - 1]; }
-        if (lane == 0) { xe[pb][w][0] = e[0]; xe[pb][w][1] = e[1]; }
-        if (lane == kWave - 1) { xe[pb][w][2] = e[K - 2]; xe[pb][w][3] = e[K - 1]; }
-        meet(lev);
-        T xl = xs[pb][wl][3], xr = xs[pb][wrr][0], xl2 = xs[pb][wl][2], xr2 = xs[pb][wrr][1];
-        T yl = xe[pb][wl][3], yr = xe[pb][wrr][0], yl2 = xe[pb][wl][2], yr2 = xe[pb][wrr][1];
+        T xl = T(0), xr = T(0), xl2 = T(0), xr2 = T(0);
+        T yl = T(0), yr = T(0), yl2 = T(0), yr2 = T(0);
+        if (!alone) {
+            const int pb = lev & 1;
+            if (lane == 0) { xs[pb][w][0] = s[0]; xs[pb][w][1] = s[1]; }
+            if (lane == kWave - 1) { xs[pb][w][2] = s[K - 2]; xs[pb][w][3] = s[K - 1]; }
+            if constexpr (COMP) {
+                if (lane == 0) { xe[pb][w][0] = e[0]; xe[pb][w][1] = e[1]; }
+                if (lane == kWave - 1) { xe[pb][w][2] = e[K - 2]; xe[pb][w][3] = e[K - 1]; }
+            }
+            meet(lev);
+            xl = xs[pb][wl][3]; xr = xs[pb][wrr][0]; xl2 = xs[pb][wl][2]; xr2 = xs[pb][wrr][1];
+            if constexpr (COMP) {
+                yl = xe[pb][wl][3]; yr = xe[pb][wrr][0]; yl2 = xe[pb][wl][2]; yr2 = xe[pb][wrr][1];
+            }
+        }
         WallLevel<T> wlv{false, T(0)};
         bool singR = false;
         if constexpr (WALL) {
-            if (left_wall) { xl = gl_hi; yl = gl_lo; }
-            if (ghost_edge) { xr = gr_hi; yr = gr_lo; }
+            if (left_wall) { xl = gl_hi; if constexpr (COMP) yl = gl_lo; }
+            if (ghost_edge) { xr = gr_hi; if constexpr (COMP) yr = gr_lo; }
             wlv.isL = left_wall && (p == 1) && (lane == 0);
             singR = has_S && (((n - 1 + p) & 1) == 0);
         }
         Lone<T> lone{T(0), T(0)};
         if (WALL && singR)
-            lone = right_lone<T, K, false>(s, e, b0, kS, xl, yl, gr_hi, gr_lo, T(0), cf, T(0));
-        pair_level<T, K, 0, WALL, p>(s, e, b0, T(0), T(0), xl, xl2, xr, xr2, yl, yl2, yr, yr2, cf,
-                                     T(0), wlv, ft);
+            lone = right_lone<T, K, false, COMP>(s, e, b0, kS, xl, yl, gr_hi, gr_lo, T(0), cf,
+                                                 T(0));
+        pair_level<T, K, 0, WALL, p, false, COMP>(s, e, b0, T(0), T(0), xl, xl2, xr, xr2, yl, yl2,
+                                                  yr, yr2, cf, T(0), wlv, ft);
         if (WALL && singR) {
             put_at<T, K>(s, kS, lane == lS, lone.s);
-            put_at<T, K>(e, kS, lane == lS, lone.e);
+            if constexpr (COMP) put_at<T, K>(e, kS, lane == lS, lone.e);
         }
     });
     }
@@ -241,8 +230,10 @@ __device__ __forceinline__ void run_task(const BatchArgs &a, const BatchTask &tk
     }
     // single registers from here on: as parts of the loads' tuples they would be
     // copied for each of the paths below
+    if constexpr (sizeof(T) == 8 || K <= 32) {
 #pragma unroll
-    for (int j = 0; j < K; ++j) asm("" : "+v"(s[j]));
+        for (int j = 0; j < K; ++j) asm("" : "+v"(s[j]));
+    }
     const int64_t w0 = (int64_t)wr * kWave * K;
     const bool wall = (rod >= 0) && (wr == 0 || rd.n - w0 <= (int64_t)kWave * K);
     if (!NBR || rod >= 0) {
@@ -272,64 +263,79 @@ __device__ __forceinline__ void run_task(const BatchArgs &a, const BatchTask &tk
 // every level.
 //
 // Walls stay exact at the rod's ends.  The first wave starts at the left
-// wall, which enters as the fill of its lane 0, and the last wave ends at the
-// right wall, the fill of its lane 63, so neither costs anything inside the
-// levels (a wall node at a data-dependent element costs a branch tree per
-// access).  The last wave then overlaps its neighbour by more than one lane,
-// and the refresh copies values by position: the writer's lanes covering the
+// wall, which enters as the fill of its lane 0.  The last wave is placed so
+// that the right wall node falls just beyond its window, the fill of its lane 63,
+// or (FP32 and the pair, whose windows start at multiples of 4) at a fixed one of
+// lane 63's last three elements: that costs a select or two per
+// level, where a wall node at a data-dependent element costs a branch tree
+// per access.  It then overlaps its neighbour by more than one lane, and the
+// refresh copies values by position: the writer's lanes covering the
 // positions store them to LDS, the reader takes k values at the offset.
 // When the last window would reach into its neighbour's duplicated lane (a
 // 1-in-62 case), or the rod has one wave, the rod goes to another task.
+//
+// FP32 and the pair keep their second differences whole here (pair_level), with
+// guarded loads and a wave's end fixed at compile time: in the form of the
+// windows (increment_level, any start, two kinds of store) the same operations
+// spilled inside the level loop at 64 points a lane, 752 bytes of scratch a lane
+// against 216, more than the runtime keeps allocated for every wave slot, which
+// adds some 20 us to a launch (sync 3: one FP32 rod of 5000 points, 200 levels
+// 226 us against 180; 1000 of 65000 points 2.58 ms against 2.12; 600 of 256 to
+// 65536 points 648 us against 542).
 constexpr int kMaxBatchK = 64;
 constexpr int kSlot = 2 * kMaxBatchK;    // values per exchange slot (two lanes)
 
 // One wave of a rod of several: END 0 = both window edges open, 1 = the
 // window starts at the left wall (it enters as the fill of lane 0, whose
 // first point stands alone at odd levels), 2 = it ends at the right wall
-// (the fill of lane 63).  level0's parity is the window's: a window that
-// starts at an odd point pairs its points the other way round.
-template <typename T, int K, bool COMP, int END>
+// (the fill of lane 63), or RQ points (0..3) past the wall node: the node is
+// then element K - RQ of lane 63, the lone point beside it element K - 1 - RQ.
+// level0's parity is the window's: an FP64 window that starts at an odd point
+// pairs its points the other way round.
+template <typename T, int K, bool COMP, int END, int RQ>
 __device__ __forceinline__ void rod_block(const BatchRod &rd, T (&s)[K], T (&e)[K],
                                           int64_t level0, int nlev)
 {
     const int lane = threadIdx.x & (kWave - 1);
     T g, gx;   // the wall's value, and its compensation
     split_wall<T, COMP>(END == 1 ? rd.gl : rd.gr, g, gx);
-    if constexpr (!COMP) {
+    if constexpr (sizeof(T) == 8) {
         const Coef<T> cf = lane_coef(Coef<T>{(T)rd.r, (T)rd.k, (T)rd.c1, (T)rd.c2, (T)rd.cs});
-        const bool lane_l = END == 1 && lane == 0, lane_r = END == 2 && lane == kWave - 1;
-        if constexpr (sizeof(T) == 8) {
-            const T kl = lane_l ? cf.cs : cf.k, kr = lane_r ? cf.cs : cf.k;
-            for_levels(level0, nlev, [&](auto par, int) {
-                constexpr int P = decltype(par)::value;
-                explicit_stage<T, K, P, END != 1, END != 2>(s, g, g, cf);
-                solve_stage<T, K, P, END != 1, END != 2>(s, g, g, cf, kl, kr);
-            });
-        } else {
-            const T cl = lane_l ? cf.cs : cf.c1, cr = lane_r ? cf.cs : cf.c1;
-            const T pl = lane_l ? T(0) : cf.c2, pr = lane_r ? T(0) : cf.c2;
-            for_levels(level0, nlev, [&](auto par, int) {
-                increment_level<T, K, false, decltype(par)::value, END != 1, END != 2>(
-                    s, s, T(0), g, g, g, g, cf, cl, pl, cr, pr);
-            });
-        }
+        const T kl = END == 1 && lane == 0 ? cf.cs : cf.k;
+        const T kr = END == 2 && lane == kWave - 1 ? cf.cs : cf.k;
+        for_levels(level0, nlev, [&](auto par, int) {
+            constexpr int P = decltype(par)::value;
+            explicit_stage<T, K, P, END != 1, END != 2>(s, g, g, cf);
+            solve_stage<T, K, P, END != 1, END != 2>(s, g, g, cf, kl, kr);
+        });
     } else {
         const PairCoef<T> cf =
             lane_coef(PairCoef<T>{(T)rd.c1, (T)rd.c2, (T)rd.cs, T(0), T(0), T(0)});
         const T b0[K] = {};
         FluxTap ft{false, 0.0, 0.0, 1.0, 0.0};
+        constexpr int kS = K - 1 - RQ;
+        const bool lone_odd = ((rd.n - 1) & 1) == 0;   // alone at even global parity
         for_levels(level0, nlev, [&](auto par, int) {
             constexpr int p = decltype(par)::value;
-            const WallLevel<T> wlv{END == 1 && p == 1 && lane == 0, T(0)};
+            if constexpr (END == 2 && RQ > 0) {
+                put_at<T, K>(s, K - RQ, lane == kWave - 1, g);
+                if constexpr (COMP) put_at<T, K>(e, K - RQ, lane == kWave - 1, gx);
+            }
+            const T xl = END == 1 ? g : T(0), yl = END == 1 && COMP ? gx : T(0);
+            const T xr = END == 2 && RQ == 0 ? g : T(0);
+            const T yr = END == 2 && RQ == 0 && COMP ? gx : T(0);
+            const bool singR = END == 2 && lone_odd == (p == 0);
             Lone<T> lone{T(0), T(0)};
-            // the window's last point has an odd place in it
-            if constexpr (END == 2 && p == 1)
-                lone = right_lone<T, K, false>(s, e, b0, K - 1, T(0), T(0), g, gx, T(0), cf, T(0));
-            pair_level<T, K, 0, END == 1, p, END == 0>(s, e, b0, T(0), T(0), g, T(0), g, T(0), gx,
-                                                       T(0), gx, T(0), cf, T(0), wlv, ft);
-            if constexpr (END == 2 && p == 1) {
-                s[K - 1] = lane == kWave - 1 ? lone.s : s[K - 1];
-                e[K - 1] = lane == kWave - 1 ? lone.e : e[K - 1];
+            if (singR)
+                lone = right_lone<T, K, false, COMP>(s, e, b0, kS, T(0), T(0), g, gx, T(0), cf,
+                                                     T(0));
+            const WallLevel<T> wlv{END == 1 && p == 1 && lane == 0, T(0)};
+            pair_level<T, K, 0, END == 1, p, END == 0, COMP>(s, e, b0, T(0), T(0), xl, T(0), xr,
+                                                             T(0), yl, T(0), yr, T(0), cf, T(0),
+                                                             wlv, ft);
+            if (singR) {
+                put_at<T, K>(s, kS, lane == kWave - 1, lone.s);
+                if constexpr (COMP) put_at<T, K>(e, kS, lane == kWave - 1, lone.e);
             }
         });
     }
@@ -343,10 +349,10 @@ __device__ __forceinline__ void rod_block(const BatchRod &rd, T (&s)[K], T (&e)[
 // that cover them, and the reader starts at the positions' offset within
 // the first.  aL / aR: window start of this wave minus the left neighbour's,
 // and of the right neighbour minus this wave's.  MODE: 0 = a wave without a
-// rod (it only passes the barriers), 1 + END = a wave of rod_block's kinds.
-// Every wave of the workgroup passes the same barriers (all rods of a task share K and the level count); the mode
-// is chosen once per wave, outside the block loop, so each wave runs one
-// instantiation of the level code.
+// rod (it only passes the barriers), 1, 2 = rod_block's END 0, 1, and 3 + RQ =
+// its END 2.  Every wave of the workgroup passes the same barriers (all rods of
+// a task share K and the level count); the mode is chosen once per wave, outside
+// the block loop, so each wave runs one instantiation of the level code.
 template <typename T, int K, bool COMP, int MODE>
 __device__ __forceinline__ void halo_blocks(const BatchArgs &a, const BatchRod &rd, int w,
                                             int64_t ws, int aL, int aR, bool hasL, bool hasR,
@@ -364,7 +370,8 @@ __device__ __forceinline__ void halo_blocks(const BatchArgs &a, const BatchRod &
     for (int blk = 0;; ++blk) {
         const int nb = (int)((a.nsteps - done) < (K - 1) ? (a.nsteps - done) : (K - 1));
         if constexpr (MODE != 0)
-            rod_block<T, K, COMP, MODE - 1>(rd, s, e, a.step0 + (ws & 1) + done, nb);
+            rod_block<T, K, COMP, MODE < 3 ? MODE - 1 : 2, MODE < 3 ? 0 : MODE - 3>(
+                rd, s, e, a.step0 + (sizeof(T) == 8 ? ws & 1 : 0) + done, nb);
         done += nb;
         if (done >= a.nsteps)
             break;
@@ -425,23 +432,24 @@ __device__ __forceinline__ void run_task_halo(const BatchArgs &a, const BatchTas
     int aL = 62 * K, aR = 62 * K, mode = 0;
     if (rod >= 0) {
         rd = a.rods[rod];
-        const HaloLayout L(rd.n, K);
-        ws = L.start(wr);                           // a multiple of 4
+        const HaloLayout L(rd.n, K, sizeof(T) == 8);
+        ws = L.start(wr);                           // FP32: a multiple of 4
         if (hasL) aL = (int)(ws - L.start(wr - 1));
         if (hasR) aR = (int)(L.start(wr + 1) - ws);
         // the last wave stores only beyond its neighbour's core
         lo = (wr == L.m - 1 && wr > 0) ? L.start(wr - 1) + 63 * K : 0;
         // the planner gives halo tasks only rods of two or more waves whose
-        // last window ends at the wall
-        mode = !hasR ? 3 : (wr == 0 ? 2 : 1);
+        // last window ends at the wall (FP32: 0 to 3 points past it)
+        mode = !hasR ? 3 + (int)(ws + 64 * K - rd.n) : (wr == 0 ? 2 : 1);
         us = static_cast<T *>(a.u) + rd.off;
         ue = static_cast<T *>(a.u) + a.estride + rd.off;
     }
     const int64_t g0 = ws + (int64_t)lane * K;
     if (rod >= 0) {
-        // every window of the rod lies inside it
-        load_lane<T, K>(us + g0, s);
-        if constexpr (COMP) load_lane<T, K>(ue + g0, e);
+        // every FP64 window of the rod lies inside it
+        if constexpr (sizeof(T) == 8) load_lane<T, K>(us + g0, s);
+        else load_lane_guarded<T, K>(us + g0, g0, rd.n, s);
+        if constexpr (COMP) load_lane_guarded<T, K>(ue + g0, g0, rd.n, e);
     } else {
 #pragma unroll
         for (int j = 0; j < K; ++j) s[j] = T(0);
@@ -457,23 +465,43 @@ __device__ __forceinline__ void run_task_halo(const BatchArgs &a, const BatchTas
     __syncthreads();
     // single registers from here on: as parts of the loads' tuples they would be
     // copied for each of the paths below
+    if constexpr (sizeof(T) == 8 || (!COMP && K <= 32)) {
 #pragma unroll
-    for (int j = 0; j < K; ++j) asm("" : "+v"(s[j]));
+        for (int j = 0; j < K; ++j) asm("" : "+v"(s[j]));
+    }
     switch (__builtin_amdgcn_readfirstlane(mode)) {
     case 1: halo_blocks<T, K, COMP, 1>(a, rd, w, ws, aL, aR, hasL, hasR, s, e, hx, he); break;
     case 2: halo_blocks<T, K, COMP, 2>(a, rd, w, ws, aL, aR, hasL, hasR, s, e, hx, he); break;
     case 3: halo_blocks<T, K, COMP, 3>(a, rd, w, ws, aL, aR, hasL, hasR, s, e, hx, he); break;
+    case 4:
+        if constexpr (sizeof(T) == 4)
+            halo_blocks<T, K, COMP, 4>(a, rd, w, ws, aL, aR, hasL, hasR, s, e, hx, he);
+        break;
+    case 5:
+        if constexpr (sizeof(T) == 4)
+            halo_blocks<T, K, COMP, 5>(a, rd, w, ws, aL, aR, hasL, hasR, s, e, hx, he);
+        break;
+    case 6:
+        if constexpr (sizeof(T) == 4)
+            halo_blocks<T, K, COMP, 6>(a, rd, w, ws, aL, aR, hasL, hasR, s, e, hx, he);
+        break;
     default: halo_blocks<T, K, COMP, 0>(a, rd, w, ws, aL, aR, hasL, hasR, s, e, hx, he); break;
     }
     // lanes 1..62, lane 0 of the first wave and lane 63 of the last (the last
     // wave from its neighbour's core end on)
     T fin = T(0);
-    if (rod >= 0 && hasR && (lane > 0 || wr == 0) && lane < kWave - 1) {
-        store_lane_chunks<T, K>(us + g0, g0, 0, rd.n, s, fin);
-        if constexpr (COMP) store_lane_chunks<T, K>(ue + g0, g0, 0, rd.n, e, fin);
-    } else if (rod >= 0 && !hasR) {
+    if constexpr (sizeof(T) == 4) {
+        // one path for every wave: two of them, with their own tuples of
+        // registers, spilled in the level loops at 64 points a lane
+        if (rod >= 0 && (lane > 0 || wr == 0) && (lane < kWave - 1 || !hasR)) {
+            store_lane_range<T, K>(us + g0, g0, lo, rd.n, s, fin);
+            if constexpr (COMP) store_lane_range<T, K>(ue + g0, g0, lo, rd.n, e, fin);
+        }
+    } else if (rod >= 0 && hasR) {
+        if ((lane > 0 || wr == 0) && lane < kWave - 1)
+            store_lane_chunks<T, K>(us + g0, g0, 0, rd.n, s, fin);
+    } else if (rod >= 0) {
         store_lane_guarded<T, K>(us + g0, g0, lo, rd.n, s, fin);
-        if constexpr (COMP) store_lane_guarded<T, K>(ue + g0, g0, lo, rd.n, e, fin);
     }
     if (rod >= 0) raise_if_nonfinite(a.status, fin);
     __syncthreads();   // LDS slots are reused by the next task

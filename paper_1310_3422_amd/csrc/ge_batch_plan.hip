@@ -133,10 +133,10 @@ int waves_for(int64_t n, int k) { return (int)((n + 64 * k - 1) / (64 * k)); }
 // Waves of a rod at k points per lane, and whether it runs as a halo-lane
 // task (halo mode, two or more overlapping waves that fit the workgroup, and
 // a last window that can end at the wall).
-int rod_waves(int64_t n, int k, bool halo_mode, int *halo)
+int rod_waves(int64_t n, int k, int prec, bool halo_mode, int *halo)
 {
     if (halo_mode) {
-        const ge::HaloLayout L(n, k);
+        const ge::HaloLayout L(n, k, prec == ge::kFP64);
         if (L.fits && L.m <= kBatchWaves) {
             *halo = 1;
             return L.m;
@@ -221,7 +221,7 @@ Plan make_plan(const std::vector<int64_t> &n, int prec, const CostModel &cm, int
             const int k = kKs[ki];
             if (k > kmax) continue;
             int h = 0;
-            const int w = rod_waves(n[r], k, halo_mode, &h);
+            const int w = rod_waves(n[r], k, prec, halo_mode, &h);
             if (w > kBatchWaves) continue;
             for (size_t b = 0; b < bins.size(); ++b) {
                 if (bins[b].k != k || bins[b].halo != h) continue;
@@ -245,7 +245,7 @@ Plan make_plan(const std::vector<int64_t> &n, int prec, const CostModel &cm, int
         }
         Bin &b = bins[best_bin];
         int hb = 0;
-        const int w = rod_waves(n[r], b.k, halo_mode, &hb);
+        const int w = rod_waves(n[r], b.k, prec, halo_mode, &hb);
         b.used += w;
         b.nwall += std::min(w, 2);
         members[best_bin].push_back(r);
@@ -267,7 +267,7 @@ Plan make_plan(const std::vector<int64_t> &n, int prec, const CostModel &cm, int
         int w = 0;
         for (int r : members[bi]) {
             int hb = 0;
-            const int nw = t.halo == 2 ? 1 : rod_waves(n[r], t.k, halo_mode, &hb);
+            const int nw = t.halo == 2 ? 1 : rod_waves(n[r], t.k, prec, halo_mode, &hb);
             for (int j = 0; j < nw; ++j) {
                 t.wave_rod[w] = r;
                 t.wave_idx[w] = j;

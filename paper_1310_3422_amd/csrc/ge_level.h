@@ -178,18 +178,28 @@ __device__ __forceinline__ void raise_if_nonfinite(int *status, T acc)
 }
 
 // ---- 16-byte vector access to a lane's K contiguous values ----------------
-// A 16-byte access needs no more than the element's alignment here (a window
-// that ends at a wall may start at any element).
+// type: at a 16-byte boundary.  any: at the element's alignment, for a window
+// that ends at a wall and may start at any element (a vector type, whose parts
+// the compiler keeps in one tuple of registers: where it is not needed, it costs
+// registers).
 typedef float float4_any __attribute__((ext_vector_type(4), aligned(4)));
 typedef double double2_any __attribute__((ext_vector_type(2), aligned(8)));
 template <typename T> struct V16;
-template <> struct V16<float> { using type = float4_any; static constexpr int E = 4; };
-template <> struct V16<double> { using type = double2_any; static constexpr int E = 2; };
+template <> struct V16<float> {
+    using type = float4;
+    using any = float4_any;
+    static constexpr int E = 4;
+};
+template <> struct V16<double> {
+    using type = double2;
+    using any = double2_any;
+    static constexpr int E = 2;
+};
 
 template <typename T, int K>
 __device__ __forceinline__ void load_lane(const T *__restrict__ p, T (&v)[K])
 {
-    using V = typename V16<T>::type;
+    using V = typename V16<T>::any;
     constexpr int E = V16<T>::E;
     constexpr int C = K / E;                      // whole chunks, then single values
 #pragma unroll
@@ -258,7 +268,7 @@ template <typename T, int K>
 __device__ __forceinline__ void store_lane_guarded(T *__restrict__ p, int64_t g0, int64_t lo,
                                                    int64_t hi, const T (&v)[K], T &fin)
 {
-    using V = typename V16<T>::type;
+    using V = typename V16<T>::any;
     constexpr int E = V16<T>::E;
 #pragma unroll
     for (int c = 0; c < K; c += E) {
@@ -276,6 +286,41 @@ __device__ __forceinline__ void store_lane_guarded(T *__restrict__ p, int64_t g0
                 if (c + i < K && g0 + c + i >= lo && g0 + c + i < hi) {
                     finite_acc(fin, v[c + i]);
                     p[c + i] = v[c + i];
+                }
+        }
+    }
+}
+
+// Store the values whose global index lies in [lo, n), lo a multiple of the
+// chunk width: whole 16-byte chunks where they lie below n, single values in the
+// chunk that straddles n.
+template <typename T, int K>
+__device__ __forceinline__ void store_lane_range(T *__restrict__ p, int64_t g0, int64_t lo,
+                                                 int64_t n, const T (&v)[K], T &fin)
+{
+    using V = typename V16<T>::type;
+    constexpr int E = V16<T>::E;
+    V *q = reinterpret_cast<V *>(p);
+#pragma unroll
+    for (int c = 0; c < K / E; ++c) {
+        if (g0 + c * E < lo)
+            continue;
+        if (g0 + (c + 1) * E <= n) {
+#pragma unroll
+            for (int i = 0; i < E; ++i) finite_acc(fin, v[c * E + i]);
+            V x;
+            if constexpr (E == 4) {
+                x.x = v[4 * c]; x.y = v[4 * c + 1]; x.z = v[4 * c + 2]; x.w = v[4 * c + 3];
+            } else {
+                x.x = v[2 * c]; x.y = v[2 * c + 1];
+            }
+            q[c] = x;
+        } else {
+#pragma unroll
+            for (int i = 0; i < E; ++i)
+                if (g0 + c * E + i < n) {
+                    finite_acc(fin, v[c * E + i]);
+                    p[c * E + i] = v[c * E + i];
                 }
         }
     }
@@ -546,24 +591,27 @@ __device__ __forceinline__ T lone_increment(const T (&u)[K], const T (&b)[K], T 
     return u1 + inc;
 }
 
-// ---- the compensated pair --------------------------------------------------
+// ---- the compensated pair (COMP), and FP32 in the persistent batch form ------
 // A first difference of two points given as (s, e).  The s and e parts stay
 // apart: for smooth data the s differences (and their differences) are
 // exact, and summing the s and e second differences only at the end keeps D
 // accurate to the precision of the pair.
-template <typename T> struct Dif { T s, e; };
+template <typename T, bool COMP> struct Dif { T s; };
+template <typename T> struct Dif<T, true> { T s, e; };
 
-template <typename T>
-__device__ __forceinline__ Dif<T> dif(T s1, T e1, T s0, T e0)
+template <bool COMP = true, typename T>
+__device__ __forceinline__ Dif<T, COMP> dif(T s1, T e1, T s0, T e0)
 {
-    return Dif<T>{s1 - s0, e1 - e0};
+    if constexpr (COMP) return Dif<T, COMP>{s1 - s0, e1 - e0};
+    else return Dif<T, COMP>{s1 - s0};
 }
 
 // second difference D = db - da from consecutive first differences
-template <typename T>
-__device__ __forceinline__ T sd(Dif<T> da, Dif<T> db)
+template <typename T, bool COMP>
+__device__ __forceinline__ T sd(Dif<T, COMP> da, Dif<T, COMP> db)
 {
-    return (db.s - da.s) + (db.e - da.e);
+    if constexpr (COMP) return (db.s - da.s) + (db.e - da.e);
+    else return db.s - da.s;
 }
 
 // What a level needs to know about the left wall, seen from one lane (the
@@ -613,7 +661,7 @@ __device__ __forceinline__ void source_weights(const T (&b)[K], T bl, T br, cons
 // Advance the K points of every lane by one level of parity P (known at
 // compile time: a runtime parity would merge the two groupings' results for
 // every point each level and cost the register file).
-//   s, e : the lane's points (e is the compensation)
+//   s, e : the lane's points (e is the compensation; not read without COMP)
 //   b    : SRC = 1: the lane's source profile, bl, br: profile of u_{-1}
 //          and u_K; SRC = 2: the weights of this parity (source_weights)
 //   xl, xl2, xr, xr2 : u_{-1}, u_{-2}, u_K, u_{K+1} for lanes 0 / 63 (DPP
@@ -622,7 +670,8 @@ __device__ __forceinline__ void source_weights(const T (&b)[K], T bl, T br, cons
 // WALL instantiations apply the lone-point formulas and the flux tap; every
 // other point of every instantiation evaluates the same expressions.  OPEN:
 // both edges of the wave are open window edges, so the fills are not used.
-template <typename T, int K, int SRC, bool WALL, int P, bool OPEN = false>
+// Without COMP a point gets the operations that increment_level gives it.
+template <typename T, int K, int SRC, bool WALL, int P, bool OPEN = false, bool COMP = true>
 __device__ __forceinline__ void pair_level(T (&s)[K], T (&e)[K], const T (&b)[K], T bl, T br,
                                            T xl, T xl2, T xr, T xr2, T yl, T yl2, T yr, T yr2,
                                            const PairCoef<T> &c, T an, const WallLevel<T> &wl,
@@ -632,7 +681,12 @@ __device__ __forceinline__ void pair_level(T (&s)[K], T (&e)[K], const T (&b)[K]
     const T c1 = c.c1, c2 = c.c2, cs = c.cs, e1 = c.e1, e2 = c.e2, es = c.es;
     // u_{-1} and u_K: neighbour lanes' edge points
     const T sl = edge_left<OPEN>(xl, s[K - 1]), sr = edge_right<OPEN>(xr, s[0]);
-    const T el = edge_left<OPEN>(yl, e[K - 1]), er = edge_right<OPEN>(yr, e[0]);
+    T el = T(0), er = T(0);
+    if constexpr (COMP) {
+        el = edge_left<OPEN>(yl, e[K - 1]);
+        er = edge_right<OPEN>(yr, e[0]);
+    }
+    auto dif = [](T s1, T e1_, T s0, T e0) { return ::ge::dev::dif<COMP>(s1, e1_, s0, e0); };
 
     // advance point j from D_self and D_partner (bp: partner's profile)
     auto upd = [&](int j, T Ds, T Dp, T bp) {
@@ -646,15 +700,19 @@ __device__ __forceinline__ void pair_level(T (&s)[K], T (&e)[K], const T (&b)[K]
                 inc = wl.isL ? alt : inc;
             }
         }
-        // Kahan: the pair absorbs the increment, e keeps what s lost
-        const T y = inc + e[j];
-        const T tt = s[j] + y;
-        e[j] = y - (tt - s[j]);
-        s[j] = tt;
+        if constexpr (COMP) {
+            // Kahan: the pair absorbs the increment, e keeps what s lost
+            const T y = inc + e[j];
+            const T tt = s[j] + y;
+            e[j] = y - (tt - s[j]);
+            s[j] = tt;
+        } else {
+            s[j] = s[j] + inc;
+        }
         if constexpr (WALL) {
             // wall first differences at the new level, accumulated in FP64
             if (ft.left && j == 0) {
-                const double v = (double)s[j] + (double)e[j];
+                const double v = (double)s[j] + (COMP ? (double)e[j] : 0.0);
                 ft.accL = ft.accL + ft.tau * (v - ft.gln) / ft.h;
             }
         }
@@ -679,7 +737,11 @@ __device__ __forceinline__ void pair_level(T (&s)[K], T (&e)[K], const T (&b)[K]
         // with the neighbouring lanes' edge points, so u_{-2} and u_{K+1}
         // are needed too
         const T sl2 = edge_left<OPEN>(xl2, s[K - 2]), sr2 = edge_right<OPEN>(xr2, s[1]);
-        const T el2 = edge_left<OPEN>(yl2, e[K - 2]), er2 = edge_right<OPEN>(yr2, e[1]);
+        T el2 = T(0), er2 = T(0);
+        if constexpr (COMP) {
+            el2 = edge_left<OPEN>(yl2, e[K - 2]);
+            er2 = edge_right<OPEN>(yr2, e[1]);
+        }
         const auto dm2 = dif(sl, el, sl2, el2);                     // d_{-2}
         const auto dm1 = dif(s[0], e[0], sl, el);                   // d_{-1}
         const auto d0 = dif(s[1], e[1], s[0], e[0]);                // d_0
@@ -710,17 +772,21 @@ __device__ __forceinline__ void pair_level(T (&s)[K], T (&e)[K], const T (&b)[K]
 // g_R(t_{m+1}) - g_R(t_m).  The arithmetic is the per-point update's.
 template <typename T> struct Lone { T s, e; };
 
-template <typename T, int K, bool SRC>
+template <typename T, int K, bool SRC, bool COMP = true>
 __device__ __forceinline__ Lone<T> right_lone(const T (&s)[K], const T (&e)[K], const T (&b)[K],
                                               int kS, T xl, T yl, T g_hi, T g_lo, T dgr,
                                               const PairCoef<T> &c, T an)
 {
-    const T sl = from_left(xl, s[K - 1]), el = from_left(yl, e[K - 1]);
-    const T u1 = get_at<T, K>(s, kS, T(0)), e1 = get_at<T, K>(e, kS, T(0));
-    const T u0 = get_at<T, K>(s, kS - 1, sl), e0 = get_at<T, K>(e, kS - 1, el);
-    const T Ds = sd(dif(u1, e1, u0, e0), dif(g_hi, g_lo, u1, e1));
+    const T sl = from_left(xl, s[K - 1]);
+    const T el = COMP ? from_left(yl, e[K - 1]) : T(0);
+    const T u1 = get_at<T, K>(s, kS, T(0));
+    const T e1 = COMP ? get_at<T, K>(e, kS, T(0)) : T(0);
+    const T u0 = get_at<T, K>(s, kS - 1, sl);
+    const T e0 = COMP ? get_at<T, K>(e, kS - 1, el) : T(0);
+    const T Ds = sd(dif<COMP>(u1, e1, u0, e0), dif<COMP>(g_hi, g_lo, u1, e1));
     T inc = c.cs * (Ds + dgr);
     if constexpr (SRC) inc = fmaT(an, c.es * get_at<T, K>(b, kS, T(0)), inc);
+    if constexpr (!COMP) return Lone<T>{u1 + inc, T(0)};
     const T y = inc + e1;
     const T tt = u1 + y;
     return Lone<T>{tt, y - (tt - u1)};
