@@ -308,7 +308,8 @@ constexpr double kWinLaunchUs = 6.0;
 // The longer rods' points decide how they are cut, as a single rod's length
 // does: up to 768000 points block windows, about one per compute unit; then
 // waves of 16 points a lane, 64 levels per pass, and from 6 million on of 32
-// points and 96 levels.
+// points and 96 levels.  The limits were measured at 256 units; where fewer
+// units leave no block window a halo of 65 points, the waves take over.
 constexpr int64_t kWinBlockMax = 768000, kWinWideMin = 6000000;
 
 Windows make_windows(const std::vector<int64_t> &n, int prec, int units)
@@ -350,7 +351,8 @@ Windows make_windows(const std::vector<int64_t> &n, int prec, int units)
             double best = 1e300;
             // rods end in short cores: leave room for some more than one
             // window per unit
-            const int64_t core = (points + units * 7 / 8 - 1) / (units * 7 / 8) / 2 * 2 + 2;
+            const int64_t share = std::max(1, units * 7 / 8);
+            const int64_t core = (points + share - 1) / share / 2 * 2 + 2;
             for (int s = 0; s < ge::kBatchBlockShapes; ++s) {
                 const int64_t halo = (cap(s) - core) / 4 * 2;
                 if (halo < 65) continue;
@@ -364,7 +366,8 @@ Windows make_windows(const std::vector<int64_t> &n, int prec, int units)
                 }
             }
             w.depth = w.halo - 1;
-        } else {
+        }
+        if (w.core == 0) {
             w.kind = ge::kWinWave;
             const bool narrow = points < kWinWideMin || prec == ge::kFP32C;
             w.k = narrow ? 16 : 32;

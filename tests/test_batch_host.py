@@ -1,0 +1,72 @@
+"""The host side of batch plans on the CPU, over a stand-in for the HIP runtime
+(fake_hip.c): plans for devices with few or no compute units, and the order in
+which runs are enqueued."""
+import json
+import os
+import subprocess
+import sys
+
+import pytest
+
+from paper_1310_3422_amd import ge
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+pytestmark = pytest.mark.skipif(not os.path.exists(ge.LIB_PATH), reason="libge.so not built")
+
+# what every child process starts with: the stand-in, then the library
+HEAD = """
+import ctypes, json, sys, threading
+import numpy as np
+fake = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)
+fake.fake_log.restype = ctypes.c_char_p
+from paper_1310_3422_amd import ge
+def table(sizes):
+    n = np.array(sizes, dtype=np.int64)
+    off = np.zeros(n.size + 1, dtype=np.int64)
+    off[1:] = np.cumsum((n + 3) // 4 * 4)
+    one = np.ones(n.size)
+    return n, off, one, 0 * one, 0 * one
+def log():
+    return [l.split() for l in fake.fake_log().decode().splitlines()]
+"""
+
+
+@pytest.fixture(scope="module")
+def fake(tmp_path_factory):
+    so = tmp_path_factory.mktemp("hip") / "fake_hip.so"
+    subprocess.run(["gcc", "-O1", "-shared", "-fPIC", "-o", str(so),
+                    os.path.join(ROOT, "tests", "fake_hip.c"), "-lpthread"], check=True)
+    return str(so)
+
+
+def _child(fake, code):
+    r = subprocess.run([sys.executable, "-c", HEAD + code, fake], cwd=ROOT, capture_output=True,
+                       text=True, timeout=120, env={**os.environ, "GE_TUNE_CACHE": "/nonexistent"})
+    assert r.returncode == 0, (r.returncode, r.stderr[-2000:])
+    return json.loads(r.stdout.splitlines()[-1])
+
+
+@pytest.mark.parametrize("units", [0, 1, 2, 8, 32, 64, 128, 256, 304])
+def test_plans_for_any_number_of_compute_units(fake, units):
+    """Every batch gets a plan (without a device, 0 units: an error), whose
+    windows cover every rod."""
+    out = _child(fake, f"""
+got = []
+for prec in ("fp64", "fp32", "fp32c"):
+    for sizes in ([5000], [4465], [300000], [60000] * 8, [768000], [100, 5000], [800000], [4464]):
+        fake.fake_reset({units}, -1, 0)
+        try:
+            b = ge.Batch(*table(sizes), prec)
+        except ge.GEError as e:
+            got.append([e.status])
+            continue
+        fake.fake_reset({units}, -1, 0)
+        st = ge.lib().ge_solve_batch(b.handle, 1 << 20, 1 << 30, 0, 100, None)
+        got.append([st, len(log())])
+print(json.dumps(got))
+""")
+    if units == 0:
+        assert all(g[0] in (ge.GE_ERR_NOMEM, ge.GE_ERR_HIP) for g in out), out
+    else:
+        assert all(g[0] == ge.GE_OK and g[1] >= 1 for g in out), out
