@@ -347,8 +347,11 @@ ge_status ge_batch_info(ge_batch_t batch, int32_t *ntasks, int32_t *grid,
  * kernels on `stream` and on a stream of its own that it forks from and joins
  * back into it.  Otherwise the first call for a given (u, workspace, parity of
  * step0, nsteps) captures the queue reset and the persistent launch in a
- * hipGraph; later calls with the same key replay it on `stream`.  Errors: GE_ERR_INVALID, GE_ERR_SYNC or GE_ERR_NONFINITE (an
- * earlier run, finished by now, raised it; nothing is enqueued), GE_ERR_HIP. */
+ * hipGraph; later calls with the same key replay it on `stream`.  Host threads
+ * may run one plan at the same time, each with its own u, workspace and stream:
+ * their calls are enqueued one after the other.  Errors: GE_ERR_INVALID,
+ * GE_ERR_SYNC or GE_ERR_NONFINITE (an earlier run, finished by now, raised it;
+ * nothing is enqueued), GE_ERR_HIP. */
 ge_status ge_solve_batch(ge_batch_t batch, void *u, void *workspace,
                          int64_t step0, int64_t nsteps, void *stream);
 

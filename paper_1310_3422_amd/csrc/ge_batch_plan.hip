@@ -426,6 +426,8 @@ struct ge_batch_s {
     hipStream_t cap;        // private stream used only for capture
     hipStream_t side;       // of win's runs, with the events that fork and join it
     hipEvent_t fork, join;
+    std::mutex run_mu;      // held while a run is enqueued: it guards the stream and
+                            // events above and the graphs below
     // instantiated graphs, one per (state, workspace, parity, level count),
     // the least recently used replaced when all slots are taken
     struct Graph {
@@ -778,6 +780,7 @@ ge_status ge_batch_set_wait_polls(ge_batch_t b, int64_t polls)
         return fail(GE_ERR_INVALID, "ge_batch_set_wait_polls: polls = %lld out of range",
                     (long long)polls);
     if (polls != b->wait_polls) {
+        std::lock_guard<std::mutex> lk(b->run_mu);
         drop_graphs(b);
         b->wait_polls = (int)polls;
     }
@@ -832,8 +835,10 @@ ge::BatchArgs run_args(const ge_batch_s *b, void *u, void *work, int64_t step0, 
 
 // One run of the split into windows: the rods that one wave or window holds on
 // the plan's side stream beside the passes, forked from and joined back into
-// the caller's stream.  Launched as they are: a graph of these few kernels took
-// 0.2-1.1 ms to instantiate (for every new state) and saved nothing after.
+// the caller's stream, also when a launch between the two fails.  Launched as
+// they are: a graph of these few kernels took 0.2-1.1 ms to instantiate (for
+// every new state) and saved nothing after.  The plan's run_mu is held: the
+// side stream waits for the fork that this call records.
 hipError_t run_windows(ge_batch_s *b, void *u, void *work, int parity, int64_t nsteps,
                        hipStream_t main)
 {
@@ -851,40 +856,50 @@ hipError_t run_windows(ge_batch_s *b, void *u, void *work, int parity, int64_t n
     const int whole = w.nwide + w.nnarrow + w.ntiny;
     const bool beside = w.npass > 0 ? whole > 0 : w.nwide > 0 && w.nnarrow + w.ntiny > 0;
     hipStream_t side = beside ? b->side : main, rest = w.npass > 0 ? side : main;
-    hipError_t e = hipSuccess;
-    if (beside) {
-        if ((e = hipEventRecord(b->fork, main)) != hipSuccess) return e;
-        if ((e = hipStreamWaitEvent(side, b->fork, 0)) != hipSuccess) return e;
-    }
-    a.list = b->d_win + w.ntiny;
-    a.count = w.nwide;
-    e = ge::launch_batch_windows(b->prec, ge::kWinBlock, ge::kBatchNarrowK + 1, a, side);
-    if (e != hipSuccess) return e;
-    a.list += w.nwide;
-    a.count = w.nnarrow;
-    e = ge::launch_batch_windows(b->prec, ge::kWinBlock, ge::kBatchNarrowK, a, rest);
-    if (e != hipSuccess) return e;
-    a.list = b->d_win;
-    a.count = w.ntiny;
-    e = ge::launch_batch_windows(b->prec, ge::kWinTiny, 4, a, rest);
-    if (e != hipSuccess) return e;
-    if (beside && (e = hipEventRecord(b->join, side)) != hipSuccess) return e;
-    if (w.npass > 0) {
+    auto whole_rods = [&]() {
+        a.list = b->d_win + w.ntiny;
+        a.count = w.nwide;
+        hipError_t e = ge::launch_batch_windows(b->prec, ge::kWinBlock, ge::kBatchNarrowK + 1, a, side);
+        if (e != hipSuccess) return e;
+        a.list += w.nwide;
+        a.count = w.nnarrow;
+        e = ge::launch_batch_windows(b->prec, ge::kWinBlock, ge::kBatchNarrowK, a, rest);
+        if (e != hipSuccess) return e;
+        a.list = b->d_win;
+        a.count = w.ntiny;
+        return ge::launch_batch_windows(b->prec, ge::kWinTiny, 4, a, rest);
+    };
+    auto passes = [&]() {
         a.list = b->d_win + whole;
         a.count = w.npass;
         a.core = w.core;
         a.halo = w.halo;
-        int64_t passes = (nsteps + w.depth - 1) / w.depth, done = 0;
-        passes += passes & 1;                // the result lands in u
-        for (int64_t p = 0; p < passes; ++p) {
+        int64_t n = (nsteps + w.depth - 1) / w.depth, done = 0;
+        n += n & 1;                          // the result lands in u
+        for (int64_t p = 0; p < n; ++p) {
             a.pass = (int32_t)(p & 1);
             a.level0 = parity + done;
-            a.nlev = (int32_t)(nsteps / passes + (p < nsteps % passes ? 1 : 0));
-            if ((e = ge::launch_batch_windows(b->prec, w.kind, w.k, a, main)) != hipSuccess) return e;
+            a.nlev = (int32_t)(nsteps / n + (p < nsteps % n ? 1 : 0));
+            const hipError_t e = ge::launch_batch_windows(b->prec, w.kind, w.k, a, main);
+            if (e != hipSuccess) return e;
             done += a.nlev;
         }
+        return hipSuccess;
+    };
+    if (!beside) {
+        const hipError_t e = whole_rods();
+        return e == hipSuccess && w.npass > 0 ? passes() : e;
     }
-    return beside ? hipStreamWaitEvent(main, b->join, 0) : hipSuccess;
+    hipError_t e = hipEventRecord(b->fork, main);
+    if (e != hipSuccess || (e = hipStreamWaitEvent(side, b->fork, 0)) != hipSuccess) return e;
+    e = whole_rods();
+    const hipError_t joined = hipEventRecord(b->join, side);
+    if (e == hipSuccess && w.npass > 0) e = passes();
+    if (joined == hipSuccess) {
+        const hipError_t waits = hipStreamWaitEvent(main, b->join, 0);
+        return e != hipSuccess ? e : waits;
+    }
+    return e != hipSuccess ? e : joined;
 }
 
 // Checks shared by both run entry points; reports what earlier runs raised.
@@ -939,6 +954,7 @@ ge_status ge_solve_batch(ge_batch_t b, void *u, void *workspace, int64_t step0, 
         return GE_OK;
     hipStream_t st = static_cast<hipStream_t>(stream);
     const int parity = (int)(step0 & 1);
+    std::lock_guard<std::mutex> lk(b->run_mu);
     if (b->win.on) {
         const hipError_t e = run_windows(b, u, workspace, parity, nsteps, st);
         return e == hipSuccess ? GE_OK : hip_fail(e, "ge_solve_batch: launch");

@@ -70,3 +70,49 @@ print(json.dumps(got))
         assert all(g[0] in (ge.GE_ERR_NOMEM, ge.GE_ERR_HIP) for g in out), out
     else:
         assert all(g[0] == ge.GE_OK and g[1] >= 1 for g in out), out
+
+
+def test_two_threads_run_one_plan(fake):
+    """Two host threads that run one plan on streams of their own: whatever the
+    side stream waits for, the calling thread's stream recorded last, and the
+    caller's stream waits for what the side stream recorded last."""
+    events = _child(fake, """
+b = ge.Batch(*table([100, 5000]), "fp32")
+fake.fake_reset(256, -1, 300)
+st = [None, None]
+def run(i):
+    st[i] = ge.lib().ge_solve_batch(b.handle, 1 << 20, 1 << 30, 0, 100, (1 + i) << 8)
+ts = [threading.Thread(target=run, args=(i,)) for i in range(2)]
+for t in ts: t.start()
+for t in ts: t.join()
+assert st == [0, 0], st
+print(json.dumps(log()))
+""")
+    main = {str(256): 0, str(512): 1}
+    last, waits = {}, 0
+    for what, stream, event, thread in events:
+        if what == "record":
+            last[event] = (stream, thread)
+        elif what == "wait":
+            waits += 1
+            assert last[event][1] == thread, (event, thread, last[event], events)
+            # the side stream waits for the thread's own main stream, and back
+            assert (stream in main) != (last[event][0] in main), events
+    assert waits == 4, events
+
+
+@pytest.mark.parametrize("fail_at", range(4))
+def test_a_failed_launch_still_joins_the_side_stream(fake, fail_at):
+    """A launch that fails after the fork: the error is returned, and the
+    caller's stream waits for what the side stream was given."""
+    status, events = _child(fake, f"""
+b = ge.Batch(*table([100, 5000, 3000]), "fp64")
+fake.fake_reset(256, {fail_at}, 0)
+st = ge.lib().ge_solve_batch(b.handle, 1 << 20, 1 << 30, 0, 100, 256)
+print(json.dumps([st, log()]))
+""")
+    assert status == ge.GE_ERR_HIP, status
+    assert any(e[0] == "failed" for e in events), events
+    assert events[-1][:2] == ["wait", "256"], events
+    joined = [e for e in events if e[0] == "record" and e[2] == events[-1][2]]
+    assert len(joined) == 1 and joined[0][1] != "256", events
