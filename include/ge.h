@@ -313,7 +313,8 @@ int64_t ge_batch_state_elems(ge_batch_t batch);
  * plus the second level buffers of the rods swept in passes from byte 256 on
  * (each rod's points rounded up to 64 elements, twice for GE_FP32_COMP): rods
  * above 4464 points when the plan splits into windows, else rods above the
- * on-chip limit. */
+ * on-chip limit.  The runs cannot see how large a workspace is: ask here, for
+ * every plan. */
 size_t ge_batch_workspace_bytes(ge_batch_t batch);
 
 /* Number of polls (each a short sleep, about 30 ns) a wave's wait for a
@@ -435,7 +436,8 @@ ge_status ge_nn_train_step(ge_nn_t net, const float *u, const float *u64, const 
  * by 64 levels of the GE sweep from the same input, with `ge`: an FP64 batch
  * plan (ge_batch_plan) of exactly these rods -- batch rods of width points,
  * in order, with the mesh ratios that r (device, batch floats) holds rounded
- * to FP32 and zero walls -- and its workspace ge_ws.  A rod whose relative
+ * to FP32 and zero walls -- and its workspace ge_ws (ge_batch_workspace_bytes
+ * of that plan; more than 256 from 4465 points on).  A rod whose relative
  * L2 distance ||u_net - u_GE|| / ||u_GE|| exceeds tol (or is not a number)
  * restarts the window from its state at the window's start and takes the
  * whole window by the GE sweep (FP64, rounded to FP32 at the end); the

@@ -451,10 +451,14 @@ class Net:
     def advance(self, ge_batch, ge_ws, u, r, njumps, step0=0, check=8, tol=1e-4,
                 accepted=None, fallbacks=None, last_err=None, stream=None):
         """Re-checked surrogate stepping (ge_nn_advance); returns the number
-        of rod-windows that fell back to the GE sweep."""
+        of rod-windows that fell back to the GE sweep.  ge_ws: the batch
+        plan's workspace (``ge_batch.new_workspace()``)."""
         b = r.numel()
         self._check(u, b * self.width, "u")
         self._check(r, b, "r")
+        if not ge_ws.is_cuda or ge_ws.numel() * ge_ws.element_size() < ge_batch.workspace_bytes:
+            raise ValueError(f"ge_ws must be a CUDA tensor of at least "
+                             f"{ge_batch.workspace_bytes} bytes")
         nfb = _i64(0)
         _check_status(lib().ge_nn_advance(
             self.handle, ge_batch.handle, _ptr(ge_ws), _ptr(u), _ptr(r), b, int(step0),
