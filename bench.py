@@ -493,8 +493,7 @@ def moving_wall_precision_extra(torch, stream, ge, inputs, prec):
 
 def batch_extra(torch, stream, ge, inputs, prec, sample_errors=True):
     """The 4096-rod batch (N log-uniform in [256, 65536], r in [0.25, 4],
-    walls in [-1, 1], seed 3), 2000 levels, one persistent graph-captured
-    launch; rods above the on-chip limit of the form run as long-rod tasks.
+    walls in [-1, 1], seed 3), 2000 levels, split into windows over the chip.
     Per-rod rel-L2 against the oracle (started from the same rounded values;
     the compensated pair against the extended-precision oracle) on the
     largest and smallest rods and ten random ones."""
@@ -513,10 +512,9 @@ def batch_extra(torch, stream, ge, inputs, prec, sample_errors=True):
     out = {"roofline": {"bound": "alu", "achieved": round(bups * fpu / 1e12, 2),
                         "peak": PEAK_TF[prec], "unit": "TFLOP/s",
                         "frac": round(bups * fpu / 1e12 / PEAK_TF[prec], 4)},
-           "updates_per_s": bups, "ms_per_run": gb / 3 * 1e3, "tasks": info["ntasks"],
+           "updates_per_s": bups, "ms_per_run": gb / 3 * 1e3, "windows": info["ntasks"],
            "workgroups": info["grid"], "rods": rb.nrods, "points": int(rb.n.sum()),
-           "levels": 2000,
-           "long_rod_tasks": int((rb.n > (65536 if prec == "fp32" else 32768)).sum())}
+           "levels": 2000}
     if sample_errors:
         with torch.cuda.stream(stream):
             ub.copy_(u0)

@@ -282,7 +282,9 @@ typedef struct {
                              /* points-per-lane choice on this device now and */
                              /* store it (file $GE_TUNE_CACHE, default        */
                              /* ~/.cache/libge/batch_tune.txt); 0: use the    */
-                             /* stored measurement, or built-in defaults      */
+                             /* stored measurement, or built-in defaults.     */
+                             /* For the persistent form: with sync = 0 only   */
+                             /* ge_solve_batch_static uses it                 */
     int32_t sync;            /* how the waves of a rod exchange edge values:  */
                              /* 0 = library choice (windows), 1 = every level,*/
                              /* at a workgroup barrier, 2 = each level, a wave*/
@@ -335,9 +337,11 @@ ge_status ge_batch_set_wait_polls(ge_batch_t batch, int64_t polls);
  * Errors: GE_ERR_INVALID (NULL batch), GE_ERR_HIP. */
 ge_status ge_batch_check(ge_batch_t batch, void *stream);
 
-/* The plan's shape: number of tasks, resident workgroups, the planner's
- * estimate of the time of one level in microseconds, and (if rod_k is not
- * NULL, host, nrods entries) the points per lane chosen for each rod. */
+/* The shape of what ge_solve_batch runs: number of tasks, workgroups, the
+ * planner's estimate of the time of one level in microseconds, and (if rod_k
+ * is not NULL, host, nrods entries) the points per lane chosen for each rod.
+ * Split into windows: the windows and the workgroups that one pass over the
+ * batch launches; in the persistent form: its tasks and resident workgroups. */
 ge_status ge_batch_info(ge_batch_t batch, int32_t *ntasks, int32_t *grid,
                         double *est_us_per_level, int32_t *rod_k);
 

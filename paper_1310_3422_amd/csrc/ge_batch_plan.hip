@@ -931,8 +931,15 @@ ge_status ge_batch_info(ge_batch_t b, int32_t *ntasks, int32_t *grid, double *es
 {
     if (!b)
         return fail(GE_ERR_INVALID, "ge_batch_info: batch is NULL");
-    if (ntasks) *ntasks = b->ntasks;
-    if (grid) *grid = b->grid;
+    // of the form that ge_solve_batch runs
+    const Windows &w = b->win;
+    const int whole = w.nwide + w.nnarrow;
+    auto groups = [](int waves) { return (waves + 3) / 4; };   // four single waves a workgroup
+    if (ntasks) *ntasks = w.on ? whole + w.ntiny + w.npass : b->ntasks;
+    if (grid)
+        *grid = !w.on ? b->grid
+                      : whole + groups(w.ntiny) +
+                            (w.kind == ge::kWinBlock ? w.npass : groups(w.npass));
     if (est_us_per_level) *est_us_per_level = b->est_us;
     if (rod_k)
         for (int64_t i = 0; i < b->nrods; ++i) rod_k[i] = b->rod_k[i];

@@ -90,7 +90,7 @@ print(json.dumps(log()))
 """)
     main = {str(256): 0, str(512): 1}
     last, waits = {}, 0
-    for what, stream, event, thread in events:
+    for what, stream, event, thread, _ in events:
         if what == "record":
             last[event] = (stream, thread)
         elif what == "wait":
@@ -116,3 +116,27 @@ print(json.dumps([st, log()]))
     assert events[-1][:2] == ["wait", "256"], events
     joined = [e for e in events if e[0] == "record" and e[2] == events[-1][2]]
     assert len(joined) == 1 and joined[0][1] != "256", events
+
+
+@pytest.mark.parametrize("sizes", [[100, 5000], [7] * 9, [4464, 4465, 3000, 1], [400000, 500000, 20]])
+def test_info_describes_the_form_that_runs(fake, sizes):
+    """ntasks and grid are those of the windows: one per rod of up to 4464
+    points, the others' windows as many as rod_k and the launches' grids say."""
+    info, grids = _child(fake, f"""
+sizes = {sizes}
+b = ge.Batch(*table(sizes), "fp32")
+fake.fake_reset(256, -1, 0)
+ge.lib().ge_solve_batch(b.handle, 1 << 20, 1 << 30, 0, 1, 256)
+i = b.info()
+print(json.dumps([[i["ntasks"], i["grid"]], [int(e[4]) for e in log() if e[0] == "launch"]]))
+""")
+    whole = [n for n in sizes if n <= 4464]
+    tiny = sum(n < 256 for n in whole)
+    assert info[0] >= len(sizes)
+    if len(whole) == len(sizes):
+        assert info == [len(sizes), len(sizes) - tiny + (tiny + 3) // 4]
+    # a launch's grid is its workgroups rounded up to 8; a pass of one level is
+    # followed by one of none
+    if len(whole) < len(sizes):
+        grids = grids[:-1]
+    assert info[1] <= sum(grids) < info[1] + 8 * len(grids), (info, grids)
