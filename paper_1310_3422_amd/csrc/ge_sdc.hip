@@ -72,6 +72,21 @@ __device__ __forceinline__ void sdc_pair(T um, T u0, T u1, T u2, const SdcCoef<T
     n1 = fmaT(k.c2, Da, fmaT(k.c1, Db, u1));
 }
 
+// wo - 2 w, rounded once.  w and wo are both needed afterwards, and the
+// compiler's choice of instruction, the one that adds to its destination, copies
+// wo first: up to k = 8 it is taken as the one with a destination of its own
+// (2^24 points, 192 levels: k = 2 814 -> 695 us, k = 4 617 -> 564).  At k = 16,
+// whose chains bind, the copy is free and the compiler's schedule the better
+// one (631 us against 639).
+template <int K>
+__device__ __forceinline__ double minus_twice(double w, double wo)
+{
+    if constexpr (K >= 32) return fmaT(-2.0, w, wo);
+    double x;
+    asm("v_fma_f64 %0, %1, -2.0, %2" : "=v"(x) : "v"(w), "v"(wo));
+    return x;
+}
+
 // One Saul'yev step: (r v + (1-r) w + r wo) / (1+r), with v the new value
 // of the sweep predecessor and wo the old value of the other neighbour, as
 // c v + t in three instructions of which one waits for v.
@@ -84,10 +99,10 @@ __device__ __forceinline__ void sdc_pair(T um, T u0, T u1, T u2, const SdcCoef<T
 // (k = 16, r = 2 0.15; the geometric mean over all 0.07), and the same near
 // 2e-16 at r = 1 (1.0 to 1.3), where ca is 0.  FP32 keeps ca w + c wo: results
 // stay within the differences of FP32 from what they have been.
-template <typename T>
+template <int K, typename T>
 __device__ __forceinline__ T sweep(T v, T w, T wo, const SdcCoef<T> &k)
 {
-    if constexpr (sizeof(T) == 8) return fmaT(k.c, v, fmaT(k.c, fmaT(T(-2), w, wo), w));
+    if constexpr (sizeof(T) == 8) return fmaT(k.c, v, fmaT(k.c, minus_twice<K>(w, wo), w));
     else return fmaT(k.c, v, fmaT(k.ca, w, k.c * wo));
 }
 
@@ -111,7 +126,7 @@ __device__ __forceinline__ void sweep_run(T (&s)[K], T v, const SdcCoef<T> &k, O
 #pragma unroll
     for (int j = 0; j < len; ++j) {
         const int e = FROM + j * step;
-        v = sweep(v, s[e], other(e), k);
+        v = sweep<K>(v, s[e], other(e), k);
         s[e] = v;
     }
 }
@@ -202,7 +217,7 @@ __device__ __forceinline__ void sdc_level(T (&s)[K], const SdcCoef<T> &cf, bool 
         sdc_pair(s[K - 3], s[K - 2], s[K - 1], oR, cf, pA, pB);
         if (last) {
             // node M-1 by scheme B against the wall, node M the wall
-            pA = sweep(gr_new, s[K - 2], s[K - 3], cf);
+            pA = sweep<K>(gr_new, s[K - 2], s[K - 3], cf);
             pB = gr_new;
         }
         edge.post_left(lane, buf, pB);
@@ -238,7 +253,7 @@ __device__ __forceinline__ void sdc_level(T (&s)[K], const SdcCoef<T> &cf, bool 
         // element K-1 is the first node of the next SDC, the end of its
         // scheme-B sweep: it needs that lane's new element 0
         const T r0 = from_right(edge.take_right(buf), s[0]);
-        const T nk = sweep(r0, o_last, o_prev, cf);
+        const T nk = sweep<K>(r0, o_last, o_prev, cf);
         s[K - 1] = last ? gr_new : nk;
     }
 }
