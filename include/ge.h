@@ -132,7 +132,8 @@ typedef struct {
                         /* the library's choice of waves, depth and schedule  */
                         /* goes by the length: the longest rods 8 waves at 48 */
                         /* levels (4 at 40, schedule 2, for GE_FP64, k = 16), */
-                        /* shorter ones fewer waves and up to 96 levels; with */
+                        /* shorter ones fewer waves and up to 96 levels (calls */
+                        /* of few levels: one wave); with                     */
                         /* some of the three given, schedule 2 for GE_FP64    */
                         /* with k = 16 from 64 windows on, 24 levels in       */
                         /* single-wave windows (20 otherwise).                */

@@ -264,6 +264,7 @@ struct ge_plan_s {
     bool persistent;  // multi-tile launches by the persistent single-wave kernel
     bool block;    // windows of overlapping waves (launch_block)
     int sdc;       // sub-domain width k >= 2 (the sub-domain scheme), or 0
+    int sdc_short; // launches of at most so many levels take single-wave windows
     double g_left, g_right;
     const void *src_b;
     ge::SchemeCoef sc;
@@ -381,6 +382,29 @@ SdcShape sdc_shape(int prec, int k, int64_t nsdc)
     return wide64 ? narrow : k == 2 ? SdcShape{8, 64, true} : SdcShape{8, 96, false};
 }
 
+// Most levels a launch of a call may have for single-wave windows, persistent
+// and with the halo of the call's own levels, to beat the shape above: a call of
+// few levels is bound by its loads and its launches, and windows laid out for
+// more levels a launch hold several waves to one barrier for nothing.  us per
+// call, those windows against the shape's, at half and at twice the limit:
+//   rods that do not fill the chip (two or four waves, 64 levels): 24 (FP64 k =
+//   16, 2^20 points, calls of 24 and 96 levels 16.1 against 20.0, 32.8 against
+//   32.4), 32 while the windows of 32 levels are at most three waves to a SIMD,
+//   FP64 with k = 16 one (FP32 k = 4, 2^18, 64 levels 13.0 against 18.8; 2^20
+//   21.7 against 18.5);
+//   eight waves, 96 levels: 16 (FP64 k = 8, 2^22, 16 and 64 levels 30.0 against
+//   42.3, 75.5 against 72.5);
+//   the widest: 8 (FP64 k = 8, 2^24, 8 levels 65 against 84, 32 levels 1.08
+//   times as long at k = 4).
+int sdc_short_levels(int prec, int k, int64_t nsdc, const SdcShape &s)
+{
+    if (s.waves == 1) return 0;
+    if (sdc_fills_wide(prec, k, nsdc, 0)) return 8;
+    if (s.waves == 8) return 16;
+    const int64_t w = sdc_launch_waves(nsdc, k, 1, 32);
+    return w > 0 && w <= (prec == ge::kFP64 && k == 16 ? 1 : 3) * 1024 ? 32 : 24;
+}
+
 // The same where the caller gives some of the three.  The persistent form
 // is the library's own choice there for FP64 with k = 16 alone (one couple
 // fills 32 FP64 registers per node pair: two waves per SIMD leave a
@@ -460,6 +484,7 @@ ge_status plan_sdc(ge_plan_t *out, const ge_desc *d)
     // for k = 16 a persistent launch that nobody asked for wants 64 tiles
     p->persistent = !single && p->ntiles >= 3 && shape.persistent && depth <= ge::kSdcMaxLevels &&
                     ((automatic && k != 16) || d->schedule == 2 || p->ntiles >= 64);
+    p->sdc_short = automatic && !single ? sdc_short_levels(prec, k, nsdc, shape) : 0;
     const double r = d->r;
     p->h = 1.0 / (double)(p->n + 1);
     p->tau = r * p->h * p->h;
@@ -728,11 +753,13 @@ ge_status ge_step_n(ge_plan_t plan, void *u, void *workspace, int64_t step0, int
     // the plan's second stream for split launches, if it holds one
     const ge::SideStream *side = plan->side_state == 1 ? &plan->side : nullptr;
     // one launch of whichever kernel the plan runs
+    int sdc_waves = plan->waves;
+    bool sdc_persistent = plan->persistent;
     auto launch = [&](const ge::TileArgs &la) {
         if (plan->sdc)
-            return plan->persistent && la.ntiles >= 3
-                       ? ge::launch_sdc_persistent(plan->prec, plan->sdc, plan->waves, la, st)
-                       : ge::launch_sdc(plan->prec, plan->sdc, plan->waves, la, st);
+            return sdc_persistent && la.ntiles >= 3
+                       ? ge::launch_sdc_persistent(plan->prec, plan->sdc, sdc_waves, la, st)
+                       : ge::launch_sdc(plan->prec, plan->sdc, sdc_waves, la, st);
         if (plan->block)
             return ge::launch_block(plan->prec, plan->tile, plan->waves, src, la, st);
         if (plan->persistent && !plan->single)
@@ -768,9 +795,15 @@ ge_status ge_step_n(ge_plan_t plan, void *u, void *workspace, int64_t step0, int
     if (plan->sdc) {
         // a call of fewer levels than the plan's depth gets the halo of its
         // own (FP64, k = 8, 3.9e6 points, 24 levels in windows for 96: 38 us
-        // against 46 with the plan's halo)
-        a.halo = std::min(plan->halo, sdc_halo((int)(base + (extra ? 1 : 0)), plan->sdc));
-        a.core = 64 * plan->waves - 2 * a.halo;
+        // against 46 with the plan's halo), one of few levels narrow windows
+        const int lev = (int)(base + (extra ? 1 : 0));
+        if (lev <= plan->sdc_short) {
+            sdc_waves = 1;
+            sdc_persistent = true;
+        }
+        a.halo = sdc_halo(lev, plan->sdc);
+        if (sdc_waves == plan->waves) a.halo = std::min(plan->halo, a.halo);
+        a.core = 64 * sdc_waves - 2 * a.halo;
         a.ntiles = (a.nsdc + a.core - 1) / a.core;
     }
     void *bufs[2] = {u, workspace};

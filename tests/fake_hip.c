@@ -37,13 +37,15 @@ static int tid(void)
     if (!me) me = ++nthreads;
     return me;
 }
-/* one line: what, stream, event (0: none), thread, workgroups; with `mu` held */
-static void line(const char *what, const void *stream, const void *event, unsigned groups)
+/* one line: what, stream, event (0: none), thread, workgroups and their threads;
+ * with `mu` held */
+static void line(const char *what, const void *stream, const void *event, unsigned groups,
+                 unsigned threads)
 {
     if (used < sizeof text - 128)
-        used += (size_t)sprintf(text + used, "%s %lu %lu %d %u\n", what,
+        used += (size_t)sprintf(text + used, "%s %lu %lu %d %u %u\n", what,
                                 (unsigned long)(uintptr_t)stream, (unsigned long)(uintptr_t)event,
-                                tid(), groups);
+                                tid(), groups, threads);
 }
 static void *handle(void)
 {
@@ -57,7 +59,7 @@ int hipEventRecord(void *event, void *stream)
 {
     static const void *first;
     pthread_mutex_lock(&mu);
-    line("record", stream, event, 0);
+    line("record", stream, event, 0, 0);
     if (pause_ms) {
         /* the first record waits for another thread's record of the same event */
         if (!first) {
@@ -81,16 +83,16 @@ int hipStreamWaitEvent(void *stream, void *event, unsigned flags)
 {
     (void)flags;
     pthread_mutex_lock(&mu);
-    line("wait", stream, event, 0);
+    line("wait", stream, event, 0, 0);
     pthread_mutex_unlock(&mu);
     return 0;
 }
 int hipLaunchKernel(const void *f, dim3 grid, dim3 block, void **args, size_t shared, void *stream)
 {
-    (void)f, (void)block, (void)args, (void)shared;
+    (void)f, (void)args, (void)shared;
     pthread_mutex_lock(&mu);
     const int failed = launches++ == fail_at;
-    line(failed ? "failed" : "launch", stream, NULL, grid.x);
+    line(failed ? "failed" : "launch", stream, NULL, grid.x, block.x);
     pthread_mutex_unlock(&mu);
     return last_error = failed ? 719 : 0;
 }
@@ -141,7 +143,7 @@ int hipMemcpyAsync(void *d, const void *s, size_t n, int k, void *stream)
 {
     (void)d, (void)s, (void)n, (void)k;
     pthread_mutex_lock(&mu);
-    line("copy", stream, NULL, 0);
+    line("copy", stream, NULL, 0, 0);
     pthread_mutex_unlock(&mu);
     return 0;
 }

@@ -1,57 +1,25 @@
 """The host side of batch plans on the CPU, over a stand-in for the HIP runtime
 (fake_hip.c): plans for devices with few or no compute units, and the order in
 which runs are enqueued."""
-import json
 import os
-import subprocess
-import sys
 
 import pytest
 
+from hip_stand_in import child
 from paper_1310_3422_amd import ge
-
-ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 pytestmark = pytest.mark.skipif(not os.path.exists(ge.LIB_PATH), reason="libge.so not built")
 
-# what every child process starts with: the stand-in, then the library
-HEAD = """
-import ctypes, json, sys, threading
-import numpy as np
-fake = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)
-fake.fake_log.restype = ctypes.c_char_p
-from paper_1310_3422_amd import ge
-def table(sizes):
-    n = np.array(sizes, dtype=np.int64)
-    off = np.zeros(n.size + 1, dtype=np.int64)
-    off[1:] = np.cumsum((n + 3) // 4 * 4)
-    one = np.ones(n.size)
-    return n, off, one, 0 * one, 0 * one
-def log():
-    return [l.split() for l in fake.fake_log().decode().splitlines()]
-"""
-
-
 @pytest.fixture(scope="module")
 def fake(tmp_path_factory):
-    so = tmp_path_factory.mktemp("hip") / "fake_hip.so"
-    subprocess.run(["gcc", "-O1", "-shared", "-fPIC", "-o", str(so),
-                    os.path.join(ROOT, "tests", "fake_hip.c"), "-lpthread"], check=True)
-    return str(so)
-
-
-def _child(fake, code):
-    r = subprocess.run([sys.executable, "-c", HEAD + code, fake], cwd=ROOT, capture_output=True,
-                       text=True, timeout=120, env={**os.environ, "GE_TUNE_CACHE": "/nonexistent"})
-    assert r.returncode == 0, (r.returncode, r.stderr[-2000:])
-    return json.loads(r.stdout.splitlines()[-1])
+    return tmp_path_factory.mktemp("hip")
 
 
 @pytest.mark.parametrize("units", [0, 1, 2, 8, 32, 64, 128, 256, 304])
 def test_plans_for_any_number_of_compute_units(fake, units):
     """Every batch gets a plan (without a device, 0 units: an error), whose
     windows cover every rod."""
-    out = _child(fake, f"""
+    out = child(fake, f"""
 got = []
 for prec in ("fp64", "fp32", "fp32c"):
     for sizes in ([5000], [4465], [300000], [60000] * 8, [768000], [100, 5000], [800000], [4464]):
@@ -76,7 +44,7 @@ def test_two_threads_run_one_plan(fake):
     """Two host threads that run one plan on streams of their own: whatever the
     side stream waits for, the calling thread's stream recorded last, and the
     caller's stream waits for what the side stream recorded last."""
-    events = _child(fake, """
+    events = child(fake, """
 b = ge.Batch(*table([100, 5000]), "fp32")
 fake.fake_reset(256, -1, 300)
 st = [None, None]
@@ -90,7 +58,7 @@ print(json.dumps(log()))
 """)
     main = {str(256): 0, str(512): 1}
     last, waits = {}, 0
-    for what, stream, event, thread, _ in events:
+    for what, stream, event, thread, _, _ in events:
         if what == "record":
             last[event] = (stream, thread)
         elif what == "wait":
@@ -105,7 +73,7 @@ print(json.dumps(log()))
 def test_a_failed_launch_still_joins_the_side_stream(fake, fail_at):
     """A launch that fails after the fork: the error is returned, and the
     caller's stream waits for what the side stream was given."""
-    status, events = _child(fake, f"""
+    status, events = child(fake, f"""
 b = ge.Batch(*table([100, 5000, 3000]), "fp64")
 fake.fake_reset(256, {fail_at}, 0)
 st = ge.lib().ge_solve_batch(b.handle, 1 << 20, 1 << 30, 0, 100, 256)
@@ -122,7 +90,7 @@ print(json.dumps([st, log()]))
 def test_info_describes_the_form_that_runs(fake, sizes):
     """ntasks and grid are those of the windows: one per rod of up to 4464
     points, the others' windows as many as rod_k and the launches' grids say."""
-    info, grids = _child(fake, f"""
+    info, grids = child(fake, f"""
 sizes = {sizes}
 b = ge.Batch(*table(sizes), "fp32")
 fake.fake_reset(256, -1, 0)
