@@ -422,8 +422,25 @@ template <typename T> Dir<T> dir(double r)
                   (T)(r * r / (1.0 + 2.0 * r)), (T)(r / (1.0 + r))};
 }
 
+// The launches of a call whose launches take at most `depth` levels (an even
+// number leaves the result in u; the levels are spread evenly over them), and
+// the halo of the longest.
+struct Launches {
+    int64_t n;
+    int levels, halo;
+};
+Launches launches_of(int64_t nsteps, int depth)
+{
+    Launches l;
+    l.n = (nsteps + depth - 1) / depth;
+    if ((l.n & 1) && nsteps > l.n) ++l.n;
+    l.levels = (int)((nsteps + l.n - 1) / l.n);
+    l.halo = (l.levels + 2) / 2 * 2;
+    return l;
+}
+
 // Rows per wave and levels per launch: the pair with the least estimated time
-// of a level, in us.  One window per compute unit takes `one` for a level,
+// of the call, in us.  One window per compute unit takes `one` for a level,
 // many at once `many` each; half of the grid's traffic at 5.8 TB/s (a grid of
 // 4096 x 4096 FP64 and its copy just exceed the 256 MB cache) is not hidden,
 // and a launch costs 2.4 us.  Fitted to 96 levels of 196 x 578 to 4096 x 4096
@@ -432,6 +449,8 @@ template <typename T> Dir<T> dir(double r)
 // more rows and fewer levels (4096 x 4096 FP64 8 rows, 6 or 8 levels 1.00 ms,
 // 12 levels 1.16; 2048 x 2048 FP32 16 rows 0.23 ms, 8 rows 0.27).  FP64 holds at
 // most 8 rows a lane: 16 spill at two workgroups per unit (1.10 ms at best).
+// A launch has the halo of the call's own levels, so a call of one level (8192
+// x 1024 FP64) recomputes 1.10 points a point and not the 1.72 of eight levels.
 struct Shape {
     int rows;
     double one64, many64, one32, many32;
@@ -442,27 +461,32 @@ constexpr int kDepths[] = {1, 2, 4, 6, 8, 10, 12, 16, 20, 24};
 constexpr double kUnits = 256.0, kBytesPerUs = 5.8e6, kLaunchUs = 2.4;
 
 struct Choice {
-    int rows, depth, halo;
+    int rows;
+    Launches l;
 };
 
 Choice choose(const Grid2dArgs &g, bool f64)
 {
-    Choice best{4, 4, 6};
+    Choice best{4, launches_of(g.nsteps, 4)};
     double best_us = 1e300;
     for (const Shape &s : kShapes) {
         const double one = f64 ? s.one64 : s.one32, many = f64 ? s.many64 : s.many32;
         const int rows = kNW * s.rows;
         if (one == 0.0 || (s.rows > 4 && g.ny < rows)) continue;
         for (int d : kDepths) {
-            const int halo = (d + 2) / 2 * 2;
-            if ((g.depth != 0 && d != g.depth) || 2 * halo >= rows) continue;
-            const double cx = kCols - 2 * halo, cy = rows - 2 * halo;
+            if (g.depth != 0 && d != g.depth) continue;
+            const Launches l = launches_of(g.nsteps, d);
+            if (2 * l.halo >= rows) continue;
+            const double cx = kCols - 2 * l.halo, cy = rows - 2 * l.halo;
             const double tiles = std::ceil(g.nx / cx) * std::ceil(g.ny / cy);
             const double mem = 2.0 * g.nx * g.ny * (f64 ? 8 : 4) / kBytesPerUs;
-            const double t = std::max(one, many * std::ceil(tiles / kUnits)) + (0.5 * mem + kLaunchUs) / d;
+            const double level = std::max(one, many * std::ceil(tiles / kUnits));
+            // an odd number of launches is followed by a copy
+            const double t = l.n * (level * l.levels + 0.5 * mem + kLaunchUs) +
+                             (l.n & 1) * (mem + kLaunchUs);
             if (t < best_us) {
                 best_us = t;
-                best = Choice{s.rows, d, halo};
+                best = Choice{s.rows, l};
             }
         }
     }
@@ -475,9 +499,9 @@ hipError_t run(const Grid2dArgs &g, const Choice &c, hipStream_t stream)
     Block2dArgs<T> a{};
     a.nx = (int)g.nx;
     a.ny = (int)g.ny;
-    a.halo = c.halo;
-    a.cx = kCols - 2 * c.halo;
-    a.cy = kNW * R - 2 * c.halo;
+    a.halo = c.l.halo;
+    a.cx = kCols - 2 * c.l.halo;
+    a.cy = kNW * R - 2 * c.l.halo;
     const int64_t tx = (g.nx + a.cx - 1) / a.cx, ty = (g.ny + a.cy - 1) / a.cy;
     if (tx * ty > 0x7ffffff0LL) return hipErrorInvalidValue;
     a.tx = (int)tx;
@@ -489,10 +513,7 @@ hipError_t run(const Grid2dArgs &g, const Choice &c, hipStream_t stream)
     a.gs = (T)g.gs;
     a.gn = (T)g.gn;
     T *bufs[2] = {static_cast<T *>(g.u), static_cast<T *>(g.work)};
-    // an even number of launches leaves the result in u; the levels are
-    // spread evenly over them
-    int64_t launches = (g.nsteps + c.depth - 1) / c.depth;
-    if ((launches & 1) && g.nsteps > launches) ++launches;
+    const int64_t launches = c.l.n;
     int64_t done = 0;
     const dim3 grid((unsigned)(((int64_t)a.ntiles + 7) / 8 * 8));
     for (int64_t i = 0; i < launches; ++i) {
