@@ -16,7 +16,7 @@
 // The last runs beside the others, on a stream of the plan.  Every point
 // gets the operations ge_step_n gives it: the same bits.
 //
-// Measured: 4096 FP32 rods of 256 to 65536 points, 2000 levels, 11.9 ms (8.1e12
+// Measured: 4096 FP32 rods of 256 to 65536 points, 2000 levels, 11.0 ms (8.7e12
 // updates/s; VALU issue binds, 5 instructions a point and the halos' recompute;
 // 12.6 in the persistent form); 1024 FP64 rods of 4096 points, 64 levels, 40 us
 // (120); the 149 rods above, 41 levels, 50 us (135); 768 FP32 rods of 1565

@@ -200,7 +200,20 @@ __device__ __forceinline__ void sweep_plain(const TileArgs &a, int tid, int64_t 
                 increment_level<T, K, SRC, P, OPEN, OPEN>(u, B, (T)an, xl[0], xl[E - 1], xr[0], xr[E - 1],
                                                     cf, cl, pl, cr, pr);
             };
-            if constexpr (!SRC) level(b);
+            // An open window without a source takes the same operations from
+            // pair_level, whose registers spread evenly over the four banks
+            // where increment_level's lean on one: 1.18 instructions a SIMD
+            // and 4 cycles, by two waves at once, against 1.04 (2^24 points,
+            // 2000 levels 3.86 ms against 4.47; 5e7 points, 192 levels 1.07
+            // against 1.26; 4096 rods 11.0 against 11.8).
+            if constexpr (!SRC && OPEN) {
+                const PairCoef<T> pc{cf.c1, cf.c2, cf.cs, T(0), T(0), T(0)};
+                FluxTap none{false, 0.0, 0.0, 0.0, 0.0};
+                T e[K];
+                pair_level<T, K, 0, false, P, true, false>(
+                    u, e, b, T(0), T(0), xl[0], xl[E - 1], xr[0], xr[E - 1], T(0), T(0), T(0), T(0),
+                    pc, T(0), WallLevel<T>{false, T(0)}, none);
+            } else if constexpr (!SRC) level(b);
             else if constexpr (P == 0) level(B0);
             else level(B1);
         }
