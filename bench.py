@@ -66,11 +66,11 @@ VALU_LANE_OPS_BY_PREC = {"fp64": VALU_LANE_OPS, "fp32": 2 * VALU_LANE_OPS,
 # fma, 3), and Kahan's add (4).  VALU_PER_UPDATE: the instructions the kernels'
 # form takes, the basis of the labelled instruction floor: FP64 in two stages
 # 3 (the explicit right-hand side over the other parity's pairs, half the
-# difference and one FMA a point; the 2 x 2 solve likewise), FP32 4 (the two
-# differences and u + c1 (D_i + cs D_q) in two FMAs).
+# difference and one FMA a point; the 2 x 2 solve likewise), FP32 5 (the two
+# differences, the increment in two and its addition).
 FLOPS_PER_UPDATE = {"fp64": 6, "fp32": 6, "fp32c": 12}
 FLOPS_SRC = 2
-VALU_PER_UPDATE = {"fp64": 3, "fp32": 4, "fp32c": 11}
+VALU_PER_UPDATE = {"fp64": 3, "fp32": 5, "fp32c": 11}
 VALU_SRC = 1
 BYTES_PER_POINT = {"fp64": 8, "fp32": 4, "fp32c": 8}
 PROFILE_TRAFFIC = os.path.join(ROOT, "profiles", "moving_wall_c5_fp64_traffic.md")

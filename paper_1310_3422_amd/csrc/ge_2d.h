@@ -1,7 +1,7 @@
-// Two-dimensional extension (ge_2d.hip): launches of `depth` levels (then
-// single levels for the rest), each level the x-level of every row then the
-// y-level of every column, ping-ponging between u and work; after an odd
-// number of launches the result is copied back into u.
+// Two-dimensional extension (ge_2d.hip): launches of at most `depth` levels,
+// the call's levels spread evenly over them, each level the x-level of every
+// row then the y-level of every column, ping-ponging between u and work; after
+// an odd number of launches the result is copied back into u.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>

@@ -32,9 +32,9 @@
 // stage.  Every point gets the same operations whatever the window, its rows
 // and the levels per launch, so none of them changes a bit.
 //
-// Measured, 96 levels: 4096 x 4096 points FP64 1.01 ms (1.74 when a wave held
+// Measured, 96 levels: 4096 x 4096 points FP64 0.98 ms (1.76 when a wave held
 // its tile alone, two columns by 36 rows a lane and four levels per launch),
-// FP32 0.66 (1.16); 196 x 578 FP64 80 us (426).  VALU issue (6 instructions a
+// FP32 0.68 (1.07); 196 x 578 FP64 71 us (416), FP32 71 (349).  VALU issue (6 instructions a
 // point and level, 11 lane moves to 16 of them) and the halo's recompute bind
 // large grids, one window's level latency small ones.
 #include <hip/hip_runtime.h>

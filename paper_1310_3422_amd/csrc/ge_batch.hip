@@ -5,12 +5,15 @@
 // (largest first).  A task is a bundle of rods that share a points-per-lane
 // choice K; each rod owns a contiguous range of the workgroup's waves and is
 // held entirely in registers for all levels, so a rod is read and written
-// once per launch.  Per level the waves of a rod exchange their edge values
-// through LDS (one workgroup barrier per level) and the per-point update is
+// once per launch.  The waves of a rod exchange their edge values through LDS,
+// every level (at a workgroup barrier, or by flags between neighbours) or, where
+// they overlap, every K - 1 levels, and the per-point update is
 // the shared one (ge_level.h), so every rod evolves bit for bit as it
 // does through ge_step_n.  The queue counter is reset by a kernel node, and
 // the reset and the sweep are captured in a hipGraph that later calls
-// replay.
+// replay.  This form runs where a caller names an exchange (sync 1 to 3) and
+// for ge_solve_batch_static; other runs are split into windows
+// (ge_batch_windows.hip).
 #include <algorithm>
 #include <cmath>
 #include <cstdarg>

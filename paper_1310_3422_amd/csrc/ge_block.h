@@ -1,5 +1,5 @@
 // A window of overlapping waves, shared by the single-rod kernel (ge_block.hip)
-// and, for FP64 and FP32, the batch kernels (ge_batch_windows.hip).
+// and the batch kernels (ge_batch_windows.hip).
 //
 // The waves of a window overlap by 2 h points (h = kBlockOverlap) and advance
 // h - 1 levels on their own, each with open edges, before they refresh what

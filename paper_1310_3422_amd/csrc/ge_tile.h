@@ -201,11 +201,12 @@ __device__ __forceinline__ void sweep_plain(const TileArgs &a, int tid, int64_t 
                                                     cf, cl, pl, cr, pr);
             };
             // An open window without a source takes the same operations from
-            // pair_level, whose registers spread evenly over the four banks
-            // where increment_level's lean on one: 1.18 instructions a SIMD
-            // and 4 cycles, by two waves at once, against 1.04 (2^24 points,
-            // 2000 levels 3.86 ms against 4.47; 5e7 points, 192 levels 1.07
-            // against 1.26; 4096 rods 11.0 against 11.8).
+            // pair_level, of which a SIMD issues 1.18 in 4 cycles, two waves at
+            // once, against 1.04 of increment_level (2^24 points, 2000 levels
+            // 3.86 ms against 4.47; 5e7 points, 192 levels 1.07 against 1.26;
+            // 4096 rods 11.0 against 11.8).  The instructions are the same; half
+            // of increment_level's results here fall into one of the four
+            // register banks, where pair_level's are spread evenly.
             if constexpr (!SRC && OPEN) {
                 const PairCoef<T> pc{cf.c1, cf.c2, cf.cs, T(0), T(0), T(0)};
                 FluxTap none{false, 0.0, 0.0, 0.0, 0.0};

@@ -279,9 +279,10 @@ def unpack_state(u, n, precision):
 
 
 class Batch:
-    """A ge_batch plan: independent rods advanced together in one persistent,
-    graph-captured launch.  Host arrays describe the rods; the packed state
-    lives in a device tensor (see ``pack_batch_state``)."""
+    """A ge_batch plan: independent rods advanced together, cut into windows
+    over the chip (sync = 0) or held by persistent workgroups in one
+    graph-captured launch (sync = 1 to 3).  Host arrays describe the rods; the
+    packed state lives in a device tensor (see ``pack_batch_state``)."""
 
     def __init__(self, n, offsets, r, g_left, g_right, precision="fp32", tune=False, sync=0):
         self.n = np.ascontiguousarray(n, dtype=np.int64)
